@@ -189,7 +189,7 @@ int rtdm_default_options(rtdm_options *opt);
  *   RTDM_RUN_REAL   outputs per row run of the real b = 13 step products (1 to 4, or 8; default 2)
  *   RTDM_RUN_CPLX   the same for the complex ones (1 to 4; default 2)
  *   RTDM_RUN_B4     b = 4 products over row runs of 16 outputs (16, default) or per-output lists (1)
- *   RTDM_ROW_TILE   rows per output tile of the b = 13 processing order (default 256)
+ *   RTDM_ROW_TILE   rows per output tile of the b = 13 processing order (default 512)
  * A run length outside these values fails with RTDM_E_ARG. */
 int rtdm_create(rtdm_ctx **out, int hip_device, const rtdm_options *opt);
 

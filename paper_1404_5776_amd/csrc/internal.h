@@ -169,6 +169,13 @@ void launch_run_fill(hipStream_t s, int64_t nch, const int32_t *run_row, const i
 // operand's op(B)[m][r] at m*B + r (conj_b: conjugated) and the output written
 // column-major if out_col_major.  b = 13, FP64.
 void launch_spgemm_cm(hipStream_t s, const SpgemmArgs &a, int conj_b, int out_col_major);
+// b = 13 FP64 product over segmented row runs of 2 with both operands in pair
+// layout (launch_pack_pairs): op(B) from right pairs, or with conj_b from the
+// left pairs of the conjugate-transposed matrix; out_pairs: the output as left pairs.
+void launch_spgemm_pairs(hipStream_t s, const SpgemmArgs &a, int conj_b, int out_pairs);
+// Pair layout of every 13 x 13 block: left pairs, right pairs, or row-major from left pairs.
+enum { kPackLeft = 0, kPackRight = 1, kUnpackLeft = 2 };
+void launch_pack_pairs(hipStream_t s, int64_t nblocks, int mode, const double *in, double *out);
 // Split-precision (BF16X3 / FP16X2) step product of real operands: column-
 // major left operand, row-major right operand, row-major FP64 output.
 void launch_spgemm_cm_split(hipStream_t s, const SpgemmArgs &a);

@@ -314,6 +314,13 @@ struct rtdm_ctx {
     // of S for the inverse iteration
     Mat Xc, Ac, Uc, Wc, Sc;
     bool Xc_valid = false, W_in_cm = false;
+    // b = 13 products with FP64 products over segmented runs of 2 read their
+    // operands in pair layout (launch_spgemm_pairs): Xc, Sc (pairs_real), Uc and
+    // Wc (pairs_cplx) then hold left pairs, Ap those of A (Ac stays the
+    // column-major copy the reduced-precision Taylor terms read), Bp the right
+    // pairs of the right operand of the product being issued
+    bool pairs_real = false, pairs_cplx = false;
+    Mat Ap, Bp;
     // FP32 copies for the reduced-precision Taylor terms (b = 13)
     DBuf<float> Ac32, tau32[2], zero32;
     DBuf<double> scratch;       // block inverse scratch and staging
@@ -361,7 +368,7 @@ struct rtdm_ctx {
     double graph_dt = 0.0;
     bool graph_rebuilds_u = false;
     // launch shape of the step products
-    int wpb = 16, row_tile = 256;   // row tile of the b = 13 processing order (measured best with the XCD deal)
+    int wpb = 16, row_tile = 512;   // row tile of the b = 13 processing order (256 -> 512: A tau 16.2 -> 15.8 ms, 4,096 atoms)
     int run_real = 2, run_cplx = 2;   // b = 13 step products: outputs per row run (1: single outputs)
     int run_b4 = 16;                  // b = 4 FP64 products: outputs per row run (1: single outputs)
     int inv_iters_total = 0, inv_fell_back = 0;
@@ -740,10 +747,17 @@ void product_key(rtdm_ctx *c, int prod, const std::tuple<int, int, int, int, int
 
 bool is_split(int prec) { return prec == RTDM_PREC_BF16X3 || prec == RTDM_PREC_FP16X2; }
 
+bool complex_kind(int prod) { return prod == RTDM_PROD_UK || prod == RTDM_PROD_WU; }
+
+// Whether the column-major copies of this kind's products are left pairs (and
+// its right operands right pairs): fixed when the ranges are set.
+bool pairs_kind(const rtdm_ctx *c, int prod) { return complex_kind(prod) ? c->pairs_cplx : c->pairs_real; }
+
 // Step product with the column-major copy Acm of the left operand (see
-// launch_spgemm_cm); same schedule, timing and flop accounting as product().
+// launch_spgemm_cm), or with both operands in pair layout (`pairs`, see
+// launch_spgemm_pairs); same schedule, timing and flop accounting as product().
 void product_cm(rtdm_ctx *c, int prod, const Mat &Acm, const Mat &B, Mat &C, int conj_b, int out_cm,
-                double alr, hipStream_t s)
+                double alr, hipStream_t s, bool pairs)
 {
     Sched &S = schedule(c, prod);
     auto key = prod_key(c, prod);
@@ -795,6 +809,7 @@ void product_cm(rtdm_ctx *c, int prod, const Mat &Acm, const Mat &B, Mat &C, int
     }
     auto go = [&]() {
         if (split) launch_spgemm_cm_split(s, a);
+        else if (pairs) launch_spgemm_pairs(s, a, conj_b, out_cm);
         else launch_spgemm_cm(s, a, conj_b, out_cm);
     };
     if (c->timing && !c->capturing) {
@@ -816,6 +831,44 @@ void transpose_into(rtdm_ctx *c, const Mat &M, Mat &out, hipStream_t s)
     const int64_t nb = c->pats[M.pat]->nnzb;
     launch_transpose_blocks(s, nb, c->b, M.re.p, out.re.p);
     if (M.cplx) launch_transpose_blocks(s, nb, c->b, M.im.p, out.im.p);
+}
+
+// M in pair layout (both planes).
+void pack_into(rtdm_ctx *c, const Mat &M, Mat &out, int mode, hipStream_t s)
+{
+    const int64_t nb = c->pats[M.pat]->nnzb;
+    launch_pack_pairs(s, nb, mode, M.re.p, out.re.p);
+    if (M.cplx) launch_pack_pairs(s, nb, mode, M.im.p, out.im.p);
+}
+
+// The copy of a left operand that products of kind `prod` read.
+void left_copy(rtdm_ctx *c, int prod, const Mat &M, Mat &out, hipStream_t s)
+{
+    if (pairs_kind(c, prod)) pack_into(c, M, out, kPackLeft, s);
+    else transpose_into(c, M, out, s);
+}
+
+// The right pairs of M, in Bp (valid until the next call).
+const Mat &right_pairs(rtdm_ctx *c, const Mat &M, hipStream_t s)
+{
+    c->Bp.pat = M.pat;
+    c->Bp.cplx = M.cplx;
+    pack_into(c, M, c->Bp, kPackRight, s);
+    return c->Bp;
+}
+
+// The right operand of a product of kind `prod`: M itself or its right pairs.
+const Mat &right_copy(rtdm_ctx *c, int prod, const Mat &M, hipStream_t s)
+{
+    return pairs_kind(c, prod) ? right_pairs(c, M, s) : M;
+}
+
+// Whether the products of kind `prod` have segmented runs of 2.
+bool runs_of_2(rtdm_ctx *c, int prod)
+{
+    auto &R = schedule(c, prod).runs;
+    auto r = R.find(2);
+    return r != R.end() && r->second->nch > 0 && r->second->seg.p;
 }
 
 bool use_cm(rtdm_ctx *c) { return c->b == 13 && (c->prec == RTDM_PREC_FP64 || c->prec == RTDM_PREC_FP32); }
@@ -990,14 +1043,16 @@ void build_propagator(rtdm_ctx *c, double dt, hipStream_t s)
             const bool split_cm = c->b == 13 && is_split(c->prec) &&
                                   (c->opt.precision == RTDM_PREC_BF16X3_TAYLOR ||
                                    c->opt.precision == RTDM_PREC_FP16X2_TAYLOR);
-            if (use_cm(c) || split_cm) product_cm(c, RTDM_PROD_AT, c->Ac, src, dst, 0, 0, dt / k, s);
+            if (c->pairs_real && c->prec == RTDM_PREC_FP64)
+                product_cm(c, RTDM_PROD_AT, c->Ap, right_copy(c, RTDM_PROD_AT, src, s), dst, 0, 0, dt / k, s, true);
+            else if (use_cm(c) || split_cm) product_cm(c, RTDM_PROD_AT, c->Ac, src, dst, 0, 0, dt / k, s, false);
             else product(c, RTDM_PROD_AT, A, src, dst, dt / k, 0.0, s);
             c->prec = saved;
             add_term(k, dst.re.p, nullptr);
         }
         cur = 1 - cur;
     }
-    if (use_cm(c)) transpose_into(c, U, c->Uc, s);
+    if (use_cm(c)) left_copy(c, RTDM_PROD_UK, U, c->Uc, s);
 }
 
 // D = P_P(U^dagger P_P(S U)) - S; sums into c->unit_sums.
@@ -1491,6 +1546,25 @@ int rtdm_set_ranges(rtdm_ctx *c, double R_hs, double R_p, double R_k)
         }
         c->u_copies_valid = false;
     }
+    {
+        // pair layout where every product of the kind runs over segmented runs of 2 (FP64 products only)
+        auto runs2 = [&](int prod) { return runs_of_2(c, prod); };
+        const bool fp64 = c->b == 13 && all_products_prec(c) == RTDM_PREC_FP64;
+        c->pairs_real = fp64 && c->run_real == 2 && runs2(RTDM_PROD_XH) && runs2(RTDM_PROD_AT) && runs2(RTDM_PROD_SX);
+        c->pairs_cplx = fp64 && c->run_cplx == 2 && runs2(RTDM_PROD_UK) && runs2(RTDM_PROD_WU);
+        c->Ap.re.release();
+        c->Bp.re.release();
+        c->Bp.im.release();
+        if (c->pairs_real) {
+            c->Ap.pat = c->range_pat[R_P];
+            c->Ap.re.alloc(elems(c, c->Ap));
+        }
+        if (c->pairs_real || c->pairs_cplx) {
+            const int64_t ne = std::max({pat_of(c, R_HS).nnzb, pat_of(c, R_P).nnzb, pat_of(c, R_K).nnzb}) * 169;
+            c->Bp.re.alloc(ne);
+            if (c->pairs_cplx) c->Bp.im.alloc(ne);
+        }
+    }
     // the unitarity product too when steps check it, so that rtdm_step allocates nothing
     if (c->opt.unit_check_every > 0) schedule(c, RTDM_PROD_UV);
     RT_HIP(hipDeviceSynchronize());
@@ -1665,7 +1739,8 @@ int rtdm_download(rtdm_ctx *c, rtdm_mat mat, void *dst, int is_device, void *str
     Mat &M = mat == RTDM_MAT_K ? kmat(c, c->kick_sel) : c->mats[mat];
     const int64_t ne = elems(c, M);
     if (mat == RTDM_MAT_W && c->W_in_cm) {             // the step keeps W column-major
-        transpose_into(c, c->Wc, M, s);
+        if (c->pairs_cplx) pack_into(c, c->Wc, M, kUnpackLeft, s);
+        else transpose_into(c, c->Wc, M, s);
         c->W_in_cm = false;
     }
     RT_CHECK(!(c->mixed && is_device), RTDM_E_UNSUPPORTED, "device downloads need equal block sizes");
@@ -1761,7 +1836,7 @@ int rtdm_build_inverse(rtdm_ctx *c, void *stream, int *iters, double *residual)
     // nothing) for the whole iteration, of X per iteration.
     const bool cm = use_cm(c);
     Mat &Sc = c->Sc;
-    if (cm) transpose_into(c, S, Sc, s);
+    if (cm) left_copy(c, RTDM_PROD_SX, S, Sc, s);
     // X moves between buffers below and Xc is used as scratch: a captured step
     // that reads either must be captured again
     drop_graph(c);
@@ -1770,9 +1845,10 @@ int rtdm_build_inverse(rtdm_ctx *c, void *stream, int *iters, double *residual)
         std::vector<double> res;
         for (int k = 0; k < c->opt.inv_max_iter; ++k) {
             if (cm) {
-                product_cm(c, RTDM_PROD_SX, Sc, X, c->Wh, 0, 0, 1.0, s);  // W = P_P(S X)
-                transpose_into(c, X, c->Xc, s);
-                product_cm(c, RTDM_PROD_AT, c->Xc, c->Wh, c->Xn, 0, 0, 1.0, s);   // P_P(X W)
+                const bool pr = c->pairs_real;
+                product_cm(c, RTDM_PROD_SX, Sc, right_copy(c, RTDM_PROD_SX, X, s), c->Wh, 0, 0, 1.0, s, pr);  // W = P_P(S X)
+                left_copy(c, RTDM_PROD_AT, X, c->Xc, s);
+                product_cm(c, RTDM_PROD_AT, c->Xc, right_copy(c, RTDM_PROD_AT, c->Wh, s), c->Xn, 0, 0, 1.0, s, pr);  // P_P(X W)
             } else {
                 product(c, RTDM_PROD_SX, S, X, c->Wh, 1.0, 0.0, s);       // W = P_P(S X)
                 product(c, RTDM_PROD_AT, X, c->Wh, c->Xn, 1.0, 0.0, s);   // P_P(X W)
@@ -1837,7 +1913,7 @@ int rtdm_build_inverse(rtdm_ctx *c, void *stream, int *iters, double *residual)
     c->X_valid = (st == 1);
     c->Xc_valid = false;
     if (cm && st == 1) {
-        transpose_into(c, X, c->Xc, s);   // the column-major copy of the converged X
+        left_copy(c, RTDM_PROD_XH, X, c->Xc, s);   // the column-major copy of the converged X
         c->Xc_valid = true;
     }
     c->U_valid = false;
@@ -1901,7 +1977,7 @@ bool a_from_a0(const rtdm_ctx *c)
 void ensure_xc(rtdm_ctx *c, hipStream_t s)
 {
     if (c->b != 13 || c->Xc_valid || !c->Xc.re.p) return;
-    transpose_into(c, c->mats[RTDM_MAT_X], c->Xc, s);
+    left_copy(c, RTDM_PROD_XH, c->mats[RTDM_MAT_X], c->Xc, s);
     c->Xc_valid = true;
 }
 
@@ -1915,7 +1991,7 @@ void ensure_a0(rtdm_ctx *c, hipStream_t s)
     c->prec = RTDM_PREC_FP64;
     if (use_cm(c)) {
         ensure_xc(c, s);
-        product_cm(c, RTDM_PROD_XH, c->Xc, H0, c->A0, 0, 0, 1.0, s);
+        product_cm(c, RTDM_PROD_XH, c->Xc, right_copy(c, RTDM_PROD_XH, H0, s), c->A0, 0, 0, 1.0, s, c->pairs_real);
     } else {
         product(c, RTDM_PROD_XH, X, H0, c->A0, 1.0, 0.0, s);
     }
@@ -1923,7 +1999,16 @@ void ensure_a0(rtdm_ctx *c, hipStream_t s)
     c->A0_valid = true;
 }
 
-// A = P_P(X H(t + theta dt)) (and its column-major copy on the b = 13 path).
+// The copies of A that the Taylor terms read on the b = 13 path: left pairs
+// for the FP64 ones, column-major for the reduced-precision ones (or both).
+void copy_a(rtdm_ctx *c, hipStream_t s)
+{
+    const Mat &A = c->mats[RTDM_MAT_A];
+    if (c->pairs_real) pack_into(c, A, c->Ap, kPackLeft, s);
+    if (!c->pairs_real || c->opt.precision != RTDM_PREC_FP64) transpose_into(c, A, c->Ac, s);
+}
+
+// A = P_P(X H(t + theta dt)) (and its copies on the b = 13 path).
 void make_a(rtdm_ctx *c, double theta, bool corr, hipStream_t s)
 {
     Mat &H = c->mats[RTDM_MAT_H], &X = c->mats[RTDM_MAT_X], &A = c->mats[RTDM_MAT_A];
@@ -1933,17 +2018,17 @@ void make_a(rtdm_ctx *c, double theta, bool corr, hipStream_t s)
         launch_a_onsite(s, pp.nnzb, c->b, pp.d_col.p, c->mixed ? c->d_nbf.p : nullptr, c->opt.h_gain, c->q_cur,
                         theta, corr ? c->q_c.p : c->q_cur, corr ? c->q_cur : c->q_prev, c->q_ref.p, c->A0.re.p,
                         X.re.p, A.re.p);
-        if (use_cm(c)) transpose_into(c, A, c->Ac, s);
+        if (use_cm(c)) copy_a(c, s);
         return;
     }
     build_h(c, theta, corr, s);
     if (use_cm(c)) {
         if (!c->Xc_valid) {
-            transpose_into(c, X, c->Xc, s);
+            left_copy(c, RTDM_PROD_XH, X, c->Xc, s);
             c->Xc_valid = true;
         }
-        product_cm(c, RTDM_PROD_XH, c->Xc, H, A, 0, 0, 1.0, s);
-        transpose_into(c, A, c->Ac, s);
+        product_cm(c, RTDM_PROD_XH, c->Xc, right_copy(c, RTDM_PROD_XH, H, s), A, 0, 0, 1.0, s, c->pairs_real);
+        copy_a(c, s);
     } else {
         product(c, RTDM_PROD_XH, X, H, A, 1.0, 0.0, s);
     }
@@ -1968,7 +2053,7 @@ void build_u(rtdm_ctx *c, double dt, bool corr, hipStream_t s)
         build_propagator(c, 0.5 * dt, s);
         product(c, RTDM_PROD_AT, U, c->E1, c->E2, 1.0, 0.0, s);
         copy_mat(c, c->E2, U, s);
-        if (use_cm(c)) transpose_into(c, U, c->Uc, s);
+        if (use_cm(c)) left_copy(c, RTDM_PROD_UK, U, c->Uc, s);
         break;
     case RTDM_PROP_M4: {
         // M = -i dt/2 (A1 + A2) - (sqrt(3) dt^2 / 12) (P(A2 A1) - P(A1 A2)), U = sum_n M^n / n!
@@ -2000,7 +2085,7 @@ void build_u(rtdm_ctx *c, double dt, bool corr, hipStream_t s)
             launch_axpby(s, ne, 1.0, U.im.p, 1.0, next.im.p, U.im.p);
             prev = &next;
         }
-        if (use_cm(c)) transpose_into(c, U, c->Uc, s);
+        if (use_cm(c)) left_copy(c, RTDM_PROD_UK, U, c->Uc, s);
         break;
     }
     default: throw Error(RTDM_E_ARG, "unknown propagator");
@@ -2021,7 +2106,7 @@ void ensure_u_copies(rtdm_ctx *c, hipStream_t s)
     Mat &U = c->mats[RTDM_MAT_U];
     const int saved = c->prec;
     c->prec = all_products_prec(c);
-    if (use_cm(c)) transpose_into(c, U, c->Uc, s);
+    if (use_cm(c)) left_copy(c, RTDM_PROD_UK, U, c->Uc, s);
     c->prec = saved;
     if (c->Uh_on) {
         const Pattern &pp = pat_of(c, R_P);
@@ -2052,8 +2137,9 @@ void step_body(rtdm_ctx *c, double dt, bool rebuild_u, int passes, hipStream_t s
                 c->U_dt = dt;
             }
             if (use_cm(c)) {
-                product_cm(c, RTDM_PROD_UK, c->Uc, K, c->Wc, 0, 1, 1.0, s);     // W, column-major
-                product_cm(c, RTDM_PROD_WU, c->Wc, c->Uc, c->Kn, 1, 0, 1.0, s); // B = U^dagger
+                const bool pc = c->pairs_cplx;
+                product_cm(c, RTDM_PROD_UK, c->Uc, right_copy(c, RTDM_PROD_UK, K, s), c->Wc, 0, 1, 1.0, s, pc);  // W, column-major
+                product_cm(c, RTDM_PROD_WU, c->Wc, c->Uc, c->Kn, 1, 0, 1.0, s, pc);                             // B = U^dagger
                 c->W_in_cm = true;
             } else {
                 product(c, RTDM_PROD_UK, U, K, W, 1.0, 0.0, s);
@@ -2862,10 +2948,12 @@ int rtdm_autotune(rtdm_ctx *c, void *stream, int *wpb_out, int *tile_out)
             set_row_tile(c, tile);
             for (int w : wpbs) {
                 c->wpb = w;
-                product_cm(c, RTDM_PROD_UK, c->Uc, c->mats[RTDM_MAT_K], c->Wc, 0, 1, 1.0, s);   // warm-up
+                const Mat &Kr = right_copy(c, RTDM_PROD_UK, c->mats[RTDM_MAT_K], s);
+                product_cm(c, RTDM_PROD_UK, c->Uc, Kr, c->Wc, 0, 1, 1.0, s, c->pairs_cplx);   // warm-up
                 RT_HIP(hipEventRecord(e0, s));
-                product_cm(c, RTDM_PROD_UK, c->Uc, c->mats[RTDM_MAT_K], c->Wc, 0, 1, 1.0, s);
-                product_cm(c, RTDM_PROD_AT, c->Ac, c->tau[0], c->tau[1], 0, 0, 1.0, s);
+                product_cm(c, RTDM_PROD_UK, c->Uc, Kr, c->Wc, 0, 1, 1.0, s, c->pairs_cplx);
+                product_cm(c, RTDM_PROD_AT, c->pairs_real ? c->Ap : c->Ac, c->tau[0], c->tau[1], 0, 0, 1.0, s,
+                           c->pairs_real);
                 RT_HIP(hipEventRecord(e1, s));
                 RT_HIP(hipEventSynchronize(e1));
                 float ms = 0.0f;
@@ -3102,17 +3190,27 @@ void multiply(rtdm_ctx *c, rtdm_mat Cm, rtdm_mat Am, rtdm_mat Bm, int op_a, int 
                 if (op_b) alloc_like(c, Bcm, B);
                 if (ccm) alloc_like(c, Ccm, C);
             }
-            transpose_into(c, A, *pa, s);
+            // pair layout as in a step; the static scratch holds no right pairs, so the call without
+            // allocations keeps the column-major copies
+            const bool pairs = !scratch && (A.cplx || B.cplx ? c->pairs_cplx : c->pairs_real) && runs_of_2(c, prod);
+            auto left = [&](const Mat &M, Mat &out) {
+                if (pairs) pack_into(c, M, out, kPackLeft, s);
+                else transpose_into(c, M, out, s);
+            };
+            left(A, *pa);
             const Mat *Bp = &B;
             if (op_b) {
-                transpose_into(c, B, *pb, s);
+                left(B, *pb);
                 Bp = pb;
+            } else if (pairs) {
+                Bp = &right_pairs(c, B, s);
             }
             if (ccm) {
-                product_cm(c, prod, *pa, *Bp, *pc, op_b, 1, alr, s);
-                transpose_into(c, *pc, C, s);
+                product_cm(c, prod, *pa, *Bp, *pc, op_b, 1, alr, s, pairs);
+                if (pairs) pack_into(c, *pc, C, kUnpackLeft, s);
+                else transpose_into(c, *pc, C, s);
             } else {
-                product_cm(c, prod, *pa, *Bp, C, op_b, 0, alr, s);
+                product_cm(c, prod, *pa, *Bp, C, op_b, 0, alr, s, pairs);
             }
             if (!scratch) RT_HIP(hipStreamSynchronize(s));   // the copies are freed on return
         } else {

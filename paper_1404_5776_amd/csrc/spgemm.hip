@@ -591,6 +591,226 @@ __global__ __launch_bounds__(256, MINW) void k_spgemm_q4j(
     }
 }
 
+// Pair layout of b x b operand blocks: element (x, m) of a block, m the
+// contraction index, sits at (m / 2) * 2b + 2x + (m & 1), so that the two
+// values a lane feeds to two consecutive MFMA steps are 16 contiguous bytes
+// (an odd b's last m has x alone: b (b - 1) + x).  "Left" pairs hold a left
+// operand (x the row, m the column), "right" pairs a right operand (x the
+// column, m the row).  A block keeps its b * b doubles.
+__device__ __host__ inline int pair_at(int b, int x, int m)
+{
+    return (b & 1) && m == b - 1 ? b * (b - 1) + x : (m >> 1) * 2 * b + 2 * x + (m & 1);
+}
+
+// Row runs of 2 (k_spgemm_q4j's dataflow, segments and order of the products)
+// on operands in pair layout.  Bound: at b = 13 the row-run products were held
+// by the vector-memory address unit, which takes 15 cycles for a wave's
+// 8-byte load and the same 15 for a 16-byte one, aligned or not (measured from
+// L1 and L2); it was busy 97 % of the real kernel's cycles with the matrix
+// cores busy 52 %.  The pair layout brings two contraction steps per load:
+// 7 loads per operand block instead of 13.  Lanes 13..15 of a row group read
+// row 12 again: they only feed rows and columns of the tile that are not
+// stored.  What holds it now is the service of L2 misses: three waves per
+// SIMD with up to 168 registers (more loads of one wave in flight, fewer
+// outputs sharing an L2) beat four by 8 % and five by 18 % on the real
+// product.  4,096 atoms, R 16, ms per launch, 8-byte loads at four waves ->
+// now: A tau 19.9 -> 15.8, U K 49.7 -> 45.8, W U^dagger 48.3 -> 45.7.
+// OUT: 0 row-major output, 1 left pairs.
+typedef double pd2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef __attribute__((address_space(1))) const pd2 gpd2;
+template <int B, bool AC, bool BC, int CJB, int OUT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_spgemm_q4p(
+    int64_t nch, const int64_t *__restrict__ off, const int32_t *__restrict__ ea,
+    const int32_t *__restrict__ eb, const int32_t *__restrict__ cout,
+    const double *__restrict__ ar, const double *__restrict__ ai, const double *__restrict__ br,
+    const double *__restrict__ bi, double *__restrict__ cr, double *__restrict__ ci, double alr,
+    double ali, const double *__restrict__ zero, const int32_t *__restrict__ order, int remap,
+    const int32_t *__restrict__ seg)
+{
+    static_assert(B >= 5 && B <= 15 && (B & 1), "odd block sizes");
+    constexpr int BB = B * B, NJ = 2;
+    const int lane = threadIdx.x & 63;
+    const int64_t w = xcd_block((nch + 3) / 4, remap) * 4 + (threadIdx.x >> 6);
+    if (w >= nch) return;                      // uniform across the wave
+    const int64_t c = order ? (int64_t)order[w] : w;
+    const int q = lane >> 4, r = min(lane & 15, B - 1);
+    const int64_t e0 = off[c];
+    const int ne = (int)(off[c + 1] - e0);
+    typedef Mfma16<double>::acc_t acc_t;
+    acc_t rr[NJ], ri[NJ], ir[NJ];
+#pragma unroll
+    for (int t = 0; t < NJ; ++t) rr[t] = ri[t] = ir[t] = acc_t{0, 0, 0, 0};
+    const gdouble *gz = (const gdouble *)zero;
+    // block indices of the group about to run, loaded one group ahead (the
+    // group after a segment's last is the next segment's first)
+    int na = 0, nb[NJ] = {0, 0};
+    auto fetch = [&](int g) {
+        const int64_t e = e0 + min(g + q, ne - 1);
+        na = ea[e];
+#pragma unroll
+        for (int t = 0; t < NJ; ++t) nb[t] = eb[e * NJ + t];
+    };
+    if (ne > 0) fetch(0);
+    auto groups = [&](int gb, int ge, auto act) {
+        constexpr int ACT = decltype(act)::value;
+        for (int g = gb; g < ge; g += 4) {
+            const gdouble *pa = gz, *pai = gz;
+            const gdouble *pb[NJ], *pbi[NJ];
+#pragma unroll
+            for (int t = 0; t < NJ; ++t) pb[t] = pbi[t] = gz;
+            if (g + q < ge) {
+                const int64_t oa = (int64_t)na * BB + 2 * r;
+                pa = (const gdouble *)(ar + oa);
+                if (AC) pai = (const gdouble *)(ai + oa);
+#pragma unroll
+                for (int t = 0; t < NJ; ++t) {
+                    if (!((ACT >> t) & 1)) continue;
+                    const int64_t ob = (int64_t)nb[t] * BB + 2 * r;   // present: segmented entries
+                    pb[t] = (const gdouble *)(br + ob);
+                    if (BC) pbi[t] = (const gdouble *)(bi + ob);
+                }
+            }
+            fetch(min(g + 4, ge));
+            auto mma = [&](double xa, double xai, const double (&xb)[NJ], const double (&xbi)[NJ]) {
+                if constexpr (AC && BC) {
+                    // re += a_r b_r + (-s a_i) b_i, im += (s a_r) b_i + a_i b_r, s = -1 for a conjugated B
+                    const double nai = CJB ? xai : -xai, sar = CJB ? -xa : xa;
+#pragma unroll
+                    for (int t = 0; t < NJ; ++t) {
+                        if (!((ACT >> t) & 1)) continue;
+                        rr[t] = Mfma16<double>::step(xa, xb[t], rr[t]);
+                        ri[t] = Mfma16<double>::step(sar, xbi[t], ri[t]);
+                        rr[t] = Mfma16<double>::step(nai, xbi[t], rr[t]);
+                        ri[t] = Mfma16<double>::step(xai, xb[t], ri[t]);
+                    }
+                } else {
+#pragma unroll
+                    for (int t = 0; t < NJ; ++t) {
+                        if (!((ACT >> t) & 1)) continue;
+                        rr[t] = Mfma16<double>::step(xa, xb[t], rr[t]);
+                        if (BC) ri[t] = Mfma16<double>::step(xa, xbi[t], ri[t]);
+                        if (AC) ir[t] = Mfma16<double>::step(xai, xb[t], ir[t]);
+                    }
+                }
+            };
+#pragma unroll
+            for (int h = 0; h < B / 2; ++h) {
+                const pd2 xa = *(const gpd2 *)(pa + 2 * B * h);
+                const pd2 xai = AC ? *(const gpd2 *)(pai + 2 * B * h) : pd2{0, 0};
+                pd2 xb[NJ], xbi[NJ];
+#pragma unroll
+                for (int t = 0; t < NJ; ++t) {
+                    xb[t] = xbi[t] = pd2{0, 0};
+                    if (!((ACT >> t) & 1)) continue;
+                    xb[t] = *(const gpd2 *)(pb[t] + 2 * B * h);
+                    if (BC) xbi[t] = *(const gpd2 *)(pbi[t] + 2 * B * h);
+                }
+                const double b0[NJ] = {xb[0].x, xb[1].x}, b0i[NJ] = {xbi[0].x, xbi[1].x};
+                const double b1[NJ] = {xb[0].y, xb[1].y}, b1i[NJ] = {xbi[0].y, xbi[1].y};
+                mma(xa.x, xai.x, b0, b0i);
+                mma(xa.y, xai.y, b1, b1i);
+            }
+            {
+                const int o = B * (B - 1) - r;         // the last, unpaired contraction index
+                const double xa = pa[o], xai = AC ? pai[o] : 0.0;
+                double xb[NJ] = {0, 0}, xbi[NJ] = {0, 0};
+#pragma unroll
+                for (int t = 0; t < NJ; ++t) {
+                    if (!((ACT >> t) & 1)) continue;
+                    xb[t] = pb[t][o];
+                    if (BC) xbi[t] = pbi[t][o];
+                }
+                mma(xa, xai, xb, xbi);
+            }
+        }
+    };
+    const int nf = seg[2 * c], n0 = seg[2 * c + 1];   // uniform across the wave
+    groups(0, nf, std::integral_constant<int, 3>());
+    groups(nf, nf + n0, std::integral_constant<int, 1>());
+    groups(nf + n0, ne, std::integral_constant<int, 2>());
+    constexpr double sb = CJB ? -1.0 : 1.0;
+    const int col = lane & 15;
+#pragma unroll
+    for (int t = 0; t < NJ; ++t) {
+        const int p = cout[c * NJ + t];
+        if (p < 0) continue;                   // uniform: a short run
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int row = 4 * e + q;
+            if (row < B && col < B) {
+                const double re = rr[t][e];
+                const double im = (AC && BC) ? ri[t][e] : sb * ri[t][e] + ir[t][e];
+                const int64_t o = (int64_t)p * BB + (OUT ? pair_at(B, row, col) : row * B + col);
+                cr[o] = alr * re - ali * im;
+                if (ci) ci[o] = alr * im + ali * re;
+            }
+        }
+    }
+}
+
+// Blocks into pair layout (kPackLeft, kPackRight) or back (kUnpackLeft).
+__global__ __launch_bounds__(256) void k_pack_pairs13(int64_t n, int mode, const double *__restrict__ in,
+                                                      double *__restrict__ out)
+{
+    constexpr int B = 13, BB = B * B;
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
+        const int64_t p = e / BB;
+        const int w = (int)(e - p * BB);
+        // (x, m) of element w of the pair layout
+        const int x = w >= B * (B - 1) ? w - B * (B - 1) : (w % (2 * B)) >> 1;
+        const int m = w >= B * (B - 1) ? B - 1 : 2 * (w / (2 * B)) + (w & 1);
+        const int64_t rm = p * BB + (mode == kPackRight ? m * B + x : x * B + m);
+        if (mode == kUnpackLeft) out[rm] = in[e];
+        else out[e] = in[rm];
+    }
+}
+
+void launch_pack_pairs(hipStream_t s, int64_t nblocks, int mode, const double *in, double *out)
+{
+    const int64_t n = nblocks * 169;
+    if (n == 0) return;
+    const int64_t g = std::min<int64_t>((n + 255) / 256, 65536);
+    hipLaunchKernelGGL(k_pack_pairs13, dim3((unsigned)g), dim3(256), 0, s, n, mode, in, out);
+    RT_HIP(hipGetLastError());
+}
+
+template <bool AC, bool BC, int CJB, int OUT>
+static void launch_q4p(hipStream_t s, const SpgemmArgs &a)
+{
+    // Chunks of 128 workgroups per XCD from 16,384 workgroups on; below that
+    // they leave the last round of chunks nearly empty, and chunks of 32 are
+    // faster (512 atoms, 7,700 workgroups: U K 3.66 -> 3.42 ms; 1,000 atoms,
+    // 19,000 workgroups: 2.81 against 2.86 ms per real product)
+    const int remap = (a.nch + 3) / 4 < 16384 ? 32 : xcd_chunk();
+    const unsigned grid = xcd_grid((a.nch + 3) / 4, remap);
+    hipLaunchKernelGGL((k_spgemm_q4p<13, AC, BC, CJB, OUT>), dim3(grid), dim3(256), 0, s, a.nch,
+                       a.ch_off, a.ch_a, a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re,
+                       a.alpha_im, a.zero, a.ch_order, remap, a.ch_seg);
+}
+
+// Products over row runs of 2 with both operands in pair layout (b = 13, FP64;
+// a conjugated right operand U^dagger is the left pairs of U): conj_b,
+// out_pairs (the output as left pairs).
+void launch_spgemm_pairs(hipStream_t s, const SpgemmArgs &a, int conj_b, int out_pairs)
+{
+    RT_CHECK(a.b == 13 && a.precision == RTDM_PREC_FP64 && a.nj == 2 && a.nch > 0 && a.ch_seg && a.zero, RTDM_E_ARG,
+             "pair-layout products need b = 13, FP64 and segmented runs of 2");
+    const bool ac = a.ai != nullptr, bc = a.bi != nullptr;
+#define RT_Q4P(AC_, BC_)                                            \
+    do {                                                            \
+        if (conj_b && out_pairs) launch_q4p<AC_, BC_, 1, 1>(s, a);  \
+        else if (conj_b) launch_q4p<AC_, BC_, 1, 0>(s, a);          \
+        else if (out_pairs) launch_q4p<AC_, BC_, 0, 1>(s, a);       \
+        else launch_q4p<AC_, BC_, 0, 0>(s, a);                      \
+    } while (0)
+    if (ac && bc) RT_Q4P(true, true);
+    else if (ac) RT_Q4P(true, false);
+    else if (bc) RT_Q4P(false, true);
+    else RT_Q4P(false, false);
+#undef RT_Q4P
+    RT_HIP(hipGetLastError());
+}
+
 // b = 4: v_mfma_f64_4x4x4_4b_f64 runs four independent 4x4x4 products, one
 // per "MFMA block".  Each output block needs SUB real sub-products (1: real x
 // real; 2: one operand complex; 4: complex x complex: re*re, im*im, re*im,

@@ -1,0 +1,78 @@
+"""Products on re-laid-out operands against the oracle, element by element.
+
+The b = 13 FP64 row-run products read both operands in pair layout (two
+contraction indices per 16-byte load, odd last index alone, lanes past the
+13th repeating the 13th).  The systems are the sizes where that can go wrong:
+a single atom, a pair, odd row lengths (a run of one output), runs whose
+entries do not fill a group of four, atoms without neighbours.
+
+Bound: both sides sum L products of doubles per real component, each with a
+forward error of at most L eps sum |a||b|; a complex component holds two real
+sums, so |C - C_ref| <= 2 * 2 (L + 2) eps * P(|A||B|) with |.| the largest
+component.
+"""
+
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_1404_5776_amd import rtdm, synth
+
+pytestmark = pytest.mark.gpu
+
+# (output, left, right, op(left), op(right)) on the kind's ranges
+KINDS = {"XH": ("A", "X", "H0", 0, 0), "AT": ("X", "A", "A", 0, 0), "UK": ("W", "U", "K", 0, 0),
+         "WU": ("K", "W", "U", 0, 1)}
+
+
+def _positions(name):
+    if name == "one":
+        return np.zeros((1, 3))
+    if name == "two":
+        return np.array([[0.0, 0.0, 0.0], [0.0, 3.1, 0.4]])
+    if name == "isolated":
+        return np.concatenate([synth.cluster_positions(7, np.random.default_rng(5)),
+                               np.array([[100.0, 0.0, 0.0], [0.0, 150.0, 0.0]])])
+    return synth.cluster_positions(int(name), np.random.default_rng(int(name)))
+
+
+def _check(b, xyz, ranges, kind):
+    R_HS, R_P, R_K = ranges
+    print(f"[gpu] {kind} b={b} n={len(xyz)} ranges={ranges}", flush=True)
+    slot_r = {"S": R_HS, "H0": R_HS, "H": R_HS, "X": R_P, "A": R_P, "U": R_P, "K": R_K, "W": R_K}
+    out, left, right, op_a, op_b = KINDS[kind]
+    ctx = rtdm.Context(0)
+    try:
+        rtdm.rtdm_set_geometry(ctx.h, xyz, np.full(len(xyz), b, dtype=np.int32))
+        rtdm.rtdm_set_ranges(ctx.h, R_HS, R_P, R_K)
+        ctx.b = b
+        mats, pats = {}, {}
+        rng = np.random.default_rng(17)
+        for s in (left, right, out):
+            pats[s] = O.pattern(xyz, slot_r[s])
+        for s in dict.fromkeys((left, right)):
+            v = rng.uniform(-1, 1, size=(pats[s].nnzb, b, b))
+            if s in "UKW":
+                v = v + 1j * rng.uniform(-1, 1, size=v.shape)
+            rtdm.rtdm_upload(ctx.h, s, v)
+            mats[s] = O.BSM(pats[s], b, v.astype(np.complex128))
+        rtdm.rtdm_multiply(ctx.h, out, left, right, op_a, op_b)
+        got = rtdm.rtdm_download(ctx.h, out, b)
+        ref, _ = O.spgemm(mats[left], mats[right], pats[out], 1.0, op_a, op_b)
+
+        def big(m):
+            return O.BSM(m.pat, b, np.maximum(np.abs(m.val.real), np.abs(m.val.imag)).astype(np.complex128))
+
+        mag, _ = O.spgemm(big(mats[left]), big(mats[right]), pats[out], 1.0, op_a, op_b)
+        L = b * int(np.diff(pats[left].row_ptr).max())
+        bound = 4.0 * (L + 2) * np.finfo(float).eps * mag.val.real
+        err = np.abs(got - ref.val)
+        assert np.all(err <= bound), (float((err - bound).max()), float(err.max()))
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("kind", sorted(KINDS))
+@pytest.mark.parametrize("name", ["one", "two", "isolated", "5", "23", "38"])
+def test_pair_layout_b13(name, kind):
+    _check(13, _positions(name), (5.0, 8.0, 7.0), kind)
