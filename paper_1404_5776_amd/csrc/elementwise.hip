@@ -587,6 +587,32 @@ void launch_conj_transpose(hipStream_t s, int64_t nnzb, int b, const int32_t *tr
     RT_HIP(hipGetLastError());
 }
 
+// U^dagger with every block transposed: block trans[p] = conj(block p), element
+// by element, b = 4.  Eight lanes move one 128-byte block as 16-byte pairs.
+__global__ __launch_bounds__(kT) void k_conj_move4(int64_t n2, const int32_t *__restrict__ trans,
+                                                   const double2 *__restrict__ in_re,
+                                                   const double2 *__restrict__ in_im, double2 *__restrict__ out_re,
+                                                   double2 *__restrict__ out_im)
+{
+    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < n2; e += (int64_t)gridDim.x * kT) {
+        const int64_t o = (int64_t)trans[e >> 3] * 8 + (e & 7);
+        const double2 v = in_im[e];
+        out_re[o] = in_re[e];
+        out_im[o] = make_double2(-v.x, -v.y);
+    }
+}
+
+void launch_conj_move(hipStream_t s, int64_t nnzb, int b, const int32_t *trans, const double *in_re,
+                      const double *in_im, double *out_re, double *out_im)
+{
+    if (nnzb == 0) return;
+    RT_CHECK(b == 4, RTDM_E_UNSUPPORTED, "conjugate moves need b = 4");
+    const int64_t n2 = nnzb * 8, g = std::min<int64_t>((n2 + kT - 1) / kT, 65536);
+    hipLaunchKernelGGL(k_conj_move4, dim3((unsigned)g), dim3(kT), 0, s, n2, trans, (const double2 *)in_re,
+                       (const double2 *)in_im, (double2 *)out_re, (double2 *)out_im);
+    RT_HIP(hipGetLastError());
+}
+
 __global__ void k_to_f32(int64_t nblocks, int b, int transpose, const double *__restrict__ in,
                          float *__restrict__ out)
 {

@@ -169,10 +169,27 @@ void launch_run_fill(hipStream_t s, int64_t nch, const int32_t *run_row, const i
 // operand's op(B)[m][r] at m*B + r (conj_b: conjugated) and the output written
 // column-major if out_col_major.  b = 13, FP64.
 void launch_spgemm_cm(hipStream_t s, const SpgemmArgs &a, int conj_b, int out_col_major);
+// A product's fused sum: p (row-major blocks, null: none) = sign * output (store) or += sign * output.
+struct SumInto {
+    double *p = nullptr;
+    double sign = 1.0;
+    int store = 0;
+};
 // b = 13 FP64 product over segmented row runs of 2 with both operands in pair
 // layout (launch_pack_pairs): op(B) from right pairs, or with conj_b from the
-// left pairs of the conjugate-transposed matrix; out_pairs: the output as left pairs.
-void launch_spgemm_pairs(hipStream_t s, const SpgemmArgs &a, int conj_b, int out_pairs);
+// left pairs of the conjugate-transposed matrix; the output row-major, as left
+// pairs or (real products) as right pairs, a.cr null when only the sum u is wanted.
+enum { kOutRows = 0, kOutLeft = 1, kOutRight = 2 };
+void launch_spgemm_pairs(hipStream_t s, const SpgemmArgs &a, int conj_b, int out, const SumInto &u);
+// tau = dt A as a right operand (b = 4: transposed blocks, b = 13: right pairs),
+// u_im = -dt A and, at b = 13, ap = the left pairs of A.
+void launch_taylor_start(hipStream_t s, int64_t nblocks, int b, double dt, const double *a, double *tau, double *u_im,
+                         double *ap);
+// b = 4 FP64 product over runs of 16 from a row-major left operand and a right
+// operand with every block transposed (conj_b: the row-major blocks of the
+// matrix whose conjugate transpose it is); out_t: the output with transposed
+// blocks; u: the fused sum of a real product (a.cr may be null).
+void launch_spgemm_b4t(hipStream_t s, const SpgemmArgs &a, int conj_b, int out_t, const SumInto &u);
 // Pair layout of every 13 x 13 block: left pairs, right pairs, or row-major from left pairs.
 enum { kPackLeft = 0, kPackRight = 1, kUnpackLeft = 2 };
 void launch_pack_pairs(hipStream_t s, int64_t nblocks, int mode, const double *in, double *out);
@@ -199,6 +216,9 @@ void launch_transpose_blocks(hipStream_t s, int64_t nblocks, int b, const double
 // out_ji = in_ij^dagger over a pattern (trans: the transpose map of the pattern)
 void launch_conj_transpose(hipStream_t s, int64_t nnzb, int b, const int32_t *trans, const double *in_re,
                            const double *in_im, double *out_re, double *out_im);
+// the same with every output block transposed: out_ji = conj(in_ij), element by element
+void launch_conj_move(hipStream_t s, int64_t nnzb, int b, const int32_t *trans, const double *in_re,
+                      const double *in_im, double *out_re, double *out_im);
 // True when a b = 4 product over nch runs of 16 outputs takes the split form
 // (one workgroup per run: small systems, whose runs are too few to fill the chip).
 bool b4_split_form(int64_t nch);

@@ -304,8 +304,8 @@ struct rtdm_ctx {
     // Mulliken model: A0 = P(X H0), so that a step's A is A0 + X D (D diagonal)
     Mat A0;
     bool A0_valid = false;
-    // b = 4, FP64 products over row runs: Uh = U^dagger stored as a matrix, so
-    // that W U^dagger reads its right operand by rows of Uh (blocks of one row k
+    // b = 4, FP64 products over row runs: Uh = U^dagger stored as a matrix (its
+    // blocks transposed, as the run kernel reads a right operand), so that W U^dagger reads its right operand by rows of Uh (blocks of one row k
     // for the 16 outputs of a run) instead of by columns of U
     Mat Uh;
     bool Uh_on = false;
@@ -652,6 +652,16 @@ Sched &schedule_key(rtdm_ctx *c, int prod, const std::tuple<int, int, int, int, 
     return ref;
 }
 
+// Whether the products of schedule S run on the b = 4 kernel that reads its
+// right operand with transposed blocks: FP64 over enough runs of 16 to fill
+// the chip (below that the split form's shorter chains are faster).
+bool b4_transposed(rtdm_ctx *c, const Sched &S)
+{
+    if (c->b != 4 || c->prec != RTDM_PREC_FP64 || c->run_b4 != 16 || !c->Bp.re.p) return false;
+    auto r = S.runs.find(16);
+    return r != S.runs.end() && r->second->nch > 0 && !b4_split_form(r->second->nch);
+}
+
 hipEvent_t event_at(rtdm_ctx *c, size_t k)
 {
     while (c->events.size() <= k) {
@@ -663,8 +673,16 @@ hipEvent_t event_at(rtdm_ctx *c, size_t k)
 }
 
 
+// Where a product's output goes beside (or in place of) row-major blocks of C.
+struct ProductOut {
+    int layout = 0;     // b = 13 pair products: kOutRows / kOutLeft / kOutRight; b_t products: 1 transposed blocks
+    SumInto u;          // fused sum
+    bool drop = false;  // C itself is not wanted
+};
+
 void product_key(rtdm_ctx *c, int prod, const std::tuple<int, int, int, int, int> &key, const Mat &A,
-                 const Mat &B, Mat &C, double alr, double ali, hipStream_t s);
+                 const Mat &B, Mat &C, double alr, double ali, hipStream_t s, bool b_t = false,
+                 const ProductOut &out = ProductOut());
 
 // C = P_C(alpha op(A) op(B)) with the schedule of `prod`.
 void product(rtdm_ctx *c, int prod, const Mat &A, const Mat &B, Mat &C, double alr, double ali,
@@ -673,9 +691,11 @@ void product(rtdm_ctx *c, int prod, const Mat &A, const Mat &B, Mat &C, double a
     product_key(c, prod, prod_key(c, prod), A, B, C, alr, ali, s);
 }
 
-// The same with the schedule of operand and output patterns `key` (timed as `prod`).
+// The same with the schedule of operand and output patterns `key` (timed as
+// `prod`); b_t: B's blocks are stored transposed (where b4_transposed holds;
+// only then does `out` differ from the default).
 void product_key(rtdm_ctx *c, int prod, const std::tuple<int, int, int, int, int> &key, const Mat &A,
-                 const Mat &B, Mat &C, double alr, double ali, hipStream_t s)
+                 const Mat &B, Mat &C, double alr, double ali, hipStream_t s, bool b_t, const ProductOut &out)
 {
     Sched &S = schedule_key(c, prod, key);
     RT_CHECK(A.pat == std::get<0>(key) && B.pat == std::get<1>(key) && C.pat == std::get<2>(key),
@@ -729,8 +749,22 @@ void product_key(rtdm_ctx *c, int prod, const std::tuple<int, int, int, int, int
             a.ch_out = R.out.p;
         }
     }
+    const bool b4t = b4_transposed(c, S) && a.op_a == 0;
+    RT_CHECK(!b_t || b4t, RTDM_E_ARG, "transposed right operand outside the b = 4 run kernel");
     auto go = [&]() {
-        launch_spgemm(s, a);
+        if (!b4t) {
+            launch_spgemm(s, a);
+            return;
+        }
+        if (!b_t && !a.op_b) {
+            const int64_t nb = c->pats[B.pat]->nnzb;
+            launch_transpose_blocks(s, nb, 4, B.re.p, c->Bp.re.p);
+            if (B.cplx) launch_transpose_blocks(s, nb, 4, B.im.p, c->Bp.im.p);
+            a.br = c->Bp.re.p;
+            a.bi = B.cplx ? c->Bp.im.p : nullptr;
+        }
+        if (out.drop) a.cr = nullptr;
+        launch_spgemm_b4t(s, a, a.op_b, out.layout, out.u);
     };
     if (c->timing && !c->capturing) {
         const size_t k = 2 * c->recs.size();
@@ -757,7 +791,7 @@ bool pairs_kind(const rtdm_ctx *c, int prod) { return complex_kind(prod) ? c->pa
 // launch_spgemm_cm), or with both operands in pair layout (`pairs`, see
 // launch_spgemm_pairs); same schedule, timing and flop accounting as product().
 void product_cm(rtdm_ctx *c, int prod, const Mat &Acm, const Mat &B, Mat &C, int conj_b, int out_cm,
-                double alr, hipStream_t s, bool pairs)
+                double alr, hipStream_t s, bool pairs, const ProductOut &out = ProductOut())
 {
     Sched &S = schedule(c, prod);
     auto key = prod_key(c, prod);
@@ -809,7 +843,10 @@ void product_cm(rtdm_ctx *c, int prod, const Mat &Acm, const Mat &B, Mat &C, int
     }
     auto go = [&]() {
         if (split) launch_spgemm_cm_split(s, a);
-        else if (pairs) launch_spgemm_pairs(s, a, conj_b, out_cm);
+        else if (pairs) {
+            if (out.drop) a.cr = nullptr;
+            launch_spgemm_pairs(s, a, conj_b, out.layout ? out.layout : out_cm ? kOutLeft : kOutRows, out.u);
+        }
         else launch_spgemm_cm(s, a, conj_b, out_cm);
     };
     if (c->timing && !c->capturing) {
@@ -918,6 +955,17 @@ int all_products_prec(rtdm_ctx *c)
     }
 }
 
+// Whether build_propagator takes its fused form: FP64 terms on the kernels that
+// read re-laid-out right operands (at b = 4 also ahead of FP32 or stored-split
+// BF16 late terms, low16, which convert from that layout).
+bool taylor_fused(rtdm_ctx *c, bool low16)
+{
+    if (c->prec != RTDM_PREC_FP64) return false;
+    if (c->b == 13) return c->pairs_real && c->opt.precision == RTDM_PREC_FP64;
+    return (c->opt.precision == RTDM_PREC_FP64 || c->opt.precision == RTDM_PREC_FP32_TAYLOR || low16) &&
+           b4_transposed(c, schedule(c, RTDM_PROD_AT));
+}
+
 // U = sum_{n=0}^{p} (-i)^n tau_n with tau_0 = I, tau_1 = dt A, tau_n = (dt/n) P_P(A tau_{n-1}).
 void build_propagator(rtdm_ctx *c, double dt, hipStream_t s)
 {
@@ -943,12 +991,26 @@ void build_propagator(rtdm_ctx *c, double dt, hipStream_t s)
     case RTDM_PREC_FP16X2_TAYLOR: n0 = c->opt.taylor_low_from; low = RTDM_PREC_FP16X2; break;
     default: break;
     }
-    launch_fill(s, ne, 0.0, U.re.p);   // kernels, not memsets: this code may be captured in a graph
-    launch_fill(s, ne, 0.0, U.im.p);
-    launch_add_identity(s, c->n, c->b, pat_of(c, R_P).d_diag.p, 1.0, U.re.p);
-    if (p >= 1) {
-        launch_axpby(s, ne, dt, A.re.p, 0.0, nullptr, c->tau[0].re.p);
-        launch_axpby(s, ne, -1.0, c->tau[0].re.p, 1.0, U.im.p, U.im.p);
+    // Fused form: the FP64 terms live in the layout of the next product's right
+    // operand and every FP64 product adds its term into U as it writes it, so a
+    // term costs U read and written and tau written instead of six passes (tau
+    // written, re-laid out, and read again into the sum).  Per step: 32,768 atoms
+    // b = 4, R_K 12: 24.4 -> 23.0 ms; 7,560 atoms, R_K 8: 1.81 -> 1.63 ms; 512
+    // atoms b = 13: 12.8 -> 12.5 ms; 4,096 atoms: 166.8 -> 165 ms.
+    const bool fused = p >= 1 && taylor_fused(c, low16);
+    const bool re_stored = fused && p >= 2 && n0 > 2;   // term 2 stores its plane: no fill before it
+    if (!re_stored) {
+        launch_fill(s, ne, 0.0, U.re.p);   // kernels, not memsets: this code may be captured in a graph
+        launch_add_identity(s, c->n, c->b, pat_of(c, R_P).d_diag.p, 1.0, U.re.p);
+    }
+    if (fused) {
+        launch_taylor_start(s, pat_of(c, R_P).nnzb, c->b, dt, A.re.p, c->tau[0].re.p, U.im.p, c->Ap.re.p);
+    } else {
+        launch_fill(s, ne, 0.0, U.im.p);
+        if (p >= 1) {
+            launch_axpby(s, ne, dt, A.re.p, 0.0, nullptr, c->tau[0].re.p);
+            launch_axpby(s, ne, -1.0, c->tau[0].re.p, 1.0, U.im.p, U.im.p);
+        }
     }
     // (-i)^k: k%4 == 0 -> +Re, 1 -> -Im, 2 -> -Re, 3 -> +Im
     auto add_term = [&](int k, const double *t64, const float *t32) {
@@ -966,7 +1028,7 @@ void build_propagator(rtdm_ctx *c, double dt, hipStream_t s)
     for (int k = 2; k <= p; ++k) {
         if (low16 && k >= n0) {
             if (!in32) {
-                launch_to_bf16x2(s, pat_of(c, R_P).nnzb, 1, c->tau[cur].re.p, as16(c->tau32[cur].p));
+                launch_to_bf16x2(s, pat_of(c, R_P).nnzb, fused ? 0 : 1, c->tau[cur].re.p, as16(c->tau32[cur].p));
                 in32 = true;
             }
             Sched &S = schedule(c, RTDM_PROD_AT);
@@ -997,7 +1059,7 @@ void build_propagator(rtdm_ctx *c, double dt, hipStream_t s)
             }
         } else if (low32 && k >= n0) {
             if (!in32) {
-                launch_to_f32(s, pat_of(c, R_P).nnzb, c->b, 0, c->tau[cur].re.p, c->tau32[cur].p);
+                launch_to_f32(s, pat_of(c, R_P).nnzb, c->b, fused ? 1 : 0, c->tau[cur].re.p, c->tau32[cur].p);
                 in32 = true;
             }
             Sched &S = schedule(c, RTDM_PROD_AT);
@@ -1034,6 +1096,17 @@ void build_propagator(rtdm_ctx *c, double dt, hipStream_t s)
                 c->recs.push_back({RTDM_PROD_AT, (int)ev, (double)S.ntrip * 2.0 * b3});
             }
             add_term(k, nullptr, c->tau32[1 - cur].p);
+        } else if (fused) {
+            ProductOut out;
+            out.layout = c->b == 13 ? kOutRight : 1;
+            out.u.p = (k % 2 == 0) ? U.re.p : U.im.p;
+            out.u.sign = (k % 4 == 0 || k % 4 == 3) ? 1.0 : -1.0;
+            out.u.store = k == 2 && re_stored;
+            out.drop = k == p;
+            Mat &src = c->tau[cur], &dst = c->tau[1 - cur];
+            if (c->b == 13) product_cm(c, RTDM_PROD_AT, c->Ap, src, dst, 0, 0, dt / k, s, true, out);
+            else product_key(c, RTDM_PROD_AT, prod_key(c, RTDM_PROD_AT), A, src, dst, dt / k, 0.0, s, true, out);
+            if (out.u.store) launch_add_identity(s, c->n, c->b, pat_of(c, R_P).d_diag.p, 1.0, U.re.p);
         } else {
             Mat &src = c->tau[cur];
             Mat &dst = c->tau[1 - cur];
@@ -1559,10 +1632,17 @@ int rtdm_set_ranges(rtdm_ctx *c, double R_hs, double R_p, double R_k)
             c->Ap.pat = c->range_pat[R_P];
             c->Ap.re.alloc(elems(c, c->Ap));
         }
-        if (c->pairs_real || c->pairs_cplx) {
-            const int64_t ne = std::max({pat_of(c, R_HS).nnzb, pat_of(c, R_P).nnzb, pat_of(c, R_K).nnzb}) * 169;
+        bool b4 = false;         // some b = 4 products over enough runs for transposed right operands
+        if (c->b == 4 && c->run_b4 == 16)
+            for (auto &kv : c->scheds) {
+                auto r = kv.second->runs.find(16);
+                b4 |= r != kv.second->runs.end() && r->second->nch > 0 && !b4_split_form(r->second->nch);
+            }
+        if (c->pairs_real || c->pairs_cplx || b4) {
+            const int64_t ne =
+                std::max({pat_of(c, R_HS).nnzb, pat_of(c, R_P).nnzb, pat_of(c, R_K).nnzb}) * (int64_t)c->b * c->b;
             c->Bp.re.alloc(ne);
-            if (c->pairs_cplx) c->Bp.im.alloc(ne);
+            if (c->pairs_cplx || b4) c->Bp.im.alloc(ne);
         }
     }
     // the unitarity product too when steps check it, so that rtdm_step allocates nothing
@@ -2004,7 +2084,8 @@ void ensure_a0(rtdm_ctx *c, hipStream_t s)
 void copy_a(rtdm_ctx *c, hipStream_t s)
 {
     const Mat &A = c->mats[RTDM_MAT_A];
-    if (c->pairs_real) pack_into(c, A, c->Ap, kPackLeft, s);
+    // (the fused Taylor form makes Ap itself)
+    if (c->pairs_real && c->opt.precision != RTDM_PREC_FP64) pack_into(c, A, c->Ap, kPackLeft, s);
     if (!c->pairs_real || c->opt.precision != RTDM_PREC_FP64) transpose_into(c, A, c->Ac, s);
 }
 
@@ -2092,7 +2173,7 @@ void build_u(rtdm_ctx *c, double dt, bool corr, hipStream_t s)
     }
     if (c->Uh_on) {
         const Pattern &pp = pat_of(c, R_P);
-        launch_conj_transpose(s, pp.nnzb, c->b, pp.d_trans.p, U.re.p, U.im.p, c->Uh.re.p, c->Uh.im.p);
+        launch_conj_move(s, pp.nnzb, c->b, pp.d_trans.p, U.re.p, U.im.p, c->Uh.re.p, c->Uh.im.p);
     }
     c->u_copies_valid = true;
 }
@@ -2110,7 +2191,7 @@ void ensure_u_copies(rtdm_ctx *c, hipStream_t s)
     c->prec = saved;
     if (c->Uh_on) {
         const Pattern &pp = pat_of(c, R_P);
-        launch_conj_transpose(s, pp.nnzb, c->b, pp.d_trans.p, U.re.p, U.im.p, c->Uh.re.p, c->Uh.im.p);
+        launch_conj_move(s, pp.nnzb, c->b, pp.d_trans.p, U.re.p, U.im.p, c->Uh.re.p, c->Uh.im.p);
     }
     c->u_copies_valid = true;
 }
@@ -2143,7 +2224,7 @@ void step_body(rtdm_ctx *c, double dt, bool rebuild_u, int passes, hipStream_t s
                 c->W_in_cm = true;
             } else {
                 product(c, RTDM_PROD_UK, U, K, W, 1.0, 0.0, s);
-                if (c->Uh_on) product_key(c, RTDM_PROD_WU, wuh_key(c), W, c->Uh, c->Kn, 1.0, 0.0, s);
+                if (c->Uh_on) product_key(c, RTDM_PROD_WU, wuh_key(c), W, c->Uh, c->Kn, 1.0, 0.0, s, true);
                 else product(c, RTDM_PROD_WU, W, U, c->Kn, 1.0, 0.0, s);
                 c->W_in_cm = false;
             }

@@ -23,6 +23,7 @@
 
 #include "internal.h"
 
+
 namespace rtdm {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
@@ -289,6 +290,12 @@ static inline unsigned xcd_grid(int64_t nblocks, int remap = 1)
 // blocks meet in the shared last-level cache; contiguous eighths measured
 // 11 % slower at b = 13).
 static int xcd_chunk() { return 128; }
+// Chunks for a launch of nwg workgroups: 128 from 16,384 workgroups on; below
+// that they leave the last round of chunks nearly empty, and chunks of 32 are
+// faster (b = 13, 512 atoms, 7,700 workgroups: U K 3.66 -> 3.42 ms; 1,000
+// atoms, 19,000 workgroups: 2.81 against 2.86 ms per real product; b = 4,
+// 7,560 atoms at R_K 8, 6,300 workgroups: U K 0.289 -> 0.279 ms).
+static int xcd_chunk_for(int64_t nwg) { return nwg < 16384 ? 32 : xcd_chunk(); }
 // The same deal in chunks of about as many output blocks (1,024) for a kernel
 // with `per_wg` output blocks per workgroup.
 static int xcd_chunk_wg(int per_wg) { return std::max(2, xcd_chunk() * 8 / std::max(per_wg, 1)); }
@@ -615,7 +622,9 @@ __device__ __host__ inline int pair_at(int b, int x, int m)
 // outputs sharing an L2) beat four by 8 % and five by 18 % on the real
 // product.  4,096 atoms, R 16, ms per launch, 8-byte loads at four waves ->
 // now: A tau 19.9 -> 15.8, U K 49.7 -> 45.8, W U^dagger 48.3 -> 45.7.
-// OUT: 0 row-major output, 1 left pairs.
+// OUT: 0 row-major output, 1 left pairs, 2 right pairs.  u (real products,
+// nullable): u = u_sign * output (u_store) or u += u_sign * output, row-major:
+// the Taylor sum, whose own pass would read the term again.
 typedef double pd2 __attribute__((ext_vector_type(2), aligned(8)));
 typedef __attribute__((address_space(1))) const pd2 gpd2;
 template <int B, bool AC, bool BC, int CJB, int OUT>
@@ -625,7 +634,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const double *__restrict__ ar, const double *__restrict__ ai, const double *__restrict__ br,
     const double *__restrict__ bi, double *__restrict__ cr, double *__restrict__ ci, double alr,
     double ali, const double *__restrict__ zero, const int32_t *__restrict__ order, int remap,
-    const int32_t *__restrict__ seg)
+    const int32_t *__restrict__ seg, double *__restrict__ u, double u_sign, int u_store)
 {
     static_assert(B >= 5 && B <= 15 && (B & 1), "odd block sizes");
     constexpr int BB = B * B, NJ = 2;
@@ -740,8 +749,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             if (row < B && col < B) {
                 const double re = rr[t][e];
                 const double im = (AC && BC) ? ri[t][e] : sb * ri[t][e] + ir[t][e];
-                const int64_t o = (int64_t)p * BB + (OUT ? pair_at(B, row, col) : row * B + col);
-                cr[o] = alr * re - ali * im;
+                const int64_t rm = (int64_t)p * BB + row * B + col;
+                const int64_t o = OUT == 0   ? rm
+                                  : OUT == 1 ? (int64_t)p * BB + pair_at(B, row, col)
+                                             : (int64_t)p * BB + pair_at(B, col, row);
+                const double vr = alr * re - ali * im;
+                if (u) u[rm] = u_store ? u_sign * vr : u[rm] + u_sign * vr;
+                if (cr) cr[o] = vr;
                 if (ci) ci[o] = alr * im + ali * re;
             }
         }
@@ -774,34 +788,79 @@ void launch_pack_pairs(hipStream_t s, int64_t nblocks, int mode, const double *i
     RT_HIP(hipGetLastError());
 }
 
-template <bool AC, bool BC, int CJB, int OUT>
-static void launch_q4p(hipStream_t s, const SpgemmArgs &a)
+// Start of the Taylor sum from A (row-major blocks), one pass: tau = dt A as
+// the right operand of the next product (b = 4: blocks transposed; b = 13:
+// right pairs), u_im = -dt A, and at b = 13 the left pairs of A (ap).
+template <int B, typename I>
+__global__ __launch_bounds__(256) void k_taylor_start(I n, double dt, const double *__restrict__ a,
+                                                      double *__restrict__ tau, double *__restrict__ u_im,
+                                                      double *__restrict__ ap)
 {
-    // Chunks of 128 workgroups per XCD from 16,384 workgroups on; below that
-    // they leave the last round of chunks nearly empty, and chunks of 32 are
-    // faster (512 atoms, 7,700 workgroups: U K 3.66 -> 3.42 ms; 1,000 atoms,
-    // 19,000 workgroups: 2.81 against 2.86 ms per real product)
-    const int remap = (a.nch + 3) / 4 < 16384 ? 32 : xcd_chunk();
+    constexpr int BB = B * B;
+    for (I e = (I)blockIdx.x * 256 + threadIdx.x; e < n; e += (I)gridDim.x * 256) {
+        const I p = e / BB;
+        const int w = (int)(e - p * BB), r = w / B, c = w - r * B;
+        const double v = a[e], t = dt * v;
+        u_im[e] = -t;
+        if (B == 4) {
+            tau[p * BB + c * B + r] = t;
+        } else {
+            tau[p * BB + pair_at(B, c, r)] = t;
+            ap[p * BB + pair_at(B, r, c)] = v;
+        }
+    }
+}
+
+void launch_taylor_start(hipStream_t s, int64_t nblocks, int b, double dt, const double *a, double *tau, double *u_im,
+                         double *ap)
+{
+    const int64_t n = nblocks * b * b;
+    if (n == 0) return;
+    RT_CHECK(b == 4 || (b == 13 && ap), RTDM_E_ARG, "the Taylor start needs b = 4 or 13");
+    const int64_t g = std::min<int64_t>((n + 255) / 256, 65536);
+    const bool small = n + g * 256 < ((int64_t)1 << 32);   // 32-bit index arithmetic
+#define RT_TS(B_, I_) \
+    hipLaunchKernelGGL((k_taylor_start<B_, I_>), dim3((unsigned)g), dim3(256), 0, s, (I_)n, dt, a, tau, u_im, ap)
+    if (b == 4 && small) RT_TS(4, uint32_t);
+    else if (b == 4) RT_TS(4, int64_t);
+    else if (small) RT_TS(13, uint32_t);
+    else RT_TS(13, int64_t);
+#undef RT_TS
+    RT_HIP(hipGetLastError());
+}
+
+template <bool AC, bool BC, int CJB, int OUT>
+static void launch_q4p(hipStream_t s, const SpgemmArgs &a, const SumInto &u)
+{
+    const int remap = xcd_chunk_for((a.nch + 3) / 4);
     const unsigned grid = xcd_grid((a.nch + 3) / 4, remap);
     hipLaunchKernelGGL((k_spgemm_q4p<13, AC, BC, CJB, OUT>), dim3(grid), dim3(256), 0, s, a.nch,
                        a.ch_off, a.ch_a, a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re,
-                       a.alpha_im, a.zero, a.ch_order, remap, a.ch_seg);
+                       a.alpha_im, a.zero, a.ch_order, remap, a.ch_seg, u.p, u.sign, u.store);
 }
 
 // Products over row runs of 2 with both operands in pair layout (b = 13, FP64;
-// a conjugated right operand U^dagger is the left pairs of U): conj_b,
-// out_pairs (the output as left pairs).
-void launch_spgemm_pairs(hipStream_t s, const SpgemmArgs &a, int conj_b, int out_pairs)
+// a conjugated right operand U^dagger is the left pairs of U): conj_b, out
+// (kOut*; right pairs and the fused sum u for real products only).
+void launch_spgemm_pairs(hipStream_t s, const SpgemmArgs &a, int conj_b, int out, const SumInto &u)
 {
     RT_CHECK(a.b == 13 && a.precision == RTDM_PREC_FP64 && a.nj == 2 && a.nch > 0 && a.ch_seg && a.zero, RTDM_E_ARG,
              "pair-layout products need b = 13, FP64 and segmented runs of 2");
     const bool ac = a.ai != nullptr, bc = a.bi != nullptr;
-#define RT_Q4P(AC_, BC_)                                            \
-    do {                                                            \
-        if (conj_b && out_pairs) launch_q4p<AC_, BC_, 1, 1>(s, a);  \
-        else if (conj_b) launch_q4p<AC_, BC_, 1, 0>(s, a);          \
-        else if (out_pairs) launch_q4p<AC_, BC_, 0, 1>(s, a);       \
-        else launch_q4p<AC_, BC_, 0, 0>(s, a);                      \
+    const bool real = !ac && !bc && !a.ci;
+    RT_CHECK(real || (!u.p && out != kOutRight), RTDM_E_ARG, "right pairs and the fused sum need real operands");
+    if (real && out == kOutRight) {
+        launch_q4p<false, false, 0, 2>(s, a, u);
+        RT_HIP(hipGetLastError());
+        return;
+    }
+    const int out_pairs = out == kOutLeft;
+#define RT_Q4P(AC_, BC_)                                               \
+    do {                                                               \
+        if (conj_b && out_pairs) launch_q4p<AC_, BC_, 1, 1>(s, a, u);  \
+        else if (conj_b) launch_q4p<AC_, BC_, 1, 0>(s, a, u);          \
+        else if (out_pairs) launch_q4p<AC_, BC_, 0, 1>(s, a, u);       \
+        else launch_q4p<AC_, BC_, 0, 0>(s, a, u);                      \
     } while (0)
     if (ac && bc) RT_Q4P(true, true);
     else if (ac) RT_Q4P(true, false);
@@ -1476,6 +1535,161 @@ __global__ __launch_bounds__(256) void k_spgemm_b4j(
             if (ci) ci[o] = alr * im + ali * re;
         }
     }
+}
+
+// FP64 b = 4 product over row runs of 16 outputs from operands whose lanes
+// take 16 bytes: A row-major, B with every block transposed (bt), so that
+// lane 16 q + 4 g + r reads A[r][2h], A[r][2h + 1] and B[2h][r], B[2h + 1][r]
+// (h = q & 1) of entry e + (q >> 1) of a pair of entries.  One
+// v_mfma_f64_4x4x4_4b then contracts over the even rows of both entries, a
+// second one over the odd rows.  A conjugate-transposed right operand in
+// row-major blocks is such a B as it is (CJB).
+//
+// Bound: the loads of k_spgemm_b4j (8 bytes a lane) kept the vector-memory
+// address unit busy 99 % of the time at one entry per seven of them; a 16-byte
+// load whose lane quads stay inside a block takes the same 15 cycles, and the
+// entry's 16 block indices come as one 4-byte load (5 cycles) spread over the
+// quad: per pair of entries 7 loads (real) in place of 14.  With the address
+// unit relieved the L2 hit rate counts, and the chunked XCD deal pays (hardware
+// order: A tau 2.8, U K 6.5 ms).  32,768 atoms, R_K 12, ms per launch, 8-byte
+// loads -> now: A tau 4.3 -> 2.6 (0.2 of it the transposition of tau),
+// U K 7.5 -> 5.3 (0.3 transposing K), W U^dagger 7.5 -> 5.0.
+template <bool AC, bool BC, int CJB, int OUT>
+__global__ __launch_bounds__(256) void k_spgemm_b4p(
+    int64_t nch, const int64_t *__restrict__ off, const int32_t *__restrict__ ea,
+    const int32_t *__restrict__ eb, const int32_t *__restrict__ cout, const double *__restrict__ ar,
+    const double *__restrict__ ai, const double *__restrict__ br, const double *__restrict__ bi,
+    double *__restrict__ cr, double *__restrict__ ci, double alr, double ali, double *__restrict__ u,
+    double u_sign, int u_store, int remap)
+{
+    const int lane = threadIdx.x & 63;
+    const int g = (lane >> 2) & 3, r = lane & 3, q = lane >> 4;
+    const int64_t c = xcd_block((nch + 3) / 4, remap) * 4 + (threadIdx.x >> 6);
+    if (c >= nch) return;                      // uniform across the wave
+    const int lo = r * 4 + 2 * (q & 1), eo = q >> 1, slot = g * 4 + r;
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    // four sums per complex output: adding the imaginary products to the real
+    // ones' sum as they come doubled its roundings (error of a product against
+    // 64-bit arithmetic 6.0e-16 -> 8.5e-16) for 0 - 4 % of the time
+    double rr[4] = {0, 0, 0, 0}, ri[4] = {0, 0, 0, 0}, ii[4] = {0, 0, 0, 0}, ir[4] = {0, 0, 0, 0};
+    struct Ops {
+        d2 xar, xai, xbr[4], xbi[4];
+    };
+    struct Idx {
+        int a, b;
+    };
+    const int64_t e0 = off[c], e1 = off[c + 1];
+    auto load_idx = [&](int64_t e) {
+        Idx x{-1, -1};
+        if (e + eo < e1) {
+            x.a = ea[e + eo];
+            x.b = eb[(e + eo) * 16 + slot];
+        }
+        return x;
+    };
+    auto load_ops = [&](Idx x, Ops &o) {
+        o.xar = o.xai = d2{0, 0};
+        if (x.a >= 0) {
+            const int64_t pa = (int64_t)x.a * 16 + lo;
+            o.xar = *reinterpret_cast<const d2 *>(ar + pa);
+            if (AC) o.xai = *reinterpret_cast<const d2 *>(ai + pa);
+        }
+        // slot g * 4 + jj of the entry sits in lane r = jj of the quad
+        const int kb[4] = {__builtin_amdgcn_mov_dpp(x.b, 0x00, 0xf, 0xf, true),
+                           __builtin_amdgcn_mov_dpp(x.b, 0x55, 0xf, 0xf, true),
+                           __builtin_amdgcn_mov_dpp(x.b, 0xaa, 0xf, 0xf, true),
+                           __builtin_amdgcn_mov_dpp(x.b, 0xff, 0xf, 0xf, true)};
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+            o.xbr[jj] = o.xbi[jj] = d2{0, 0};
+            if (kb[jj] >= 0) {
+                const int64_t pb = (int64_t)kb[jj] * 16 + lo;
+                o.xbr[jj] = *reinterpret_cast<const d2 *>(br + pb);
+                if (BC) o.xbi[jj] = *reinterpret_cast<const d2 *>(bi + pb);
+            }
+        }
+    };
+    auto mma1 = [&](double xa, double xi, double yr, double yi, double &srr, double &sri, double &sii, double &sir) {
+        srr = __builtin_amdgcn_mfma_f64_4x4x4f64(xa, yr, srr, 0, 0, 0);
+        if (AC && BC) sii = __builtin_amdgcn_mfma_f64_4x4x4f64(xi, yi, sii, 0, 0, 0);
+        if (BC) sri = __builtin_amdgcn_mfma_f64_4x4x4f64(xa, yi, sri, 0, 0, 0);
+        if (AC) sir = __builtin_amdgcn_mfma_f64_4x4x4f64(xi, yr, sir, 0, 0, 0);
+    };
+    auto products = [&](const Ops &o) {
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) mma1(o.xar.x, o.xai.x, o.xbr[jj].x, o.xbi[jj].x, rr[jj], ri[jj], ii[jj], ir[jj]);
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) mma1(o.xar.y, o.xai.y, o.xbr[jj].y, o.xbi[jj].y, rr[jj], ri[jj], ii[jj], ir[jj]);
+    };
+    if constexpr (!(AC && BC)) {
+        // the next pair's operands in flight while this pair's products run
+        Ops cur, nxt;
+        Idx n1 = load_idx(e0 + 2);
+        load_ops(load_idx(e0), cur);
+        for (int64_t e = e0; e < e1; e += 2) {
+            const Idx n2 = load_idx(e + 4);
+            load_ops(n1, nxt);
+            products(cur);
+            cur = nxt;
+            n1 = n2;
+        }
+    } else {
+        // complex x complex: the second set of operands costs waves per SIMD
+        // (32,768 atoms, R 12: U K 5.0 -> 5.5 ms), so only the indices run ahead
+        Idx n1 = load_idx(e0);
+        for (int64_t e = e0; e < e1; e += 2) {
+            Ops o;
+            load_ops(n1, o);
+            n1 = load_idx(e + 2);
+            products(o);
+        }
+    }
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+        const int p = cout[c * 16 + 4 * jj + g];
+        if (p >= 0) {
+            const int64_t rm = (int64_t)p * 16 + q * 4 + r, tr = (int64_t)p * 16 + r * 4 + q;
+            constexpr double sb = CJB ? -1.0 : 1.0;
+            const double vr = rr[jj] - sb * ii[jj], vi = sb * ri[jj] + ir[jj];
+            const double re = alr * vr - ali * vi;
+            if (u) u[rm] = u_store ? u_sign * re : u[rm] + u_sign * re;
+            if (cr) cr[OUT ? tr : rm] = re;
+            if (ci) ci[OUT ? tr : rm] = alr * vi + ali * vr;
+        }
+    }
+}
+
+template <bool AC, bool BC, int CJB, int OUT>
+static void launch_b4p_as(hipStream_t s, const SpgemmArgs &a, const SumInto &u)
+{
+    const int remap = xcd_chunk_for((a.nch + 3) / 4);
+    hipLaunchKernelGGL((k_spgemm_b4p<AC, BC, CJB, OUT>), dim3(xcd_grid((a.nch + 3) / 4, remap)), dim3(256), 0, s, a.nch, a.ch_off, a.ch_a, a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re,
+                       a.alpha_im, u.p, u.sign, u.store, remap);
+}
+
+// b = 4 FP64 product over runs of 16 from a row-major left operand and a right
+// operand with transposed blocks (conj_b: the row-major blocks of the matrix
+// whose conjugate transpose it is); out_t: the output with transposed blocks;
+// u: the output's fused sum (real products).
+void launch_spgemm_b4t(hipStream_t s, const SpgemmArgs &a, int conj_b, int out_t, const SumInto &u)
+{
+    RT_CHECK(a.b == 4 && a.precision == RTDM_PREC_FP64 && a.nj == 16 && a.nch > 0 && a.op_a == 0, RTDM_E_ARG,
+             "transposed-block products need b = 4, FP64 and runs of 16");
+    const bool ac = a.ai != nullptr, bc = a.bi != nullptr;
+    RT_CHECK(!u.p || (!ac && !bc && !a.ci), RTDM_E_ARG, "the fused sum needs real operands");
+#define RT_B4P(AC_, BC_)                                                              \
+    do {                                                                              \
+        if (conj_b && out_t) launch_b4p_as<AC_, BC_, 1, 1>(s, a, u);          \
+        else if (conj_b) launch_b4p_as<AC_, BC_, 1, 0>(s, a, u);              \
+        else if (out_t) launch_b4p_as<AC_, BC_, 0, 1>(s, a, u);               \
+        else launch_b4p_as<AC_, BC_, 0, 0>(s, a, u);                          \
+    } while (0)
+    if (ac && bc) RT_B4P(true, true);
+    else if (ac) RT_B4P(true, false);
+    else if (bc) RT_B4P(false, true);
+    else RT_B4P(false, false);
+#undef RT_B4P
+    RT_HIP(hipGetLastError());
 }
 
 // The same product for products with few runs (small systems): one

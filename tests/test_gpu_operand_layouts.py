@@ -76,3 +76,20 @@ def _check(b, xyz, ranges, kind):
 @pytest.mark.parametrize("name", ["one", "two", "isolated", "5", "23", "38"])
 def test_pair_layout_b13(name, kind):
     _check(13, _positions(name), (5.0, 8.0, 7.0), kind)
+
+
+@pytest.mark.parametrize("kind", sorted(KINDS))
+@pytest.mark.parametrize("ranges", [(5.0, 6.5, 6.5), (6.5, 6.5, 4.0), (4.0, 5.0, 11.0)])
+def test_transposed_right_operand_b4(ranges, kind):
+    """b = 4 over enough runs of 16 (at least 4,096) for the kernel that reads
+    A by rows and B with transposed blocks, two entries at a time: short rows
+    (one partly filled run each), odd numbers of entries, rows of several runs."""
+    n = {11.0: 1400}.get(ranges[2], 4200)
+    rng = np.random.default_rng(3)
+    g = DENSITY ** (-1.0 / 3.0)
+    m = int(np.ceil(n ** (1.0 / 3.0)))
+    p = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3)[:n] * g
+    _check(4, np.ascontiguousarray(p + rng.uniform(-0.4, 0.4, size=p.shape)), ranges, kind)
+
+
+DENSITY = synth.CLUSTER_DENSITY
