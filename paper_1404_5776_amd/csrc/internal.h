@@ -317,7 +317,9 @@ void launch_mlp_forward(hipStream_t s, int64_t n, int in, int out, const int32_t
 void launch_mlp_delta(hipStream_t s, int64_t n, int out, const int32_t *idx, const float *tgt, const float *y,
                       const float *hid, const __half *w2, float *dy, float *dh, float *sqerr);
 void launch_mlp_grad(hipStream_t s, int64_t n, int in, int out, const int32_t *idx, const float *x,
-                     const float *hid, const float *dy, const float *dh, float *grad);
+                     const float *hid, const float *dy, const float *dh, float *part, float *grad);
+// chunks of samples whose partial gradients launch_mlp_grad writes to part (one: none)
+int64_t mlp_grad_chunks(int64_t n);
 void launch_adam(hipStream_t s, int64_t np, int64_t nw1, int64_t nb1, int64_t nw2, const float *grad, float *w,
                  float *m, float *v, float lr, double beta1, double beta2, float eps, int step, __half *w1h,
                  __half *w2h);

@@ -269,7 +269,7 @@ struct MlpState {
     bool ready = false;
     DBuf<float> ds_x, ds_t;
     int64_t ns = 0, cap = 0;
-    DBuf<float> hid, y, dy, dh, sqerr, tx, tt;
+    DBuf<float> hid, y, dy, dh, sqerr, tx, tt, part;
     int64_t work_n = 0;
     DBuf<int32_t> idx;
     DBuf<double> dsum;
@@ -1275,6 +1275,7 @@ void mlp_work(rtdm_ctx *c, int64_t n)
     M.dy.alloc((size_t)n * M.out);
     M.dh.alloc((size_t)n * kMlpHidden);
     M.sqerr.alloc(n);
+    M.part.alloc((size_t)(std::min<int64_t>(64, (n + 63) / 64) * M.np));   // chunks of any count up to n
     M.work_n = n;
 }
 
@@ -1289,7 +1290,7 @@ double mlp_loss_grad(rtdm_ctx *c, int64_t n, const int32_t *idx, const float *x,
     mlp_work(c, n);
     launch_mlp_forward(s, n, M.in, M.out, idx, x, M.w1h.p, mlp_b1(M), M.w2h.p, mlp_b2(M), M.hid.p, M.y.p);
     launch_mlp_delta(s, n, M.out, idx, t, M.y.p, M.hid.p, M.w2h.p, M.dy.p, M.dh.p, M.sqerr.p);
-    launch_mlp_grad(s, n, M.in, M.out, idx, x, M.hid.p, M.dy.p, M.dh.p, M.grad.p);
+    launch_mlp_grad(s, n, M.in, M.out, idx, x, M.hid.p, M.dy.p, M.dh.p, M.part.p, M.grad.p);
     launch_sum_f32(s, n, M.sqerr.p, M.dsum.p);
     double sum = 0.0;
     read_scalars(&sum, M.dsum.p, 1, s);
