@@ -321,6 +321,9 @@ struct rtdm_ctx {
     // pairs of the right operand of the product being issued
     bool pairs_real = false, pairs_cplx = false;
     Mat Ap, Bp;
+    // left pairs of the left operand of a product without a kept copy (ETRS and
+    // Magnus propagators at b = 13: U E1, the commutator, M T_k); allocated with them
+    Mat Lp;
     // FP32 copies for the reduced-precision Taylor terms (b = 13)
     DBuf<float> Ac32, tau32[2], zero32;
     DBuf<double> scratch;       // block inverse scratch and staging
@@ -662,6 +665,21 @@ bool b4_transposed(rtdm_ctx *c, const Sched &S)
     return r != S.runs.end() && r->second->nch > 0 && !b4_split_form(r->second->nch);
 }
 
+// Whether schedule S has segmented row runs of 2 (b = 13).
+bool segmented_runs(const Sched &S)
+{
+    auto r = S.runs.find(2);
+    return r != S.runs.end() && r->second->nch > 0 && r->second->seg.p;
+}
+
+// M in pair layout (both planes).
+void pack_planes(rtdm_ctx *c, const Mat &M, Mat &out, int mode, hipStream_t s)
+{
+    const int64_t nb = c->pats[M.pat]->nnzb;
+    launch_pack_pairs(s, nb, mode, M.re.p, out.re.p);
+    if (M.cplx) launch_pack_pairs(s, nb, mode, M.im.p, out.im.p);
+}
+
 hipEvent_t event_at(rtdm_ctx *c, size_t k)
 {
     while (c->events.size() <= k) {
@@ -749,9 +767,35 @@ void product_key(rtdm_ctx *c, int prod, const std::tuple<int, int, int, int, int
             a.ch_out = R.out.p;
         }
     }
+    // b = 13, FP64: both operands packed, the row-run kernel of the step products
+    const bool pairs = c->b == 13 && c->prec == RTDM_PREC_FP64 && c->Lp.re.p && A.pat == c->range_pat[R_P] && a.op_a == 0 &&
+                       a.op_b == 0 &&
+                       (A.cplx || B.cplx ? c->pairs_cplx : c->pairs_real) && segmented_runs(S);
+    if (pairs) {
+        const Runs &R = *S.runs.find(2)->second;
+        a.nj = 2;
+        a.nch = R.nch;
+        a.ch_off = R.off.p;
+        a.ch_a = R.a.p;
+        a.ch_b = R.b.p;
+        a.ch_out = R.out.p;
+        a.ch_order = R.order.p;
+        a.ch_seg = R.seg.p;
+        a.zero = c->zero.p;
+    }
     const bool b4t = b4_transposed(c, S) && a.op_a == 0;
     RT_CHECK(!b_t || b4t, RTDM_E_ARG, "transposed right operand outside the b = 4 run kernel");
     auto go = [&]() {
+        if (pairs) {
+            pack_planes(c, A, c->Lp, kPackLeft, s);
+            pack_planes(c, B, c->Bp, kPackRight, s);
+            a.ar = c->Lp.re.p;
+            a.ai = A.cplx ? c->Lp.im.p : nullptr;
+            a.br = c->Bp.re.p;
+            a.bi = B.cplx ? c->Bp.im.p : nullptr;
+            launch_spgemm_pairs(s, a, 0, kOutRows, SumInto());
+            return;
+        }
         if (!b4t) {
             launch_spgemm(s, a);
             return;
@@ -870,18 +914,10 @@ void transpose_into(rtdm_ctx *c, const Mat &M, Mat &out, hipStream_t s)
     if (M.cplx) launch_transpose_blocks(s, nb, c->b, M.im.p, out.im.p);
 }
 
-// M in pair layout (both planes).
-void pack_into(rtdm_ctx *c, const Mat &M, Mat &out, int mode, hipStream_t s)
-{
-    const int64_t nb = c->pats[M.pat]->nnzb;
-    launch_pack_pairs(s, nb, mode, M.re.p, out.re.p);
-    if (M.cplx) launch_pack_pairs(s, nb, mode, M.im.p, out.im.p);
-}
-
 // The copy of a left operand that products of kind `prod` read.
 void left_copy(rtdm_ctx *c, int prod, const Mat &M, Mat &out, hipStream_t s)
 {
-    if (pairs_kind(c, prod)) pack_into(c, M, out, kPackLeft, s);
+    if (pairs_kind(c, prod)) pack_planes(c, M, out, kPackLeft, s);
     else transpose_into(c, M, out, s);
 }
 
@@ -890,7 +926,7 @@ const Mat &right_pairs(rtdm_ctx *c, const Mat &M, hipStream_t s)
 {
     c->Bp.pat = M.pat;
     c->Bp.cplx = M.cplx;
-    pack_into(c, M, c->Bp, kPackRight, s);
+    pack_planes(c, M, c->Bp, kPackRight, s);
     return c->Bp;
 }
 
@@ -901,12 +937,7 @@ const Mat &right_copy(rtdm_ctx *c, int prod, const Mat &M, hipStream_t s)
 }
 
 // Whether the products of kind `prod` have segmented runs of 2.
-bool runs_of_2(rtdm_ctx *c, int prod)
-{
-    auto &R = schedule(c, prod).runs;
-    auto r = R.find(2);
-    return r != R.end() && r->second->nch > 0 && r->second->seg.p;
-}
+bool runs_of_2(rtdm_ctx *c, int prod) { return segmented_runs(schedule(c, prod)); }
 
 bool use_cm(rtdm_ctx *c) { return c->b == 13 && (c->prec == RTDM_PREC_FP64 || c->prec == RTDM_PREC_FP32); }
 
@@ -1128,12 +1159,35 @@ void build_propagator(rtdm_ctx *c, double dt, hipStream_t s)
     if (use_cm(c)) left_copy(c, RTDM_PROD_UK, U, c->Uc, s);
 }
 
+// Whether the unitarity measure's products both run on the b = 4 kernel that
+// reads transposed right operands.
+bool unitarity_by_rows(rtdm_ctx *c)
+{
+    return b4_transposed(c, schedule(c, RTDM_PROD_SX)) && b4_transposed(c, schedule(c, RTDM_PROD_AT));
+}
+
 // D = P_P(U^dagger P_P(S U)) - S; sums into c->unit_sums.
 void unitarity_sums(rtdm_ctx *c, hipStream_t s)
 {
-    Mat &U = c->mats[RTDM_MAT_U];
-    product(c, RTDM_PROD_SX, c->mats[RTDM_MAT_S], U, c->V, 1.0, 0.0, s);
-    product(c, RTDM_PROD_UV, U, c->V, c->Z, 1.0, 0.0, s);
+    Mat &U = c->mats[RTDM_MAT_U], &S = c->mats[RTDM_MAT_S];
+    const int p = c->range_pat[R_P];
+    const std::tuple<int, int, int, int, int> plain{p, p, p, 0, 0};
+    if (unitarity_by_rows(c)) {
+        // U^dagger V as a plain product over row runs, U^dagger by rows in Bp and V
+        // written as a right operand: op(A) = U^dagger on the general kernel reads U by
+        // columns, one output per wave quarter (2,744 atoms, R 16: 7.1 -> 2.0 ms)
+        ProductOut t;
+        t.layout = 1;
+        product_key(c, RTDM_PROD_SX, prod_key(c, RTDM_PROD_SX), S, U, c->V, 1.0, 0.0, s, false, t);
+        const Pattern &pp = pat_of(c, R_P);
+        c->Bp.pat = p;
+        c->Bp.cplx = true;
+        launch_conj_transpose(s, pp.nnzb, c->b, pp.d_trans.p, U.re.p, U.im.p, c->Bp.re.p, c->Bp.im.p);
+        product_key(c, RTDM_PROD_UV, plain, c->Bp, c->V, c->Z, 1.0, 0.0, s, true);
+    } else {
+        product(c, RTDM_PROD_SX, S, U, c->V, 1.0, 0.0, s);
+        product(c, RTDM_PROD_UV, U, c->V, c->Z, 1.0, 0.0, s);
+    }
     launch_red_unitarity(s, pat_of(c, R_P).nnzb, c->b, c->p_to_hs.p, c->mats[RTDM_MAT_S].re.p,
                          c->Z.re.p, c->Z.im.p, c->partials.p);
     reduce_finish(c, s, c->unit_sums.p);
@@ -1629,9 +1683,15 @@ int rtdm_set_ranges(rtdm_ctx *c, double R_hs, double R_p, double R_k)
         c->Ap.re.release();
         c->Bp.re.release();
         c->Bp.im.release();
+        c->Lp.re.release();
+        c->Lp.im.release();
         if (c->pairs_real) {
             c->Ap.pat = c->range_pat[R_P];
             c->Ap.re.alloc(elems(c, c->Ap));
+        }
+        if (c->pairs_real && c->pairs_cplx && c->opt.propagator != RTDM_PROP_EM) {
+            c->Lp.re.alloc(pat_of(c, R_P).nnzb * 169);
+            c->Lp.im.alloc(pat_of(c, R_P).nnzb * 169);
         }
         bool b4 = false;         // some b = 4 products over enough runs for transposed right operands
         if (c->b == 4 && c->run_b4 == 16)
@@ -1647,7 +1707,7 @@ int rtdm_set_ranges(rtdm_ctx *c, double R_hs, double R_p, double R_k)
         }
     }
     // the unitarity product too when steps check it, so that rtdm_step allocates nothing
-    if (c->opt.unit_check_every > 0) schedule(c, RTDM_PROD_UV);
+    if (c->opt.unit_check_every > 0 && !unitarity_by_rows(c)) schedule(c, RTDM_PROD_UV);
     RT_HIP(hipDeviceSynchronize());
     API_END(c)
 }
@@ -1820,7 +1880,7 @@ int rtdm_download(rtdm_ctx *c, rtdm_mat mat, void *dst, int is_device, void *str
     Mat &M = mat == RTDM_MAT_K ? kmat(c, c->kick_sel) : c->mats[mat];
     const int64_t ne = elems(c, M);
     if (mat == RTDM_MAT_W && c->W_in_cm) {             // the step keeps W column-major
-        if (c->pairs_cplx) pack_into(c, c->Wc, M, kUnpackLeft, s);
+        if (c->pairs_cplx) pack_planes(c, c->Wc, M, kUnpackLeft, s);
         else transpose_into(c, c->Wc, M, s);
         c->W_in_cm = false;
     }
@@ -2086,7 +2146,7 @@ void copy_a(rtdm_ctx *c, hipStream_t s)
 {
     const Mat &A = c->mats[RTDM_MAT_A];
     // (the fused Taylor form makes Ap itself)
-    if (c->pairs_real && c->opt.precision != RTDM_PREC_FP64) pack_into(c, A, c->Ap, kPackLeft, s);
+    if (c->pairs_real && c->opt.precision != RTDM_PREC_FP64) pack_planes(c, A, c->Ap, kPackLeft, s);
     if (!c->pairs_real || c->opt.precision != RTDM_PREC_FP64) transpose_into(c, A, c->Ac, s);
 }
 
@@ -3276,7 +3336,7 @@ void multiply(rtdm_ctx *c, rtdm_mat Cm, rtdm_mat Am, rtdm_mat Bm, int op_a, int 
             // allocations keeps the column-major copies
             const bool pairs = !scratch && (A.cplx || B.cplx ? c->pairs_cplx : c->pairs_real) && runs_of_2(c, prod);
             auto left = [&](const Mat &M, Mat &out) {
-                if (pairs) pack_into(c, M, out, kPackLeft, s);
+                if (pairs) pack_planes(c, M, out, kPackLeft, s);
                 else transpose_into(c, M, out, s);
             };
             left(A, *pa);
@@ -3289,7 +3349,7 @@ void multiply(rtdm_ctx *c, rtdm_mat Cm, rtdm_mat Am, rtdm_mat Bm, int op_a, int 
             }
             if (ccm) {
                 product_cm(c, prod, *pa, *Bp, *pc, op_b, 1, alr, s, pairs);
-                if (pairs) pack_into(c, *pc, C, kUnpackLeft, s);
+                if (pairs) pack_planes(c, *pc, C, kUnpackLeft, s);
                 else transpose_into(c, *pc, C, s);
             } else {
                 product_cm(c, prod, *pa, *Bp, C, op_b, 0, alr, s, pairs);

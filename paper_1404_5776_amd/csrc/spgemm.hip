@@ -646,9 +646,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const int64_t e0 = off[c];
     const int ne = (int)(off[c + 1] - e0);
     typedef Mfma16<double>::acc_t acc_t;
-    acc_t rr[NJ], ri[NJ], ir[NJ];
+    // four sums per complex output (two, with the sign folded into an operand, were
+    // no faster at three waves and doubled the roundings of the real part: K of the
+    // 512-atom lattice after 4 steps 5.6e-15 -> 2.6e-15 from 64-bit arithmetic)
+    acc_t rr[NJ], ri[NJ], ir[NJ], ii[NJ];
 #pragma unroll
-    for (int t = 0; t < NJ; ++t) rr[t] = ri[t] = ir[t] = acc_t{0, 0, 0, 0};
+    for (int t = 0; t < NJ; ++t) rr[t] = ri[t] = ir[t] = ii[t] = acc_t{0, 0, 0, 0};
     const gdouble *gz = (const gdouble *)zero;
     // block indices of the group about to run, loaded one group ahead (the
     // group after a segment's last is the next segment's first)
@@ -681,25 +684,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             }
             fetch(min(g + 4, ge));
             auto mma = [&](double xa, double xai, const double (&xb)[NJ], const double (&xbi)[NJ]) {
-                if constexpr (AC && BC) {
-                    // re += a_r b_r + (-s a_i) b_i, im += (s a_r) b_i + a_i b_r, s = -1 for a conjugated B
-                    const double nai = CJB ? xai : -xai, sar = CJB ? -xa : xa;
 #pragma unroll
-                    for (int t = 0; t < NJ; ++t) {
-                        if (!((ACT >> t) & 1)) continue;
-                        rr[t] = Mfma16<double>::step(xa, xb[t], rr[t]);
-                        ri[t] = Mfma16<double>::step(sar, xbi[t], ri[t]);
-                        rr[t] = Mfma16<double>::step(nai, xbi[t], rr[t]);
-                        ri[t] = Mfma16<double>::step(xai, xb[t], ri[t]);
-                    }
-                } else {
-#pragma unroll
-                    for (int t = 0; t < NJ; ++t) {
-                        if (!((ACT >> t) & 1)) continue;
-                        rr[t] = Mfma16<double>::step(xa, xb[t], rr[t]);
-                        if (BC) ri[t] = Mfma16<double>::step(xa, xbi[t], ri[t]);
-                        if (AC) ir[t] = Mfma16<double>::step(xai, xb[t], ir[t]);
-                    }
+                for (int t = 0; t < NJ; ++t) {
+                    if (!((ACT >> t) & 1)) continue;
+                    rr[t] = Mfma16<double>::step(xa, xb[t], rr[t]);
+                    if (AC && BC) ii[t] = Mfma16<double>::step(xai, xbi[t], ii[t]);
+                    if (BC) ri[t] = Mfma16<double>::step(xa, xbi[t], ri[t]);
+                    if (AC) ir[t] = Mfma16<double>::step(xai, xb[t], ir[t]);
                 }
             };
 #pragma unroll
@@ -747,8 +738,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         for (int e = 0; e < 4; ++e) {
             const int row = 4 * e + q;
             if (row < B && col < B) {
-                const double re = rr[t][e];
-                const double im = (AC && BC) ? ri[t][e] : sb * ri[t][e] + ir[t][e];
+                const double re = rr[t][e] - sb * ii[t][e];
+                const double im = sb * ri[t][e] + ir[t][e];
                 const int64_t rm = (int64_t)p * BB + row * B + col;
                 const int64_t o = OUT == 0   ? rm
                                   : OUT == 1 ? (int64_t)p * BB + pair_at(B, row, col)
