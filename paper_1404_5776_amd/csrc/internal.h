@@ -200,10 +200,14 @@ void launch_spgemm_cm_split(hipStream_t s, const SpgemmArgs &a);
 // operand, c32 = alpha * P_C(A B) row-major FP32 (b = 13).
 void launch_spgemm_r32(hipStream_t s, const SpgemmArgs &a, const float *a32, const float *b32, float *c32,
                        const float *zero32);
+// b = 4 FP32 Taylor term alpha P_C(A B): a32 row-major, b32 and c32 (null: not
+// stored) with transposed blocks; u += u_sign * term (FP64, row-major).
+void launch_spgemm_b4_r32(hipStream_t s, const SpgemmArgs &a, const float *a32, const float *b32, float *c32, double *u,
+                          double u_sign);
 // out = (float)in, optionally transposing every b x b block.
 void launch_to_f32(hipStream_t s, int64_t nblocks, int b, int transpose, const double *in, float *out);
-// b = 4 blocks as BF16 hi / lo parts, 32 values per block (its 16 hi parts,
-// then its 16 lo parts; transpose: each block stored transposed)
+// b = 4 blocks as BF16 hi / lo parts, 32 values per block (per row its four hi
+// parts, then its four lo parts; transpose: each block stored transposed)
 void launch_to_bf16x2(hipStream_t s, int64_t nblocks, int transpose, const double *in, short *out);
 // BF16x3 Taylor term at b = 4 over row runs of 16 (a.ch_*, alpha a.alpha_re) from split
 // operands: u += u_sign * tau, and tau stored split and transposed in c16 (if set)

@@ -1090,7 +1090,8 @@ void build_propagator(rtdm_ctx *c, double dt, hipStream_t s)
             }
         } else if (low32 && k >= n0) {
             if (!in32) {
-                launch_to_f32(s, pat_of(c, R_P).nnzb, c->b, fused ? 1 : 0, c->tau[cur].re.p, c->tau32[cur].p);
+                launch_to_f32(s, pat_of(c, R_P).nnzb, c->b, c->b == 4 && !fused ? 1 : 0, c->tau[cur].re.p,
+                              c->tau32[cur].p);   // b = 4: transposed blocks, as the fused form keeps tau
                 in32 = true;
             }
             Sched &S = schedule(c, RTDM_PROD_AT);
@@ -1120,13 +1121,18 @@ void build_propagator(rtdm_ctx *c, double dt, hipStream_t s)
             const bool rec = c->timing && !c->capturing;
             const size_t ev = 2 * c->recs.size();
             if (rec) RT_HIP(hipEventRecord(event_at(c, ev), s));
-            launch_spgemm_r32(s, a, c->Ac32.p, c->tau32[cur].p, c->tau32[1 - cur].p, c->zero32.p);
+            // (at b = 4 the kernel adds the term into U itself)
+            const double sign = (k % 4 == 0 || k % 4 == 3) ? 1.0 : -1.0;
+            if (c->b == 4)
+                launch_spgemm_b4_r32(s, a, c->Ac32.p, c->tau32[cur].p, k < p ? c->tau32[1 - cur].p : nullptr,
+                                     (k % 2 == 0) ? U.re.p : U.im.p, sign);
+            else launch_spgemm_r32(s, a, c->Ac32.p, c->tau32[cur].p, c->tau32[1 - cur].p, c->zero32.p);
             if (rec) {
                 RT_HIP(hipEventRecord(event_at(c, ev + 1), s));
                 const double b3 = (double)c->b * c->b * c->b;
                 c->recs.push_back({RTDM_PROD_AT, (int)ev, (double)S.ntrip * 2.0 * b3});
             }
-            add_term(k, nullptr, c->tau32[1 - cur].p);
+            if (c->b != 4) add_term(k, nullptr, c->tau32[1 - cur].p);
         } else if (fused) {
             ProductOut out;
             out.layout = c->b == 13 ? kOutRight : 1;

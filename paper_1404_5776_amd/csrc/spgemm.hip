@@ -2052,23 +2052,43 @@ __global__ __launch_bounds__(256) void k_spgemm_q4jr32(
 }
 
 // Real FP32-storage b = 4 product (the late Taylor terms of the fp32_taylor
-// form): FP32 row-major blocks, v_mfma_f32_4x4x1_16b with FP32 accumulation,
-// FP32 output scaled by alpha; lane 4 blk + r holds row r of A_blk and
-// column r of B_blk.  RUNS: one row run of 16 outputs per wave (entries
-// shared by all blocks, b = 4 slot order); otherwise 16 consecutive outputs
-// per wave, each with its own triple list.
+// form): A in FP32 row-major blocks, B in FP32 transposed blocks, so that a
+// lane's row of A and column of B are one 16-byte load each;
+// v_mfma_f32_4x4x1_16b with FP32 accumulation, lane 4 blk + r holding row r
+// of A_blk and column r of B_blk.  The term alpha * sum is added into the FP64
+// plane u (u += u_sign * term: the propagator's sum) and, when c32 is set,
+// stored in FP32 transposed blocks as the next term's right operand.  RUNS:
+// one row run of 16 outputs per wave (entries shared by all blocks, b = 4
+// slot order); otherwise 16 consecutive outputs per wave, each with its own
+// triple list.  Bound: the vector-memory address unit (15 cycles per 16-byte
+// load, 5 per 4-byte one): 22 cycles an entry over runs, where one load of A
+// an entry and four 4-byte loads of B took 45.  2,744 atoms, R 16, per term
+// with its sum: 0.78 -> 0.49 ms.
+struct F32Idx8 {
+    int a, b[8];
+};
+// h += A_s B_s over entries s = E .. 7, A_s broadcast from MFMA block s
+template <int E>
+__device__ inline void mfma_f32_8(const f32x4 &xa, const f32x4 (&xb)[8], f32x4 &h)
+{
+#pragma unroll
+    for (int k = 0; k < 4; ++k) h = __builtin_amdgcn_mfma_f32_4x4x1f32(xa[k], xb[E][k], h, 4, E, 0);
+    if constexpr (E < 7) mfma_f32_8<E + 1>(xa, xb, h);
+}
+
 template <bool RUNS>
 __global__ __launch_bounds__(256) void k_spgemm_b4r32(
     int64_t n, const int64_t *__restrict__ off, const int2 *__restrict__ trip, const int32_t *__restrict__ ea,
     const int32_t *__restrict__ eb, const int32_t *__restrict__ rout, const float *__restrict__ a,
-    const float *__restrict__ b, float *__restrict__ c32, float alpha)
+    const float *__restrict__ b, float *__restrict__ c32, float alpha, double *__restrict__ u, double u_sign,
+    int remap)
 {
     const int lane = threadIdx.x & 63;
     const int blk = lane >> 2, r = lane & 3;
-    const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t c0 = RUNS ? wv : wv * 16;
-    if (c0 >= n) return;                       // uniform across the wave
-    const int64_t c = RUNS ? (int64_t)rout[wv * 16 + blk] : c0 + blk;
+    const int64_t nwv = RUNS ? n : (n + 15) / 16;
+    const int64_t wv = xcd_block((nwv + 3) / 4, remap) * 4 + (threadIdx.x >> 6);
+    if (wv >= nwv) return;                     // uniform across the wave
+    const int64_t c = RUNS ? (int64_t)rout[wv * 16 + blk] : wv * 16 + blk;
     const bool live = RUNS ? c >= 0 : c < n;
     const int64_t t0 = RUNS ? off[wv] : (live ? off[c] : 0);
     const int nt = RUNS ? (int)(off[wv + 1] - t0) : (live ? (int)(off[c + 1] - t0) : 0);
@@ -2079,73 +2099,97 @@ __global__ __launch_bounds__(256) void k_spgemm_b4r32(
     }
     const int slot = (blk & 3) * 4 + (blk >> 2);
     f32x4 h = {0, 0, 0, 0};
-    auto load_ops = [&](int2 ab, float (&xa)[4], float (&xb)[4]) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) xa[k] = xb[k] = 0.0f;
+    auto load_ops = [&](int2 ab, f32x4 &xa, f32x4 &xb) {
+        xa = xb = f32x4{0, 0, 0, 0};
         if (ab.y >= 0) {
-            const f32x4 ar4 = *reinterpret_cast<const f32x4 *>(a + (int64_t)ab.x * 16 + r * 4);   // A[r][0..3]
-            const int64_t pb = (int64_t)ab.y * 16 + r;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                xa[k] = ar4[k];
-                xb[k] = b[pb + k * 4];                                                         // B[k][r]
-            }
+            xa = *reinterpret_cast<const f32x4 *>(a + (int64_t)ab.x * 16 + r * 4);   // A[r][0..3]
+            xb = *reinterpret_cast<const f32x4 *>(b + (int64_t)ab.y * 16 + r * 4);   // B[0..3][r]
         }
     };
+    auto products = [&](const f32x4 &xa, const f32x4 &xb) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) h = __builtin_amdgcn_mfma_f32_4x4x1f32(xa[k], xb[k], h, 0, 0, 0);
+    };
     if constexpr (RUNS) {
-        // software pipeline as in b4_run_entries: indices two entries ahead,
-        // operands one entry ahead, products in entry order
-        auto load_idx = [&](int t) { return make_int2(ea[t0 + t], eb[(t0 + t) * 16 + slot]); };
-        if (nt > 0) {
-            float xa[4], xb[4];
-            int2 ab_n = make_int2(0, -1);
-            const int2 ab0 = load_idx(0);
-            if (1 < nt) ab_n = load_idx(1);
-            load_ops(ab0, xa, xb);
-            for (int t = 0; t < nt; ++t) {
-                int2 ab_nn = make_int2(0, -1);
-                if (t + 2 < nt) ab_nn = load_idx(t + 2);
-                float na[4] = {0, 0, 0, 0}, nb[4] = {0, 0, 0, 0};
-                if (t + 1 < nt) load_ops(ab_n, na, nb);
+        // Eight entries at a time: lane 4 blk + r loads row r of the A block of
+        // entry blk % 8, and the MFMAs of entry s broadcast block s's rows to all
+        // sixteen blocks (cbsz 4, abid s), so one load serves the A of eight
+        // entries.  The next eight entries' indices are loaded ahead.
+        auto load_idx = [&](int t) {
+            F32Idx8 x{-1, {-1, -1, -1, -1, -1, -1, -1, -1}};
+            if (t + (blk & 7) < nt) x.a = ea[t0 + t + (blk & 7)];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) h = __builtin_amdgcn_mfma_f32_4x4x1f32(xa[k], xb[k], h, 0, 0, 0);
+            for (int e = 0; e < 8; ++e)
+                if (t + e < nt) x.b[e] = eb[(t0 + t + e) * 16 + slot];
+            return x;
+        };
+        F32Idx8 cur = load_idx(0);
+        for (int t = 0; t < nt; t += 8) {
+            f32x4 xa = {0, 0, 0, 0}, xb[8];
+            if (cur.a >= 0) xa = *reinterpret_cast<const f32x4 *>(a + (int64_t)cur.a * 16 + r * 4);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    xa[k] = na[k];
-                    xb[k] = nb[k];
-                }
-                ab_n = ab_nn;
+            for (int e = 0; e < 8; ++e) {
+                xb[e] = f32x4{0, 0, 0, 0};
+                if (cur.b[e] >= 0) xb[e] = *reinterpret_cast<const f32x4 *>(b + (int64_t)cur.b[e] * 16 + r * 4);
             }
+            cur = load_idx(t + 8);
+            mfma_f32_8<0>(xa, xb, h);
         }
     } else {
         for (int t = 0; t < ntmax; ++t) {
             const int2 ab = t < nt ? trip[t0 + t] : make_int2(0, -1);
-            float xa[4], xb[4];
+            f32x4 xa, xb;
             load_ops(ab, xa, xb);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) h = __builtin_amdgcn_mfma_f32_4x4x1f32(xa[k], xb[k], h, 0, 0, 0);
+            products(xa, xb);
         }
     }
     if (!live) return;
+    f32x4 v;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) c32[c * 16 + e * 4 + r] = alpha * h[e];
+    for (int e = 0; e < 4; ++e) {
+        v[e] = alpha * h[e];
+        const int64_t o = c * 16 + e * 4 + r;
+        u[o] += u_sign * (double)v[e];
+    }
+    if (c32) *reinterpret_cast<f32x4 *>(c32 + c * 16 + r * 4) = v;   // column r of the block
+}
+
+// The b = 4 FP32 Taylor term: b32 and c32 (nullable) with transposed blocks, u += u_sign * term.
+void launch_spgemm_b4_r32(hipStream_t s, const SpgemmArgs &a, const float *a32, const float *b32, float *c32, double *u,
+                          double u_sign)
+{
+    RT_CHECK(a.b == 4 && u, RTDM_E_ARG, "b = 4 FP32 Taylor terms are summed as they are written");
+    const bool runs = a.nch > 0;
+    RT_CHECK(!runs || a.nj == 16, RTDM_E_ARG, "b = 4 row runs hold 16 outputs");
+    if (!runs && a.nout == 0) return;
+    const int64_t nwg = ((runs ? a.nch : (a.nout + 15) / 16) + 3) / 4;
+    const int remap = xcd_chunk_for(nwg);
+    const dim3 g(xcd_grid(nwg, remap)), t(256);
+    if (runs)
+        hipLaunchKernelGGL(k_spgemm_b4r32<true>, g, t, 0, s, a.nch, a.ch_off, nullptr, a.ch_a, a.ch_b, a.ch_out, a32,
+                           b32, c32, (float)a.alpha_re, u, u_sign, remap);
+    else
+        hipLaunchKernelGGL(k_spgemm_b4r32<false>, g, t, 0, s, a.nout, a.off, a.trip, nullptr, nullptr, nullptr, a32,
+                           b32, c32, (float)a.alpha_re, u, u_sign, remap);
+    RT_HIP(hipGetLastError());
 }
 
 // BF16 x 2 storage of b = 4 blocks for the BF16x3 late Taylor terms: x =
 // hi + lo with the split of the register-split kernels (Split4<0>: round to
 // FP32, hi its BF16 rounding, lo that of the remainder).  Block p takes 32
-// values, its 16 hi parts then its 16 lo parts (64 bytes, one memory sector
-// like an FP32 block); `transpose` stores each block transposed, so that
-// column r of a right operand is four contiguous values.
+// values (64 bytes, one memory sector like an FP32 block): per row its four hi
+// parts, then its four lo parts, one 16-byte load of a lane; `transpose`
+// stores each block transposed (the columns of a right operand).
 __global__ void k_to_bf16x2(int64_t n, int transpose, const double *__restrict__ in, short *__restrict__ out)
 {
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
         const int w = (int)(e & 15);
-        const int64_t o = (e >> 4) * 32 + (transpose ? (w & 3) * 4 + (w >> 2) : w);
+        const int row = transpose ? w & 3 : w >> 2, k = transpose ? w >> 2 : w & 3;
+        const int64_t o = (e >> 4) * 32 + row * 8 + k;
         short h, l;
         Split4<0>::split(in[e], 1.0f, h, l);
         out[o] = h;
-        out[o + 16] = l;
+        out[o + 4] = l;
     }
 }
 
@@ -2160,65 +2204,67 @@ void launch_to_bf16x2(hipStream_t s, int64_t nblocks, int transpose, const doubl
 }
 
 // BF16x3 late Taylor term at b = 4 over row runs of 16 outputs, operands
-// stored split (launch_to_bf16x2: A row-major, tau transposed): one wave per
-// run, lane 4 blk + r holding row r of the entry's A block and column r of
-// output blk's B block as four BF16 values per part (8-byte loads), three
+// stored split (launch_to_bf16x2: A by rows, tau by columns): one wave per
+// run, lane 4 blk + r holding row r of A and column r of output blk's B as
+// four BF16 values per part, both parts one 16-byte load; three
 // v_mfma_f32_4x4x4_16b_bf16 per entry (hi hi, then hi lo and lo hi into a
-// second accumulator).  The result tau = alpha (h + m) is added into the FP64
-// plane u (u += u_sign tau: the propagator's sum) and, when c16 is set,
-// stored split and transposed as the next term's right operand.  The split,
-// the products and their order per output are those of the register-split
-// kernel (k_spgemm_b4x<..., 1, true>); this one moves half of its operand
-// bytes per triple (two 16-bit values instead of one FP64 per element).
+// second accumulator), eight entries at a time with A broadcast from one
+// MFMA block per entry as in k_spgemm_b4r32.  The result tau = alpha (h + m)
+// is added into the FP64 plane u (u += u_sign tau: the propagator's sum) and,
+// when c16 is set, stored split and transposed as the next term's right
+// operand.  The split, the products and their order per output are those of
+// the register-split kernel (k_spgemm_b4x<..., 1, true>).  Per entry 22
+// cycles of the vector-memory address unit (70 with 8-byte loads of each part).
+typedef short bf16q __attribute__((ext_vector_type(4)));
+typedef short bf16o __attribute__((ext_vector_type(8)));
+template <int E>
+__device__ inline void mfma_bf16_8(bf16o xa, const bf16o (&xb)[8], f32x4 &h, f32x4 &m)
+{
+    const bf16q ah = __builtin_shufflevector(xa, xa, 0, 1, 2, 3), al = __builtin_shufflevector(xa, xa, 4, 5, 6, 7);
+    const bf16q bh = __builtin_shufflevector(xb[E], xb[E], 0, 1, 2, 3),
+                bl = __builtin_shufflevector(xb[E], xb[E], 4, 5, 6, 7);
+    h = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ah, bh, h, 4, E, 0);
+    m = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ah, bl, m, 4, E, 0);
+    m = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(al, bh, m, 4, E, 0);
+    if constexpr (E < 7) mfma_bf16_8<E + 1>(xa, xb, h, m);
+}
+
 __global__ __launch_bounds__(256) void k_spgemm_b4r16(
     int64_t nch, const int64_t *__restrict__ off, const int32_t *__restrict__ ea, const int32_t *__restrict__ eb,
     const int32_t *__restrict__ rout, const short *__restrict__ a16, const short *__restrict__ b16,
-    short *__restrict__ c16, double alpha, double *__restrict__ u, double u_sign)
+    short *__restrict__ c16, double alpha, double *__restrict__ u, double u_sign, int remap)
 {
-    typedef short v4 __attribute__((ext_vector_type(4)));
     const int lane = threadIdx.x & 63;
     const int blk = lane >> 2, r = lane & 3;
-    const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t wv = xcd_block((nch + 3) / 4, remap) * 4 + (threadIdx.x >> 6);
     if (wv >= nch) return;                     // uniform across the wave
     const int64_t c = rout[wv * 16 + blk];
     const int64_t t0 = off[wv];
     const int nt = (int)(off[wv + 1] - t0);
     const int slot = (blk & 3) * 4 + (blk >> 2);
     f32x4 h = {0, 0, 0, 0}, m = {0, 0, 0, 0};
-    struct Ops {
-        v4 ah, al, bh, bl;
+    auto load_idx = [&](int t) {
+        F32Idx8 x{-1, {-1, -1, -1, -1, -1, -1, -1, -1}};
+        if (t + (blk & 7) < nt) x.a = ea[t0 + t + (blk & 7)];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (t + e < nt) x.b[e] = eb[(t0 + t + e) * 16 + slot];
+        return x;
     };
-    auto load_idx = [&](int t) { return make_int2(ea[t0 + t], eb[(t0 + t) * 16 + slot]); };
-    auto load_ops = [&](int2 ab, Ops &o) {
-        o.ah = o.al = o.bh = o.bl = v4{0, 0, 0, 0};
-        if (ab.y >= 0) {
-            const short *pa = a16 + (int64_t)ab.x * 32 + r * 4, *pb = b16 + (int64_t)ab.y * 32 + r * 4;
-            o.ah = *reinterpret_cast<const v4 *>(pa);        // A[r][0..3]
-            o.al = *reinterpret_cast<const v4 *>(pa + 16);
-            o.bh = *reinterpret_cast<const v4 *>(pb);        // B[0..3][r]
-            o.bl = *reinterpret_cast<const v4 *>(pb + 16);
+    F32Idx8 cur = load_idx(0);
+    for (int t = 0; t < nt; t += 8) {
+        bf16o xa = {}, xb[8];
+        if (cur.a >= 0) xa = *reinterpret_cast<const bf16o *>(a16 + (int64_t)cur.a * 32 + r * 8);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            xb[e] = bf16o{};
+            if (cur.b[e] >= 0) xb[e] = *reinterpret_cast<const bf16o *>(b16 + (int64_t)cur.b[e] * 32 + r * 8);
         }
-    };
-    if (nt > 0) {
-        // software pipeline as in b4_run_entries: indices two entries ahead, operands one
-        Ops cur, nxt;
-        int2 ab_n = make_int2(0, -1);
-        const int2 ab0 = load_idx(0);
-        if (1 < nt) ab_n = load_idx(1);
-        load_ops(ab0, cur);
-        for (int t = 0; t < nt; ++t) {
-            int2 ab_nn = make_int2(0, -1);
-            if (t + 2 < nt) ab_nn = load_idx(t + 2);
-            if (t + 1 < nt) load_ops(ab_n, nxt);
-            h = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(cur.ah, cur.bh, h, 0, 0, 0);
-            m = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(cur.ah, cur.bl, m, 0, 0, 0);
-            m = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(cur.al, cur.bh, m, 0, 0, 0);
-            cur = nxt;
-            ab_n = ab_nn;
-        }
+        cur = load_idx(t + 8);
+        mfma_bf16_8<0>(xa, xb, h, m);
     }
     if (c < 0) return;
-    v4 sh, sl;
+    bf16o st;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const double v = alpha * ((double)h[e] + 1.0 * (double)m[e]);
@@ -2226,21 +2272,19 @@ __global__ __launch_bounds__(256) void k_spgemm_b4r16(
         u[o] = u[o] + u_sign * v;
         short hh, ll;
         Split4<0>::split(v, 1.0f, hh, ll);
-        sh[e] = hh;
-        sl[e] = ll;
+        st[e] = hh;
+        st[e + 4] = ll;
     }
-    if (c16) {
-        *reinterpret_cast<v4 *>(c16 + c * 32 + r * 4) = sh;        // transposed: column r of the block
-        *reinterpret_cast<v4 *>(c16 + c * 32 + 16 + r * 4) = sl;
-    }
+    if (c16) *reinterpret_cast<bf16o *>(c16 + c * 32 + r * 8) = st;   // column r of the block
 }
 
 void launch_spgemm_r16(hipStream_t s, const SpgemmArgs &a, const short *a16, const short *b16, short *c16,
                        double *u, double u_sign)
 {
     RT_CHECK(a.b == 4 && a.nch > 0 && a.nj == 16, RTDM_E_ARG, "split BF16 Taylor terms need b = 4 row runs of 16");
-    hipLaunchKernelGGL(k_spgemm_b4r16, dim3((unsigned)((a.nch + 3) / 4)), dim3(256), 0, s, a.nch, a.ch_off, a.ch_a,
-                       a.ch_b, a.ch_out, a16, b16, c16, a.alpha_re, u, u_sign);
+    const int remap = xcd_chunk_for((a.nch + 3) / 4);
+    hipLaunchKernelGGL(k_spgemm_b4r16, dim3(xcd_grid((a.nch + 3) / 4, remap)), dim3(256), 0, s, a.nch, a.ch_off, a.ch_a,
+                       a.ch_b, a.ch_out, a16, b16, c16, a.alpha_re, u, u_sign, remap);
     RT_HIP(hipGetLastError());
 }
 
@@ -2248,19 +2292,7 @@ void launch_spgemm_r32(hipStream_t s, const SpgemmArgs &a, const float *a32, con
                        const float *zero32)
 {
     if (a.nout == 0) return;
-    RT_CHECK(a.b == 13 || a.b == 4, RTDM_E_UNSUPPORTED, "FP32 step products need b = 4 or 13");
-    if (a.b == 4) {
-        if (a.nch > 0) {
-            RT_CHECK(a.nj == 16, RTDM_E_ARG, "b = 4 row runs hold 16 outputs");
-            hipLaunchKernelGGL(k_spgemm_b4r32<true>, dim3((unsigned)((a.nch + 3) / 4)), dim3(256), 0, s, a.nch,
-                               a.ch_off, nullptr, a.ch_a, a.ch_b, a.ch_out, a32, b32, c32, (float)a.alpha_re);
-        } else {
-            hipLaunchKernelGGL(k_spgemm_b4r32<false>, dim3((unsigned)((a.nout + 63) / 64)), dim3(256), 0, s,
-                               a.nout, a.off, a.trip, nullptr, nullptr, nullptr, a32, b32, c32, (float)a.alpha_re);
-        }
-        RT_HIP(hipGetLastError());
-        return;
-    }
+    RT_CHECK(a.b == 13, RTDM_E_UNSUPPORTED, "FP32 step products of this form need b = 13");
     if (a.nch > 0) {
         const int remap = xcd_chunk();
         const unsigned grid = xcd_grid((a.nch + 3) / 4, remap);
