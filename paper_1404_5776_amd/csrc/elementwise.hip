@@ -23,28 +23,33 @@ __device__ inline double wave_sum(double v)
     return v;
 }
 
-// Fixed-tree reduction of 4 slots (0..2 sums, 3 max) over a workgroup of kT threads.
+// Reduction of 4 slots (0..2 sums, 3 max) over a workgroup of kT threads, in a
+// fixed order: a shuffle tree per wave, then the waves' values in wave order.
+// The result on every thread; sh holds 4 kT / 64 doubles and may be used again
+// after the next workgroup barrier.
 __device__ inline void block_reduce4(double v[4], double *sh)
 {
-    const int t = threadIdx.x;
+    const int wv = threadIdx.x >> 6;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) sh[k * kT + t] = v[k];
-    __syncthreads();
-    for (int w = kT / 2; w >= 1; w >>= 1) {
-        if (t < w) {
+    for (int k = 0; k < 3; ++k) v[k] = wave_sum(v[k]);
 #pragma unroll
-            for (int k = 0; k < 3; ++k) sh[k * kT + t] += sh[k * kT + t + w];
-            sh[3 * kT + t] = fmax(sh[3 * kT + t], sh[3 * kT + t + w]);
-        }
-        __syncthreads();
+    for (int o = 32; o >= 1; o >>= 1) v[3] = fmax(v[3], __shfl_xor(v[3], o, 64));
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sh[4 * wv + k] = v[k];
     }
+    __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = sh[k * kT];
+    for (int k = 0; k < 4; ++k) {
+        v[k] = sh[k];
+#pragma unroll
+        for (int w = 1; w < kT / 64; ++w) v[k] = k < 3 ? v[k] + sh[4 * w + k] : fmax(v[k], sh[4 * w + k]);
+    }
 }
 
 __device__ inline void write_partials(double v[4], double *partials)
 {
-    __shared__ double sh[4 * kT];
+    __shared__ double sh[4 * (kT / 64)];
     block_reduce4(v, sh);
     if (threadIdx.x == 0) {
 #pragma unroll
@@ -92,56 +97,98 @@ void launch_add_identity(hipStream_t s, int64_t n_atoms, int b, const int32_t *d
     RT_HIP(hipGetLastError());
 }
 
-__global__ void k_kick(int64_t nnzb, int b, const int32_t *__restrict__ rowof,
-                       const int32_t *__restrict__ col, const double *__restrict__ xyz, double kx,
-                       double ky, double kz, double *__restrict__ kr, double *__restrict__ ki)
+// K_ij *= exp(i kappa . (r_i - r_j)), kappa that of atom i's group where `group`
+// is set (pairs never cross groups in a block-diagonal batch: kappa[3 g ..]).
+// kr_t, ki_t (nullable, b = 4 or 13): K as a right operand as well (see
+// k_hermitize).  Bound: HBM (two planes read and written); a phase per block
+// shared by 32 lanes instead of one per element was slower (4,096 atoms b = 13
+// 1.0 -> 1.9 ms).
+template <int B, typename I>
+__global__ __launch_bounds__(kT) void k_kick(I n, int b, const int32_t *__restrict__ rowof,
+                                             const int32_t *__restrict__ col, const double *__restrict__ xyz,
+                                             const int32_t *__restrict__ group, const double *__restrict__ kappa,
+                                             double kx, double ky, double kz, double *__restrict__ kr,
+                                             double *__restrict__ ki, double *__restrict__ kr_t,
+                                             double *__restrict__ ki_t)
 {
-    const int bb = b * b;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nnzb * bb;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t p = e / bb;
-        const int i = rowof[p], j = col[p];
+    const I bs = B ? B : b, bb = bs * bs;
+    for (I e = (I)blockIdx.x * kT + threadIdx.x; e < n; e += (I)gridDim.x * kT) {
+        const I p = e / bb, w = e - p * bb;
+        const int64_t i = rowof[p], j = col[p];
+        if (group) {
+            const int64_t g = group[i];
+            kx = kappa[3 * g];
+            ky = kappa[3 * g + 1];
+            kz = kappa[3 * g + 2];
+        }
         const double ph = kx * (xyz[3 * i] - xyz[3 * j]) + ky * (xyz[3 * i + 1] - xyz[3 * j + 1]) +
                           kz * (xyz[3 * i + 2] - xyz[3 * j + 2]);
         double sn, cs;
         sincos(ph, &sn, &cs);
         const double xr = kr[e], xi = ki[e];
-        kr[e] = cs * xr - sn * xi;
-        ki[e] = cs * xi + sn * xr;
+        const double vr = cs * xr - sn * xi, vi = cs * xi + sn * xr;
+        kr[e] = vr;
+        ki[e] = vi;
+        if (B && kr_t) {
+            const I a = w / bs, c = w - a * bs;
+            const int64_t o = (int64_t)p * bb + (B == 4 ? (int)(c * 4 + a) : pair_at(B, (int)c, (int)a));
+            kr_t[o] = vr;
+            ki_t[o] = vi;
+        }
     }
 }
 
-void launch_kick(hipStream_t s, int64_t nnzb, int b, const int32_t *rowof, const int32_t *col,
-                 const double *xyz, double kx, double ky, double kz, double *kr, double *ki)
+void launch_kick(hipStream_t s, int64_t nnzb, int b, const int32_t *rowof, const int32_t *col, const double *xyz,
+                 const int32_t *group, const double *kappa_g, const double kappa[3], double *kr, double *ki,
+                 double *kr_t, double *ki_t)
 {
     const int64_t n = nnzb * b * b;
     if (n == 0) return;
-    int64_t g = (n + kT - 1) / kT;
-    if (g > 65536) g = 65536;
-    hipLaunchKernelGGL(k_kick, dim3((unsigned)g), dim3(kT), 0, s, nnzb, b, rowof, col, xyz, kx, ky,
-                       kz, kr, ki);
+    RT_CHECK(!kr_t || b == 4 || b == 13, RTDM_E_ARG, "right-operand copies need b = 4 or 13");
+    const double kx = kappa ? kappa[0] : 0.0, ky = kappa ? kappa[1] : 0.0, kz = kappa ? kappa[2] : 0.0;
+    const int64_t g = std::min<int64_t>((n + kT - 1) / kT, 65536);
+    const bool small = n + g * kT < ((int64_t)1 << 32);   // 32-bit index arithmetic
+#define RT_KICK(B_, I_)                                                                                          \
+    hipLaunchKernelGGL((k_kick<B_, I_>), dim3((unsigned)g), dim3(kT), 0, s, (I_)n, b, rowof, col, xyz, group,    \
+                       kappa_g, kx, ky, kz, kr, ki, kr_t, ki_t)
+    if (b == 4 && small) RT_KICK(4, uint32_t);
+    else if (b == 4) RT_KICK(4, int64_t);
+    else if (b == 13 && small) RT_KICK(13, uint32_t);
+    else if (b == 13) RT_KICK(13, int64_t);
+    else if (small) RT_KICK(0, uint32_t);
+    else RT_KICK(0, int64_t);
+#undef RT_KICK
     RT_HIP(hipGetLastError());
 }
 
-// K_ij[a][c] = (Kn_ij[a][c] + conj(Kn_ji[c][a])) / 2
-__global__ __launch_bounds__(kT) void k_hermitize(int64_t nnzb, int b,
-                                                  const int32_t *__restrict__ trans,
+// K_ij[a][c] = (Kn_ij[a][c] + conj(Kn_ji[c][a])) / 2.  B: the block size when
+// fixed at compile time (4, 13: the index divisions by constants), else 0.
+// kr_t, ki_t (nullable, B = 4 or 13): K as the right operand of the next U K
+// (transposed blocks, right pairs), written here instead of by a pass of its
+// own over K before the product.
+template <int B, typename I>
+__global__ __launch_bounds__(kT) void k_hermitize(I n, int b, const int32_t *__restrict__ trans,
                                                   const double *__restrict__ knr,
                                                   const double *__restrict__ kni,
                                                   double *__restrict__ kr, double *__restrict__ ki,
+                                                  double *__restrict__ kr_t, double *__restrict__ ki_t,
                                                   double *__restrict__ partials)
 {
-    const int bb = b * b;
+    const I bs = B ? B : b, bb = bs * bs;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nnzb * bb;
-         e += (int64_t)kRedBlocks * kT) {
-        const int64_t p = e / bb;
-        const int w = (int)(e - p * bb);
-        const int a = w / b, c = w - a * b;
-        const int64_t pe = (int64_t)trans[p] * bb + c * b + a;
+    for (I e = (I)blockIdx.x * kT + threadIdx.x; e < n; e += (I)kRedBlocks * kT) {
+        const I p = e / bb, w = e - p * bb;
+        const I a = w / bs, c = w - a * bs;
+        const int64_t pe = (int64_t)trans[p] * bb + c * bs + a;
         const double xr = knr[e], xi = kni[e], yr = knr[pe], yi = -kni[pe];
-        kr[e] = 0.5 * (xr + yr);
-        ki[e] = 0.5 * (xi + yi);
+        const double hr = 0.5 * (xr + yr), hi = 0.5 * (xi + yi);
+        kr[e] = hr;
+        ki[e] = hi;
+        if (B && kr_t) {
+            const int64_t o = (int64_t)p * bb + (B == 4 ? (int)(c * 4 + a) : pair_at(B, (int)c, (int)a));
+            kr_t[o] = hr;
+            ki_t[o] = hi;
+        }
         const double dr = xr - yr, di = xi - yi;
         v[0] += dr * dr + di * di;
         v[1] += xr * xr + xi * xi;
@@ -150,51 +197,99 @@ __global__ __launch_bounds__(kT) void k_hermitize(int64_t nnzb, int b,
 }
 
 void launch_hermitize(hipStream_t s, int64_t nnzb, int b, const int32_t *trans, const double *knr,
-                      const double *kni, double *kr, double *ki, double *partials)
+                      const double *kni, double *kr, double *ki, double *partials, double *kr_t, double *ki_t)
 {
-    hipLaunchKernelGGL(k_hermitize, dim3(kRedBlocks), dim3(kT), 0, s, nnzb, b, trans, knr, kni, kr,
-                       ki, partials);
+    RT_CHECK(!kr_t || b == 4 || b == 13, RTDM_E_ARG, "right-operand copies need b = 4 or 13");
+    const int64_t n = nnzb * b * b;
+    const bool small = n + (int64_t)kRedBlocks * kT < ((int64_t)1 << 32);   // 32-bit index arithmetic
+#define RT_HERM(B_, I_)                                                                                       \
+    hipLaunchKernelGGL((k_hermitize<B_, I_>), dim3(kRedBlocks), dim3(kT), 0, s, (I_)n, b, trans, knr, kni, kr, ki, \
+                       kr_t, ki_t, partials)
+    if (b == 4 && small) RT_HERM(4, uint32_t);
+    else if (b == 4) RT_HERM(4, int64_t);
+    else if (b == 13 && small) RT_HERM(13, uint32_t);
+    else if (b == 13) RT_HERM(13, int64_t);
+    else if (small) RT_HERM(0, uint32_t);
+    else RT_HERM(0, int64_t);
+#undef RT_HERM
     RT_HIP(hipGetLastError());
 }
 
-// One wave per atom: q_i = Re sum_{j in S row i, (i,j) in K} sum_{a,c} K_ij[a][c] S_ji[c][a]
-__global__ __launch_bounds__(kT) void k_mulliken(int64_t n_atoms, int b,
-                                                 const int64_t *__restrict__ s_ptr,
+// q_i = Re sum_{j in S row i, (i,j) in K} sum_{a,c} K_ij[a][c] S_ji[c][a], W waves
+// per atom, every K of a kick set in one launch.  The row's (block, element)
+// pairs are flattened, 64 W per pass, so every lane works and a pass has
+// 64 W independent loads.  Bound: the chain of dependent loads of a wave (the
+// block maps, then K and S) and, before the block size was a constant, the
+// 64-bit divisions of every pass.  Four waves per atom where the atoms alone
+// leave the chip idle or an atom is long (b > 4): 64 atoms b = 4 9.7 -> 4.5
+// us; three kicks of 380 atoms in clusters b = 13, three launches of 80 -> one
+// of 50 us.
+// prev (nullable) receives the old q_i (keep_old) or the new one, ref
+// (nullable) the new one of the first K.
+template <int B, int W>
+__global__ __launch_bounds__(kT) void k_mulliken(int n_atoms, int n_k, int b, const int64_t *__restrict__ s_ptr,
                                                  const int32_t *__restrict__ s_trans,
-                                                 const int32_t *__restrict__ s_to_k,
-                                                 const double *__restrict__ sv,
-                                                 const double *__restrict__ kr,
-                                                 double *__restrict__ q)
+                                                 const int32_t *__restrict__ s_to_k, const double *__restrict__ sv,
+                                                 KPlanes kp, double *__restrict__ q, double *__restrict__ prev,
+                                                 int keep_old, double *__restrict__ ref)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6);
-    if (i >= n_atoms) return;
-    const int bb = b * b;
-    // the row's (block, element) pairs flattened, 64 per pass, so every lane
-    // works and a pass has 64 independent loads (b = 4: four blocks at once)
+    __shared__ double part[kT / 64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    constexpr int PER = kT / 64 / W;           // atoms per workgroup
+    const int x0 = blockIdx.x * PER + wv / W;  // (kick, atom) of this wave
+    const bool live = x0 < n_atoms * n_k;
+    const int kk = live ? x0 / n_atoms : 0, i = live ? x0 - kk * n_atoms : 0;
+    const int bs = B ? B : b, bb = bs * bs;
+    const double *__restrict__ kr = kp.re[kk];
     const int64_t p0 = s_ptr[i];
-    const int64_t nel = (s_ptr[i + 1] - p0) * bb;
+    const int nel = live ? (int)(s_ptr[i + 1] - p0) * bb : 0;
     double acc = 0.0;
-    for (int64_t x = lane; x < nel; x += 64) {
-        const int64_t p = p0 + x / bb;
-        const int w = (int)(x % bb);
+#pragma unroll 4
+    for (int x = (wv % W) * 64 + lane; x < nel; x += 64 * W) {
+        const int pp = x / bb, w = x - pp * bb;
+        const int64_t p = p0 + pp;
         const int kb = s_to_k[p];
-        if (kb < 0) continue;
-        const int a = w / b, c = w - a * b;
-        acc += kr[(int64_t)kb * bb + w] * sv[(int64_t)s_trans[p] * bb + c * b + a];
+        const int a = w / bs, c = w - a * bs;
+        const double sval = sv[(int64_t)s_trans[p] * bb + c * bs + a];
+        if (kb >= 0) acc += kr[(int64_t)kb * bb + w] * sval;
     }
     acc = wave_sum(acc);
-    if (lane == 0) q[i] = acc;
+    if (W > 1) {
+        if (lane == 0) part[wv] = acc;
+        __syncthreads();
+        if (wv % W == 0) {
+            acc = part[wv];
+#pragma unroll
+            for (int k = 1; k < W; ++k) acc += part[wv + k];
+        }
+    }
+    if (live && lane == 0 && wv % W == 0) {
+        if (prev) prev[x0] = keep_old ? q[x0] : acc;
+        if (ref && kk == 0) ref[i] = acc;
+        q[x0] = acc;
+    }
 }
 
-void launch_mulliken(hipStream_t s, int64_t n_atoms, int b, const int64_t *s_ptr,
-                     const int32_t *s_trans, const int32_t *s_to_k, const double *sv,
-                     const double *kr, double *q)
+void launch_mulliken(hipStream_t s, int64_t n_atoms, int n_k, int b, const int64_t *s_ptr, const int32_t *s_trans,
+                     const int32_t *s_to_k, const double *sv, const KPlanes &k, double *q, double *prev, int keep_old,
+                     double *ref)
 {
     if (n_atoms == 0) return;
-    const int per = kT / 64;
-    hipLaunchKernelGGL(k_mulliken, dim3((unsigned)((n_atoms + per - 1) / per)), dim3(kT), 0, s,
-                       n_atoms, b, s_ptr, s_trans, s_to_k, sv, kr, q);
+    RT_CHECK(n_k >= 1 && n_k <= kMaxKicks && n_atoms * n_k < INT32_MAX, RTDM_E_UNSUPPORTED, "too many charges");
+    // one wave per atom only for b <= 4 with enough atoms to fill the 1,024 SIMDs four times
+    // (by the atoms alone: a kick set's sums are those of a run with that kick only)
+    const bool wide = b > 4 || n_atoms < 4096;
+    const int per = wide ? 1 : kT / 64;
+    const dim3 g((unsigned)((n_atoms * n_k + per - 1) / per)), t(kT);
+#define RT_MULL(B_, W_)                                                                                             \
+    hipLaunchKernelGGL((k_mulliken<B_, W_>), g, t, 0, s, (int)n_atoms, n_k, b, s_ptr, s_trans, s_to_k, sv, k, q, prev, \
+                       keep_old, ref)
+    if (b == 4 && wide) RT_MULL(4, 4);
+    else if (b == 4) RT_MULL(4, 1);
+    else if (b == 13) RT_MULL(13, 4);
+    else if (wide) RT_MULL(0, 4);
+    else RT_MULL(0, 1);
+#undef RT_MULL
     RT_HIP(hipGetLastError());
 }
 
@@ -387,41 +482,64 @@ void launch_spectrum(hipStream_t s, int64_t n_omega, const double *omega, double
     RT_HIP(hipGetLastError());
 }
 
-// Single workgroup: centroid, dipole P = -sum (r_i - r_c) q_i, Tr(KS) = sum q_i.
-// With a step state st/tt the row is out + 8 * st[0], the time tt[0] +
-// (st[1] + 1) * tt[1] (k_step_end advances both counters); without one (st null) the
-// row is `out` and the time `t`.
-__global__ __launch_bounds__(kT) void k_observables(int64_t n, const double *__restrict__ xyz,
-                                                    const double *__restrict__ centre,
-                                                    const double *__restrict__ q,
-                                                    const double *__restrict__ herm_sums, double t,
-                                                    double *__restrict__ out, int64_t *st,
-                                                    const double *__restrict__ tt)
+// Dipole -sum (r_i - r_c) q_i and sum q_i of atoms a0 .. a1-1 about (cx, cy, cz),
+// by one workgroup of kT threads: d[0..2] and d[3] on every thread.
+__device__ inline void dipole_sums(int64_t a0, int64_t a1, const double *__restrict__ xyz,
+                                   const double *__restrict__ centre, const double *__restrict__ q, double *sh,
+                                   double d[4])
 {
-    __shared__ double sh[4 * kT];
     const double cx = centre[0], cy = centre[1], cz = centre[2];
     double w[4] = {0.0, 0.0, 0.0, 0.0};
     double tr = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += kT) {
+    for (int64_t i = a0 + threadIdx.x; i < a1; i += kT) {
         const double qi = q[i];
         w[0] -= (xyz[3 * i] - cx) * qi;
         w[1] -= (xyz[3 * i + 1] - cy) * qi;
         w[2] -= (xyz[3 * i + 2] - cz) * qi;
         tr += qi;
     }
-    w[3] = 0.0;
     block_reduce4(w, sh);
     __syncthreads();
     double u[4] = {tr, 0.0, 0.0, 0.0};
     block_reduce4(u, sh);
+    __syncthreads();
+    d[0] = w[0];
+    d[1] = w[1];
+    d[2] = w[2];
+    d[3] = u[0];
+}
+
+// The kRedBlocks partials of a reduction summed by one workgroup (k_red_finish's
+// order): v[0..2] sums, v[3] max, on every thread.
+__device__ inline void finish_sums(const double *__restrict__ partials, double *sh, double v[4])
+{
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) v[k] = partials[t * 4 + k] + partials[(t + kT) * 4 + k];
+    v[3] = fmax(partials[t * 4 + 3], partials[(t + kT) * 4 + 3]);
+    block_reduce4(v, sh);
+    __syncthreads();
+}
+
+__device__ inline double herm_error(double d2, double k2) { return k2 > 0.0 ? sqrt(d2 / k2) : 0.0; }
+
+// Observables of the current K into `row` at time t (a single workgroup).
+__global__ __launch_bounds__(kT) void k_observables(int64_t n, const double *__restrict__ xyz,
+                                                    const double *__restrict__ centre,
+                                                    const double *__restrict__ q,
+                                                    const double *__restrict__ herm_sums, double t,
+                                                    double *__restrict__ row)
+{
+    __shared__ double sh[4 * (kT / 64)];
+    double d[4];
+    dipole_sums(0, n, xyz, centre, q, sh, d);
     if (threadIdx.x == 0) {
-        double *row = st ? out + 8 * st[0] : out;
-        row[0] = st ? tt[0] + (double)(st[1] + 1) * tt[1] : t;
-        row[1] = w[0];
-        row[2] = w[1];
-        row[3] = w[2];
-        row[4] = u[0];
-        row[5] = herm_sums ? (herm_sums[1] > 0.0 ? sqrt(herm_sums[0] / herm_sums[1]) : 0.0) : 0.0;
+        row[0] = t;
+        row[1] = d[0];
+        row[2] = d[1];
+        row[3] = d[2];
+        row[4] = d[3];
+        row[5] = herm_sums ? herm_error(herm_sums[0], herm_sums[1]) : 0.0;
         row[6] = __builtin_nan("");
         row[7] = 0.0;
     }
@@ -430,31 +548,61 @@ __global__ __launch_bounds__(kT) void k_observables(int64_t n, const double *__r
 void launch_observables(hipStream_t s, int64_t n_atoms, const double *xyz, const double *centre, const double *q,
                         const double *herm_sums, double t, double *row)
 {
-    hipLaunchKernelGGL(k_observables, dim3(1), dim3(kT), 0, s, n_atoms, xyz, centre, q, herm_sums, t, row,
-                       (int64_t *)nullptr, (const double *)nullptr);
+    hipLaunchKernelGGL(k_observables, dim3(1), dim3(kT), 0, s, n_atoms, xyz, centre, q, herm_sums, t, row);
     RT_HIP(hipGetLastError());
 }
 
-// Advance the step state after a step's observables (st[0]++, st[1]++).
-__global__ void k_step_end(int64_t *st)
+// End of a step, one launch: workgroup (k, 0) finishes kick k's Hermiticity sums
+// and writes its trace row obs + k obs_stride + 8 st[0] at time tt[0] + (st[1] +
+// 1) tt[1]; workgroup (k, 1 + g) writes group g's row; the last workgroup to
+// finish (counted in st[2]) advances st[0] and st[1].  In small systems, where a
+// step is a chain of launches, this stands for a launch each of the sums, the
+// rows and the counters.
+__global__ __launch_bounds__(kT) void k_step_tail(StepTail a)
 {
+    __shared__ double sh[4 * (kT / 64)];
+    const int per = 1 + (int)a.n_groups, kk = blockIdx.x / per, j = blockIdx.x - kk * per;
+    const double *q = a.q + (int64_t)kk * a.n;
+    const int64_t row_at = a.st[0];
+    double d[4];
+    if (j == 0) {
+        double v[4];
+        finish_sums(a.partials + (int64_t)kk * kRedBlocks * 4, sh, v);
+        dipole_sums(0, a.n, a.xyz, a.centre, q, sh, d);
+        if (threadIdx.x == 0) {
+            for (int k = 0; k < 4; ++k) a.herm[4 * kk + k] = v[k];
+            double *row = a.obs + kk * a.obs_stride + 8 * row_at;
+            row[0] = a.tt[0] + (double)(a.st[1] + 1) * a.tt[1];
+            row[1] = d[0];
+            row[2] = d[1];
+            row[3] = d[2];
+            row[4] = d[3];
+            row[5] = herm_error(v[0], v[1]);
+            row[6] = __builtin_nan("");
+            row[7] = 0.0;
+        }
+    } else {
+        const int64_t g = j - 1;
+        dipole_sums(a.gptr[g], a.gptr[g + 1], a.xyz, a.centre_g + 3 * g, q, sh, d);
+        if (threadIdx.x == 0) {
+            double *o = a.obs_g + kk * a.obs_g_stride + (row_at * a.n_groups + g) * 4;
+            for (int k = 0; k < 4; ++k) o[k] = d[k];
+        }
+    }
+    // every thread of this workgroup has read st by now (the reductions above synchronise)
     if (threadIdx.x == 0) {
-        st[0] += 1;
-        st[1] += 1;
+        __threadfence();
+        if (atomicAdd((unsigned long long *)&a.st[2], 1ull) == (unsigned long long)gridDim.x - 1) {
+            a.st[0] = row_at + 1;
+            a.st[1] += 1;
+            a.st[2] = 0;
+        }
     }
 }
 
-void launch_observables_step(hipStream_t s, int64_t n_atoms, const double *xyz, const double *centre,
-                             const double *q, const double *herm_sums, double *obs, int64_t *st, const double *tt)
+void launch_step_tail(hipStream_t s, int n_kicks, const StepTail &a)
 {
-    hipLaunchKernelGGL(k_observables, dim3(1), dim3(kT), 0, s, n_atoms, xyz, centre, q, herm_sums, 0.0, obs, st,
-                       tt);
-    RT_HIP(hipGetLastError());
-}
-
-void launch_step_end(hipStream_t s, int64_t *st)
-{
-    hipLaunchKernelGGL(k_step_end, dim3(1), dim3(64), 0, s, st);
+    hipLaunchKernelGGL(k_step_tail, dim3((unsigned)(n_kicks * (1 + a.n_groups))), dim3(kT), 0, s, a);
     RT_HIP(hipGetLastError());
 }
 
@@ -673,100 +821,23 @@ void launch_fill(hipStream_t s, int64_t n, double v, double *out)
 }
 
 // Step state kept on the device so that one captured step can be replayed:
-// st[0] = next trace row, st[1] = steps done in this call, and
-// tt[0] = time at the start of the call, tt[1] = dt.
-__global__ void k_step_begin(int64_t *st, double *tt, double t0, double dt)
+// st[0] = next trace row (0 with `reset`), st[1] = steps done in this call,
+// st[2] = workgroups of k_step_tail done, and tt[0] = time at the start of the
+// call, tt[1] = dt.
+__global__ void k_step_begin(int64_t *st, double *tt, double t0, double dt, int reset)
 {
     if (threadIdx.x == 0) {
+        if (reset) st[0] = 0;
         st[1] = 0;
+        st[2] = 0;
         tt[0] = t0;
         tt[1] = dt;
     }
 }
 
-void launch_step_begin(hipStream_t s, int64_t *st, double *tt, double t0, double dt)
+void launch_step_begin(hipStream_t s, int64_t *st, double *tt, double t0, double dt, int reset)
 {
-    hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(64), 0, s, st, tt, t0, dt);
-    RT_HIP(hipGetLastError());
-}
-
-// Per-group observables of the new K (one workgroup per group of contiguous
-// atoms): centroid, dipole -sum (r_i - r_c) q_i and Tr(KS) = sum q_i, written
-// to out[row][g][0..3] with row = st[0].
-__global__ __launch_bounds__(kT) void k_group_obs(const int64_t *__restrict__ gptr,
-                                                  const double *__restrict__ xyz,
-                                                  const double *__restrict__ centre,
-                                                  const double *__restrict__ q,
-                                                  const int64_t *__restrict__ st, int64_t n_groups,
-                                                  double *__restrict__ out)
-{
-    __shared__ double sh[4 * kT];
-    const int64_t g = blockIdx.x;
-    const int64_t a0 = gptr[g], a1 = gptr[g + 1];
-    const double cx = centre[3 * g], cy = centre[3 * g + 1], cz = centre[3 * g + 2];
-    double w[4] = {0.0, 0.0, 0.0, 0.0};
-    double tr = 0.0;
-    for (int64_t i = a0 + threadIdx.x; i < a1; i += kT) {
-        const double qi = q[i];
-        w[0] -= (xyz[3 * i] - cx) * qi;
-        w[1] -= (xyz[3 * i + 1] - cy) * qi;
-        w[2] -= (xyz[3 * i + 2] - cz) * qi;
-        tr += qi;
-    }
-    block_reduce4(w, sh);
-    __syncthreads();
-    double u[4] = {tr, 0.0, 0.0, 0.0};
-    block_reduce4(u, sh);
-    if (threadIdx.x == 0) {
-        double *o = out + (st[0] * n_groups + g) * 4;
-        o[0] = w[0];
-        o[1] = w[1];
-        o[2] = w[2];
-        o[3] = u[0];
-    }
-}
-
-void launch_group_obs(hipStream_t s, int64_t n_groups, const int64_t *gptr, const double *xyz, const double *centre,
-                      const double *q, const int64_t *st, double *out)
-{
-    if (n_groups == 0) return;
-    hipLaunchKernelGGL(k_group_obs, dim3((unsigned)n_groups), dim3(kT), 0, s, gptr, xyz, centre, q, st, n_groups,
-                       out);
-    RT_HIP(hipGetLastError());
-}
-
-// K_ij *= exp(i kappa_g . (r_i - r_j)) with the kick of atom i's group (pairs
-// never cross groups in a block-diagonal batch).
-__global__ void k_kick_groups(int64_t nnzb, int b, const int32_t *__restrict__ rowof,
-                              const int32_t *__restrict__ col, const double *__restrict__ xyz,
-                              const int32_t *__restrict__ group, const double *__restrict__ kappa,
-                              double *__restrict__ kr, double *__restrict__ ki)
-{
-    const int bb = b * b;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nnzb * bb;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t p = e / bb;
-        const int i = rowof[p], j = col[p];
-        const double *k = kappa + 3 * group[i];
-        const double ph = k[0] * (xyz[3 * i] - xyz[3 * j]) + k[1] * (xyz[3 * i + 1] - xyz[3 * j + 1]) +
-                          k[2] * (xyz[3 * i + 2] - xyz[3 * j + 2]);
-        double sn, cs;
-        sincos(ph, &sn, &cs);
-        const double xr = kr[e], xi = ki[e];
-        kr[e] = cs * xr - sn * xi;
-        ki[e] = cs * xi + sn * xr;
-    }
-}
-
-void launch_kick_groups(hipStream_t s, int64_t nnzb, int b, const int32_t *rowof, const int32_t *col,
-                        const double *xyz, const int32_t *group, const double *kappa, double *kr, double *ki)
-{
-    const int64_t n = nnzb * b * b;
-    if (n == 0) return;
-    int64_t g = (n + kT - 1) / kT;
-    if (g > 65536) g = 65536;
-    hipLaunchKernelGGL(k_kick_groups, dim3((unsigned)g), dim3(kT), 0, s, nnzb, b, rowof, col, xyz, group, kappa,
-                       kr, ki);
+    hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(64), 0, s, st, tt, t0, dt, reset);
     RT_HIP(hipGetLastError());
 }
 
@@ -934,14 +1005,10 @@ void launch_red_max(hipStream_t s, int64_t n, const double *x, double *partials)
 __global__ __launch_bounds__(kT) void k_red_finish(const double *__restrict__ partials,
                                                    double *__restrict__ out)
 {
-    __shared__ double sh[4 * kT];
-    const int t = threadIdx.x;
+    __shared__ double sh[4 * (kT / 64)];
     double v[4];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) v[k] = partials[t * 4 + k] + partials[(t + kT) * 4 + k];
-    v[3] = fmax(partials[t * 4 + 3], partials[(t + kT) * 4 + 3]);
-    block_reduce4(v, sh);
-    if (t == 0)
+    finish_sums(partials, sh, v);
+    if (threadIdx.x == 0)
         for (int k = 0; k < 4; ++k) out[k] = v[k];
 }
 
@@ -965,6 +1032,25 @@ void launch_unit_to_row(hipStream_t s, const double *unit_sums, const double *s_
 }
 
 // ----------------------------------------------------------------- layout
+
+// re = in, im = 0: a real upload into a complex slot (the caller's data may sit
+// on any 8-byte boundary, so 8 bytes a lane).
+__global__ void k_copy_real(int64_t n, const double *__restrict__ in, double *__restrict__ re,
+                            double *__restrict__ im)
+{
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
+        re[e] = in[e];
+        im[e] = 0.0;
+    }
+}
+
+void launch_copy_real(hipStream_t s, int64_t n, const double *in, double *re, double *im)
+{
+    if (n == 0) return;
+    const int64_t g = std::min<int64_t>((n + kT - 1) / kT, 65536);
+    hipLaunchKernelGGL(k_copy_real, dim3((unsigned)g), dim3(kT), 0, s, n, in, re, im);
+    RT_HIP(hipGetLastError());
+}
 
 __global__ void k_split(int64_t n, const double *__restrict__ inter, double *__restrict__ re,
                         double *__restrict__ im)

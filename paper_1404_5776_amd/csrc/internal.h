@@ -122,6 +122,17 @@ void launch_sym_fill(hipStream_t s, int64_t nout, const int32_t *c_rowof, const 
                      const int64_t *b_ptr, const int32_t *b_col, const int32_t *b_trans, int op_a,
                      int op_b, const int64_t *off, int2 *trip);
 
+// Pair layout of b x b operand blocks: element (x, m) of a block, m the
+// contraction index, sits at (m / 2) * 2b + 2x + (m & 1), so that the two
+// values a lane feeds to two consecutive MFMA steps are 16 contiguous bytes
+// (an odd b's last m has x alone: b (b - 1) + x).  "Left" pairs hold a left
+// operand (x the row, m the column), "right" pairs a right operand (x the
+// column, m the row).  A block keeps its b * b doubles.
+__device__ __host__ inline int pair_at(int b, int x, int m)
+{
+    return (b & 1) && m == b - 1 ? b * (b - 1) + x : (m >> 1) * 2 * b + 2 * x + (m & 1);
+}
+
 struct SpgemmArgs {
     int64_t nout = 0;
     const int64_t *off = nullptr;   // [nout+1] triple offsets
@@ -233,16 +244,27 @@ void launch_axpby(hipStream_t s, int64_t n, double a, const double *x, double c,
 // m[diag blocks] += val * I.
 void launch_add_identity(hipStream_t s, int64_t n_atoms, int b, const int32_t *diag, double val,
                          double *m);
-// K_ij *= exp(i kappa.(r_i - r_j)).
-void launch_kick(hipStream_t s, int64_t nnzb, int b, const int32_t *rowof, const int32_t *col,
-                 const double *xyz, double kx, double ky, double kz, double *kr, double *ki);
-// K = (Kn + Kn^H)/2 with partial sums of ||Kn - Kn^H||^2 and ||Kn||^2.
+// K_ij *= exp(i kappa.(r_i - r_j)), kappa or (group set) that of atom i's group in
+// kappa_g (device); kr_t, ki_t (nullable): K as a right operand too.
+void launch_kick(hipStream_t s, int64_t nnzb, int b, const int32_t *rowof, const int32_t *col, const double *xyz,
+                 const int32_t *group, const double *kappa_g, const double kappa[3], double *kr, double *ki,
+                 double *kr_t, double *ki_t);
+// K = (Kn + Kn^H)/2 with partial sums of ||Kn - Kn^H||^2 and ||Kn||^2; kr_t, ki_t
+// (nullable): K as a right operand (b = 4 transposed blocks, b = 13 right pairs).
 void launch_hermitize(hipStream_t s, int64_t nnzb, int b, const int32_t *trans, const double *knr,
-                      const double *kni, double *kr, double *ki, double *partials);
-// q_i = Re sum_j tr(K_ij S_ji).
-void launch_mulliken(hipStream_t s, int64_t n_atoms, int b, const int64_t *s_ptr,
-                     const int32_t *s_trans, const int32_t *s_to_k, const double *sv,
-                     const double *kr, double *q);
+                      const double *kni, double *kr, double *ki, double *partials, double *kr_t = nullptr,
+                      double *ki_t = nullptr);
+// Real planes of the K of every kick set.
+constexpr int kMaxKicks = 8;
+struct KPlanes {
+    const double *re[kMaxKicks] = {};
+};
+// q_i = Re sum_j tr(K_ij S_ji) of n_k kick sets (q[k * n_atoms + i]); prev
+// (nullable): the old charges (keep_old) or the new ones; ref (nullable): the
+// new charges of the first set.
+void launch_mulliken(hipStream_t s, int64_t n_atoms, int n_k, int b, const int64_t *s_ptr, const int32_t *s_trans,
+                     const int32_t *s_to_k, const double *sv, const KPlanes &k, double *q, double *prev, int keep_old,
+                     double *ref);
 // H[diag] += gain*(q_a + theta (q_x - q_y) - q_ref) on the diagonal elements.
 void launch_add_scalar(hipStream_t s, double *x, double v);
 void launch_a_onsite(hipStream_t s, int64_t nnzb, int b, const int32_t *col, const int32_t *nbf, double gain,
@@ -262,16 +284,21 @@ void launch_spectrum(hipStream_t s, int64_t n_omega, const double *omega, double
 // centre: the atoms' centroid (3 doubles, computed on the host with an exactly rounded sum).
 void launch_observables(hipStream_t s, int64_t n_atoms, const double *xyz, const double *centre, const double *q,
                         const double *herm_sums, double t, double *row);
-// The same observables written to obs + 8 * st[0] at time tt[0] + (st[1] + 1) * tt[1].
-void launch_observables_step(hipStream_t s, int64_t n_atoms, const double *xyz, const double *centre,
-                             const double *q, const double *herm_sums, double *obs, int64_t *st, const double *tt);
-void launch_step_begin(hipStream_t s, int64_t *st, double *tt, double t0, double dt);
-void launch_step_end(hipStream_t s, int64_t *st);
+// End of a step (k_step_tail): the Hermiticity sums, trace rows of every kick
+// set and group, and the step counters.
+struct StepTail {
+    int64_t n, n_groups;                  // n_groups 0: no group rows
+    const double *xyz, *centre, *centre_g;
+    const int64_t *gptr;
+    const double *q, *partials;           // [kick][n], [kick][kRedBlocks * 4]
+    double *herm, *obs, *obs_g;           // [kick][4], rows of 8, rows of n_groups * 4
+    int64_t obs_stride, obs_g_stride;     // doubles between kick sets
+    int64_t *st;
+    const double *tt;
+};
+void launch_step_tail(hipStream_t s, int n_kicks, const StepTail &a);
+void launch_step_begin(hipStream_t s, int64_t *st, double *tt, double t0, double dt, int reset);
 void launch_fill(hipStream_t s, int64_t n, double v, double *out);
-void launch_group_obs(hipStream_t s, int64_t n_groups, const int64_t *gptr, const double *xyz, const double *centre,
-                      const double *q, const int64_t *st, double *out);
-void launch_kick_groups(hipStream_t s, int64_t nnzb, int b, const int32_t *rowof, const int32_t *col,
-                        const double *xyz, const int32_t *group, const double *kappa, double *kr, double *ki);
 // X_ii = S_ii^{-1} (Gauss-Jordan, partial pivoting); other blocks untouched.
 void launch_block_inverse(hipStream_t s, int64_t n_atoms, int b, const int32_t *s_diag,
                           const double *sv, const int32_t *x_diag, double *xv, double *scratch);
@@ -297,6 +324,8 @@ void launch_red_finish(hipStream_t s, const double *partials, double *out);
 // unit-row update: row[6] = sqrt(sums[0] / s2)
 void launch_unit_to_row(hipStream_t s, const double *unit_sums, const double *s_norm2, double *row);
 
+// re = in, im = 0
+void launch_copy_real(hipStream_t s, int64_t n, const double *in, double *re, double *im);
 // interleave / split complex128
 void launch_split(hipStream_t s, int64_t n, const double *inter, double *re, double *im);
 void launch_interleave(hipStream_t s, int64_t n, const double *re, const double *im, double *inter);

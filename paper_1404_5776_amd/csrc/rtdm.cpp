@@ -337,6 +337,10 @@ struct rtdm_ctx {
     // every kick shares S, H, X and U; the API reads kick kick_sel
     std::vector<Mat> Kx;
     int kick_sel = 0;
+    // K of every kick as the right operand of U K (b = 4: transposed blocks, b = 13:
+    // right pairs), written with K by the Hermitisation; K_right_valid: they follow K
+    std::vector<Mat> Kr;
+    bool K_right_valid = false;
     bool q_ref_valid = false, charges_valid = false;
 
     bool uploaded[RTDM_MAT_COUNT] = {};
@@ -655,14 +659,21 @@ Sched &schedule_key(rtdm_ctx *c, int prod, const std::tuple<int, int, int, int, 
     return ref;
 }
 
-// Whether the products of schedule S run on the b = 4 kernel that reads its
-// right operand with transposed blocks: FP64 over enough runs of 16 to fill
-// the chip (below that the split form's shorter chains are faster).
+// Whether the products of schedule S can run on the b = 4 kernels that read
+// the right operand with transposed blocks: FP64 over runs of 16.
+bool b4_takes_transposed(rtdm_ctx *c, const Sched &S)
+{
+    if (c->b != 4 || c->prec != RTDM_PREC_FP64 || c->run_b4 != 16) return false;
+    auto r = S.runs.find(16);
+    return r != S.runs.end() && r->second->nch > 0;
+}
+
+// ... and do so for an operand by rows too, transposed into Bp first: where the
+// runs fill the chip.  In the split form of small systems that launch would
+// cost more than the narrower loads of k_spgemm_b4js.
 bool b4_transposed(rtdm_ctx *c, const Sched &S)
 {
-    if (c->b != 4 || c->prec != RTDM_PREC_FP64 || c->run_b4 != 16 || !c->Bp.re.p) return false;
-    auto r = S.runs.find(16);
-    return r != S.runs.end() && r->second->nch > 0 && !b4_split_form(r->second->nch);
+    return b4_takes_transposed(c, S) && !b4_split_form(S.runs.find(16)->second->nch);
 }
 
 // Whether schedule S has segmented row runs of 2 (b = 13).
@@ -710,8 +721,8 @@ void product(rtdm_ctx *c, int prod, const Mat &A, const Mat &B, Mat &C, double a
 }
 
 // The same with the schedule of operand and output patterns `key` (timed as
-// `prod`); b_t: B's blocks are stored transposed (where b4_transposed holds;
-// only then does `out` differ from the default).
+// `prod`); b_t: B's blocks are stored transposed (where b4_takes_transposed
+// holds; only then does `out` differ from the default).
 void product_key(rtdm_ctx *c, int prod, const std::tuple<int, int, int, int, int> &key, const Mat &A,
                  const Mat &B, Mat &C, double alr, double ali, hipStream_t s, bool b_t, const ProductOut &out)
 {
@@ -783,7 +794,8 @@ void product_key(rtdm_ctx *c, int prod, const std::tuple<int, int, int, int, int
         a.ch_seg = R.seg.p;
         a.zero = c->zero.p;
     }
-    const bool b4t = b4_transposed(c, S) && a.op_a == 0;
+    // a conjugate-transposed right operand by rows has the transposed form as it is
+    const bool b4t = a.op_a == 0 && (b4_transposed(c, S) || ((b_t || a.op_b) && b4_takes_transposed(c, S)));
     RT_CHECK(!b_t || b4t, RTDM_E_ARG, "transposed right operand outside the b = 4 run kernel");
     auto go = [&]() {
         if (pairs) {
@@ -949,18 +961,27 @@ void read_scalars(double *dst, const double *src, int n, hipStream_t s)
     RT_HIP(hipStreamSynchronize(s));
 }
 
+// Mulliken charges of the kick sets' K into q (see launch_mulliken).
+void charges_into(rtdm_ctx *c, int n_k, const KPlanes &k, double *q, double *prev, int keep_old, double *ref,
+                  hipStream_t s)
+{
+    const Pattern &ps = pat_of(c, R_HS);
+    launch_mulliken(s, c->n, n_k, c->b, ps.d_rowptr.p, ps.d_trans.p, c->s_to_k.p, c->mats[RTDM_MAT_S].re.p, k, q, prev,
+                    keep_old, ref);
+}
+
+KPlanes k_planes(rtdm_ctx *c)
+{
+    KPlanes k;
+    for (int i = 0; i < n_kicks(c); ++i) k.re[i] = kmat(c, i).re.p;
+    return k;
+}
+
 void ensure_charges(rtdm_ctx *c, hipStream_t s)
 {
     if (c->charges_valid) return;
-    Pattern &ps = pat_of(c, R_HS);
-    for (int k = 0; k < n_kicks(c); ++k)
-        launch_mulliken(s, c->n, c->b, ps.d_rowptr.p, ps.d_trans.p, c->s_to_k.p, c->mats[RTDM_MAT_S].re.p,
-                        kmat(c, k).re.p, qcur(c, k));
-    RT_HIP(hipMemcpyAsync(c->q_prev, c->q_cur, n_kicks(c) * c->n * sizeof(double), hipMemcpyDeviceToDevice, s));
-    if (!c->q_ref_valid) {
-        RT_HIP(hipMemcpyAsync(c->q_ref.p, c->q_cur, c->n * sizeof(double), hipMemcpyDeviceToDevice, s));
-        c->q_ref_valid = true;
-    }
+    charges_into(c, n_kicks(c), k_planes(c), c->q_cur, c->q_prev, 0, c->q_ref_valid ? nullptr : c->q_ref.p, s);
+    c->q_ref_valid = true;
     c->charges_valid = true;
 }
 
@@ -994,7 +1015,7 @@ bool taylor_fused(rtdm_ctx *c, bool low16)
     if (c->prec != RTDM_PREC_FP64) return false;
     if (c->b == 13) return c->pairs_real && c->opt.precision == RTDM_PREC_FP64;
     return (c->opt.precision == RTDM_PREC_FP64 || c->opt.precision == RTDM_PREC_FP32_TAYLOR || low16) &&
-           b4_transposed(c, schedule(c, RTDM_PROD_AT));
+           b4_takes_transposed(c, schedule(c, RTDM_PROD_AT));
 }
 
 // U = sum_{n=0}^{p} (-i)^n tau_n with tau_0 = I, tau_1 = dt A, tau_n = (dt/n) P_P(A tau_{n-1}).
@@ -1274,6 +1295,7 @@ void after_upload(rtdm_ctx *c, int m)
     case RTDM_MAT_H0: c->U_valid = false; c->A0_valid = false; break;
     case RTDM_MAT_X: c->X_valid = true; c->U_valid = false; c->Xc_valid = false; c->A0_valid = false; break;
     case RTDM_MAT_K:
+        c->K_right_valid = false;
         for (int k = 1; k < n_kicks(c); ++k) {   // every kick starts from the uploaded K
             const int64_t ne = elems(c, c->mats[RTDM_MAT_K]);
             RT_HIP(hipMemcpy(c->Kx[k - 1].re.p, c->mats[RTDM_MAT_K].re.p, ne * sizeof(double),
@@ -1452,7 +1474,7 @@ int rtdm_create(rtdm_ctx **out, int hip_device, const rtdm_options *opt)
              "row runs of 1 to 4 or 8 outputs for real products");
     RT_CHECK(c->run_cplx >= 1 && c->run_cplx <= 4, RTDM_E_ARG,
              "row runs of 1 to 4 outputs for complex products");
-    c->partials.alloc(kRedBlocks * 4);
+    c->partials.alloc((size_t)kRedBlocks * 4 * c->opt.n_kicks);   // one set of partials per kick
     c->herm_sums.alloc(4 * c->opt.n_kicks);
     c->unit_sums.alloc(4);
     c->s_norm2.alloc(4);
@@ -1652,7 +1674,7 @@ int rtdm_set_ranges(rtdm_ctx *c, double R_hs, double R_p, double R_k)
     }
     c->step_count = 0;
     c->trace_dt_mixed = false;
-    c->step_st.alloc(2);
+    c->step_st.alloc(3);
     c->step_tt.alloc(2);
     c->obs_reset_pending = true;
     c->obs_cap = 0;
@@ -1691,6 +1713,12 @@ int rtdm_set_ranges(rtdm_ctx *c, double R_hs, double R_p, double R_k)
         c->Bp.im.release();
         c->Lp.re.release();
         c->Lp.im.release();
+        c->Kr.clear();
+        c->K_right_valid = false;
+        if (c->pairs_cplx || (all_products_prec(c) == RTDM_PREC_FP64 && b4_takes_transposed(c, schedule(c, RTDM_PROD_UK)))) {
+            c->Kr.resize(n_kicks(c));
+            for (auto &Km : c->Kr) alloc_like(c, Km, c->mats[RTDM_MAT_K]);
+        }
         if (c->pairs_real) {
             c->Ap.pat = c->range_pat[R_P];
             c->Ap.re.alloc(elems(c, c->Ap));
@@ -1822,8 +1850,8 @@ int rtdm_upload(rtdm_ctx *c, rtdm_mat mat, const void *data, int is_complex, int
     } else {
         const double *d = (const double *)data;
         if (!is_complex) {
-            RT_HIP(hipMemcpyAsync(M.re.p, d, ne * sizeof(double), hipMemcpyDeviceToDevice, s));
-            if (M.cplx) RT_HIP(hipMemsetAsync(M.im.p, 0, M.im.bytes(), s));
+            if (M.cplx) launch_copy_real(s, ne, d, M.re.p, M.im.p);
+            else RT_HIP(hipMemcpyAsync(M.re.p, d, ne * sizeof(double), hipMemcpyDeviceToDevice, s));
         } else if (M.cplx) {
             launch_split(s, ne, d, M.re.p, M.im.p);
         } else {
@@ -1925,6 +1953,34 @@ int rtdm_download(rtdm_ctx *c, rtdm_mat mat, void *dst, int is_device, void *str
     API_END(c)
 }
 
+namespace {
+
+// A kick on the K of kick set k (and its right-operand copy): kappa, or with
+// `groups` that of each atom's group in kick_g.
+void kick_k(rtdm_ctx *c, int k, const double *kappa, bool groups, hipStream_t s)
+{
+    const Pattern &P = pat_of(c, R_K);
+    const bool right = !c->Kr.empty();
+    launch_kick(s, P.nnzb, c->b, P.d_rowof.p, P.d_col.p, c->d_xyz.p, groups ? c->d_group.p : nullptr,
+                groups ? c->kick_g.p : nullptr, kappa, kmat(c, k).re.p, kmat(c, k).im.p,
+                right ? c->Kr[k].re.p : nullptr, right ? c->Kr[k].im.p : nullptr);
+}
+
+// Host state after a kick on every K: a new trace and charge history.
+void after_kick(rtdm_ctx *c)
+{
+    c->charges_valid = false;
+    c->K_right_valid = !c->Kr.empty();
+    c->obs_rows = 0;
+    c->obs_reset_pending = true;
+    c->t_now = 0.0;
+    c->step_count = 0;
+    c->trace_dt_mixed = false;
+    c->herm_valid = false;
+}
+
+}  // namespace
+
 int rtdm_apply_kick(rtdm_ctx *c, const double kappa[3], void *stream)
 {
     if (!c) return RTDM_E_ARG;
@@ -1938,17 +1994,8 @@ int rtdm_apply_kick(rtdm_ctx *c, const double kappa[3], void *stream)
         c->charges_valid = false;
         ensure_charges(c, s);
     }
-    const Pattern &P = pat_of(c, R_K);
-    for (int k = 0; k < n_kicks(c); ++k)
-        launch_kick(s, P.nnzb, c->b, P.d_rowof.p, P.d_col.p, c->d_xyz.p, kappa[0], kappa[1], kappa[2],
-                    kmat(c, k).re.p, kmat(c, k).im.p);
-    c->charges_valid = false;
-    c->obs_rows = 0;
-    c->obs_reset_pending = true;
-    c->t_now = 0.0;
-    c->step_count = 0;
-    c->trace_dt_mixed = false;
-    c->herm_valid = false;
+    for (int k = 0; k < n_kicks(c); ++k) kick_k(c, k, kappa, false, s);
+    after_kick(c);
     API_END(c)
 }
 
@@ -2245,6 +2292,28 @@ void build_u(rtdm_ctx *c, double dt, bool corr, hipStream_t s)
     c->u_copies_valid = true;
 }
 
+// K of every kick as a right operand (Kr) after an upload or a kick, made
+// before the steps, outside any capture: each step's Hermitisation keeps them.
+void refresh_k_right(rtdm_ctx *c, int kk, hipStream_t s)
+{
+    const Mat &K = kmat(c, kk);
+    Mat &R = c->Kr[kk];
+    if (c->b == 13) {
+        pack_planes(c, K, R, kPackRight, s);
+        return;
+    }
+    const int64_t nb = c->pats[K.pat]->nnzb;
+    launch_transpose_blocks(s, nb, 4, K.re.p, R.re.p);
+    launch_transpose_blocks(s, nb, 4, K.im.p, R.im.p);
+}
+
+void ensure_k_right(rtdm_ctx *c, hipStream_t s)
+{
+    if (c->K_right_valid || c->Kr.empty()) return;
+    for (int k = 0; k < n_kicks(c); ++k) refresh_k_right(c, k, s);
+    c->K_right_valid = true;
+}
+
 // After an upload of U: its column-major copy (b = 13) and U^dagger (b = 4),
 // made before the steps, outside any capture, since a step that keeps U
 // (fixed H) does not rebuild them.
@@ -2271,7 +2340,7 @@ void ensure_u_copies(rtdm_ctx *c, hipStream_t s)
 void step_body(rtdm_ctx *c, double dt, bool rebuild_u, int passes, hipStream_t s)
 {
     Mat &U = c->mats[RTDM_MAT_U], &W = c->mats[RTDM_MAT_W];
-    const Pattern &ps = pat_of(c, R_HS), &pk = pat_of(c, R_K);
+    const Pattern &pk = pat_of(c, R_K);
     const int NK = n_kicks(c);                   // several kicks: fixed H, no corrector (checked at creation)
     c->prec = all_products_prec(c);
     const bool sc = passes > 1;
@@ -2286,41 +2355,54 @@ void step_body(rtdm_ctx *c, double dt, bool rebuild_u, int passes, hipStream_t s
             }
             if (use_cm(c)) {
                 const bool pc = c->pairs_cplx;
-                product_cm(c, RTDM_PROD_UK, c->Uc, right_copy(c, RTDM_PROD_UK, K, s), c->Wc, 0, 1, 1.0, s, pc);  // W, column-major
-                product_cm(c, RTDM_PROD_WU, c->Wc, c->Uc, c->Kn, 1, 0, 1.0, s, pc);                             // B = U^dagger
+                product_cm(c, RTDM_PROD_UK, c->Uc, pc ? c->Kr[kk] : K, c->Wc, 0, 1, 1.0, s, pc);   // W, column-major
+                product_cm(c, RTDM_PROD_WU, c->Wc, c->Uc, c->Kn, 1, 0, 1.0, s, pc);               // B = U^dagger
                 c->W_in_cm = true;
             } else {
-                product(c, RTDM_PROD_UK, U, K, W, 1.0, 0.0, s);
+                if (!c->Kr.empty())
+                    product_key(c, RTDM_PROD_UK, prod_key(c, RTDM_PROD_UK), U, c->Kr[kk], W, 1.0, 0.0, s, true);
+                else product(c, RTDM_PROD_UK, U, K, W, 1.0, 0.0, s);
                 if (c->Uh_on) product_key(c, RTDM_PROD_WU, wuh_key(c), W, c->Uh, c->Kn, 1.0, 0.0, s, true);
                 else product(c, RTDM_PROD_WU, W, U, c->Kn, 1.0, 0.0, s);
                 c->W_in_cm = false;
             }
             launch_hermitize(s, pk.nnzb, c->b, pk.d_trans.p, c->Kn.re.p, c->Kn.im.p, dst.re.p, dst.im.p,
-                             c->partials.p);
-            if (sc)
-                launch_mulliken(s, c->n, c->b, ps.d_rowptr.p, ps.d_trans.p, c->s_to_k.p,
-                                c->mats[RTDM_MAT_S].re.p, dst.re.p, c->q_c.p);
+                             c->partials.p + (int64_t)kk * kRedBlocks * 4,
+                             sc || c->Kr.empty() ? nullptr : c->Kr[kk].re.p,
+                             sc || c->Kr.empty() ? nullptr : c->Kr[kk].im.p);
+            if (sc) {
+                KPlanes k;
+                k.re[0] = dst.re.p;
+                charges_into(c, 1, k, c->q_c.p, nullptr, 0, nullptr, s);
+            }
         }
-        reduce_finish(c, s, herm_of(c, kk));
     }
     c->herm_valid = true;
-    launch_axpby(s, c->n * NK, 1.0, c->q_cur, 0.0, nullptr, c->q_prev);            // q(t - dt) <- q(t)
     if (sc) {
+        launch_axpby(s, c->n, 1.0, c->q_cur, 0.0, nullptr, c->q_prev);              // q(t - dt) <- q(t)
         copy_mat(c, c->Kt, c->mats[RTDM_MAT_K], s);
+        if (!c->Kr.empty()) refresh_k_right(c, 0, s);
         launch_axpby(s, c->n, 1.0, c->q_c.p, 0.0, nullptr, c->q_cur);
     } else {
-        for (int kk = 0; kk < NK; ++kk)
-            launch_mulliken(s, c->n, c->b, ps.d_rowptr.p, ps.d_trans.p, c->s_to_k.p, c->mats[RTDM_MAT_S].re.p,
-                            kmat(c, kk).re.p, qcur(c, kk));
+        charges_into(c, NK, k_planes(c), c->q_cur, c->q_prev, 1, nullptr, s);       // q(t - dt) <- q(t), q(t) <- K
     }
-    for (int kk = 0; kk < NK; ++kk) {
-        launch_observables_step(s, c->n, c->d_xyz.p, c->d_centre_all.p, qcur(c, kk), herm_of(c, kk), obs_of(c, kk),
-                                c->step_st.p, c->step_tt.p);
-        if (c->n_groups > 1)
-            launch_group_obs(s, c->n_groups, c->d_gptr.p, c->d_xyz.p, c->d_centre.p, qcur(c, kk), c->step_st.p,
-                             obs_g_of(c, kk));
-    }
-    launch_step_end(s, c->step_st.p);
+    StepTail tail;
+    tail.n = c->n;
+    tail.n_groups = c->n_groups > 1 ? c->n_groups : 0;
+    tail.xyz = c->d_xyz.p;
+    tail.centre = c->d_centre_all.p;
+    tail.centre_g = c->d_centre.p;
+    tail.gptr = c->d_gptr.p;
+    tail.q = c->q_cur;
+    tail.partials = c->partials.p;
+    tail.herm = c->herm_sums.p;
+    tail.obs = c->obs.p;
+    tail.obs_g = c->obs_g.p;
+    tail.obs_stride = c->obs_cap * 8;
+    tail.obs_g_stride = c->obs_cap * c->n_groups * 4;
+    tail.st = c->step_st.p;
+    tail.tt = c->step_tt.p;
+    launch_step_tail(s, NK, tail);
     c->prec = RTDM_PREC_FP64;
 }
 
@@ -2355,11 +2437,9 @@ StepCall step_begin(rtdm_ctx *c, double dt, int64_t n_steps, hipStream_t s)
     ensure_xc(c, s);
     ensure_a0(c, s);
     ensure_u_copies(c, s);
-    if (c->obs_reset_pending) {
-        RT_HIP(hipMemsetAsync(c->step_st.p, 0, c->step_st.bytes(), s));
-        c->obs_reset_pending = false;
-    }
-    launch_step_begin(s, c->step_st.p, c->step_tt.p, c->t_now, dt);
+    ensure_k_right(c, s);
+    launch_step_begin(s, c->step_st.p, c->step_tt.p, c->t_now, dt, c->obs_reset_pending);
+    c->obs_reset_pending = false;
     return StepCall{c, dt, n_steps, s, c->t_now, h_varies(c)};
 }
 
@@ -2969,26 +3049,15 @@ int rtdm_apply_kick_groups(rtdm_ctx *c, const double *kappa, void *stream)
         c->charges_valid = false;
         ensure_charges(c, s);
     }
-    const Pattern &P = pat_of(c, R_K);
     if (c->n_groups == 1) {
-        for (int k = 0; k < n_kicks(c); ++k)
-            launch_kick(s, P.nnzb, c->b, P.d_rowof.p, P.d_col.p, c->d_xyz.p, kappa[0], kappa[1], kappa[2],
-                        kmat(c, k).re.p, kmat(c, k).im.p);
+        for (int k = 0; k < n_kicks(c); ++k) kick_k(c, k, kappa, false, s);
     } else {
         c->kick_g.alloc(3 * c->n_groups);
         RT_HIP(hipMemcpyAsync(c->kick_g.p, kappa, c->kick_g.bytes(), hipMemcpyHostToDevice, s));
-        for (int k = 0; k < n_kicks(c); ++k)
-            launch_kick_groups(s, P.nnzb, c->b, P.d_rowof.p, P.d_col.p, c->d_xyz.p, c->d_group.p, c->kick_g.p,
-                               kmat(c, k).re.p, kmat(c, k).im.p);
+        for (int k = 0; k < n_kicks(c); ++k) kick_k(c, k, nullptr, true, s);
         RT_HIP(hipStreamSynchronize(s));
     }
-    c->charges_valid = false;
-    c->obs_rows = 0;
-    c->obs_reset_pending = true;
-    c->t_now = 0.0;
-    c->step_count = 0;
-    c->trace_dt_mixed = false;
-    c->herm_valid = false;
+    after_kick(c);
     API_END(c)
 }
 
@@ -3005,17 +3074,8 @@ int rtdm_apply_kicks(rtdm_ctx *c, const double *kappa, void *stream)
         c->charges_valid = false;
         ensure_charges(c, s);
     }
-    const Pattern &P = pat_of(c, R_K);
-    for (int k = 0; k < n_kicks(c); ++k)
-        launch_kick(s, P.nnzb, c->b, P.d_rowof.p, P.d_col.p, c->d_xyz.p, kappa[3 * k], kappa[3 * k + 1],
-                    kappa[3 * k + 2], kmat(c, k).re.p, kmat(c, k).im.p);
-    c->charges_valid = false;
-    c->obs_rows = 0;
-    c->obs_reset_pending = true;
-    c->t_now = 0.0;
-    c->step_count = 0;
-    c->trace_dt_mixed = false;
-    c->herm_valid = false;
+    for (int k = 0; k < n_kicks(c); ++k) kick_k(c, k, kappa + 3 * k, false, s);
+    after_kick(c);
     API_END(c)
 }
 

@@ -299,9 +299,6 @@ static int xcd_chunk_for(int64_t nwg) { return nwg < 16384 ? 32 : xcd_chunk(); }
 // The same deal in chunks of about as many output blocks (1,024) for a kernel
 // with `per_wg` output blocks per workgroup.
 static int xcd_chunk_wg(int per_wg) { return std::max(2, xcd_chunk() * 8 / std::max(per_wg, 1)); }
-// The b = 4 run kernels keep the hardware order (the deal changed their rate by
-// under 2 % either way).
-static int b4_chunk() { return 0; }
 
 // Matrix-core step on one 16x16 tile: FP64 (v_mfma_f64_16x16x4_f64) or
 // FP32 (v_mfma_f32_16x16x4_f32).  Both take A[r][q] / B[q][r] from lane
@@ -596,17 +593,6 @@ __global__ __launch_bounds__(256, MINW) void k_spgemm_q4j(
             }
         }
     }
-}
-
-// Pair layout of b x b operand blocks: element (x, m) of a block, m the
-// contraction index, sits at (m / 2) * 2b + 2x + (m & 1), so that the two
-// values a lane feeds to two consecutive MFMA steps are 16 contiguous bytes
-// (an odd b's last m has x alone: b (b - 1) + x).  "Left" pairs hold a left
-// operand (x the row, m the column), "right" pairs a right operand (x the
-// column, m the row).  A block keeps its b * b doubles.
-__device__ __host__ inline int pair_at(int b, int x, int m)
-{
-    return (b & 1) && m == b - 1 ? b * (b - 1) + x : (m >> 1) * 2 * b + 2 * x + (m & 1);
 }
 
 // Row runs of 2 (k_spgemm_q4j's dataflow, segments and order of the products)
@@ -1406,15 +1392,16 @@ __global__ __launch_bounds__(256) void k_spgemm_b4w(
     }
 }
 
-// The entries [e0, e1) (every `stride`-th) of one b = 4 row run, software
-// pipelined (complex x complex only in the split form for few runs, where
-// latency and not occupancy decides): the indices of entry e + 2 and the operands of
-// entry e + 1 are requested before the products of entry e, so that a wave
-// has the next entry's loads in flight while its products run (the loads
-// return in order, so waiting for an entry's operands never waits for later
-// requests).  The products are issued in the same order as a plain loop over
-// the entries.
-template <bool AC, bool BC, bool PIPE_CPLX>
+// The entries [e0, e1) (every `stride`-th) of one b = 4 row run
+// (SpgemmArgs::ch_*) with both operands by rows.  Each entry k of the run is
+// one triple step: every lane loads the same op(A)_ik element position (one
+// block for the whole wave) and the op(B)_kj elements of its four outputs
+// (zero where an output has no triple with this k); instruction jj of the
+// four v_mfma_f64_4x4x4_4b runs outputs 4 jj + g in its blocks g.  Software
+// pipelined: the indices of entry e + 2 and the operands of entry e + 1 are
+// requested before the products of entry e (the loads return in order, so
+// waiting for an entry's operands never waits for later requests).
+template <bool AC, bool BC>
 __device__ inline void b4_run_entries(int64_t e0, int64_t e1, int stride, const int32_t *__restrict__ ea,
                                       const int32_t *__restrict__ eb, const double *__restrict__ ar,
                                       const double *__restrict__ ai, const double *__restrict__ br,
@@ -1444,26 +1431,6 @@ __device__ inline void b4_run_entries(int64_t e0, int64_t e1, int stride, const 
         }
     };
     if (e0 >= e1) return;
-    if constexpr (AC && BC && !PIPE_CPLX) {
-        // complex x complex over many runs: twice the operand registers; the
-        // pipeline's extra set cost waves per SIMD and made these products
-        // slower, so they take the entries one at a time
-        for (int64_t e = e0; e < e1; e += stride) {
-            int a;
-            int4 kb;
-            Ops o;
-            load_idx(e, a, kb);
-            load_ops(a, kb, o);
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                rr[jj] = __builtin_amdgcn_mfma_f64_4x4x4f64(o.xar, o.xbr[jj], rr[jj], 0, 0, 0);
-                ii[jj] = __builtin_amdgcn_mfma_f64_4x4x4f64(o.xai, o.xbi[jj], ii[jj], 0, 0, 0);
-                ri[jj] = __builtin_amdgcn_mfma_f64_4x4x4f64(o.xar, o.xbi[jj], ri[jj], 0, 0, 0);
-                ir[jj] = __builtin_amdgcn_mfma_f64_4x4x4f64(o.xai, o.xbr[jj], ir[jj], 0, 0, 0);
-            }
-        }
-        return;
-    }
     Ops cur, nxt;
     int a_n = 0;
     int4 kb_n = make_int4(-1, -1, -1, -1);
@@ -1492,41 +1459,13 @@ __device__ inline void b4_run_entries(int64_t e0, int64_t e1, int stride, const 
     }
 }
 
-// FP64 b = 4 product over row runs of 16 outputs (SpgemmArgs::ch_*, slots in
-// the lane order below): one wave per run.  Each entry k of the run is one
-// triple step: every lane loads the same op(A)_ik element position (one
-// block for the whole wave) and the op(B)_kj elements of its four outputs
-// (zero where an output has no triple with this k); instruction jj of the
-// four v_mfma_f64_4x4x4_4b runs outputs 4 jj + g in its blocks g.  Against
-// k_spgemm_b4w the left-operand loads fall from one block per output and
-// triple to one per entry; the price is the absent (zero) products.
-template <bool AC, bool BC, int OPB>
-__global__ __launch_bounds__(256) void k_spgemm_b4j(
-    int64_t nch, const int64_t *__restrict__ off, const int32_t *__restrict__ ea,
-    const int32_t *__restrict__ eb, const int32_t *__restrict__ cout, const double *__restrict__ ar,
-    const double *__restrict__ ai, const double *__restrict__ br, const double *__restrict__ bi,
-    double *__restrict__ cr, double *__restrict__ ci, double alr, double ali, int remap)
-{
-    const int lane = threadIdx.x & 63;
-    const int g = (lane >> 2) & 3, r = lane & 3, q = lane >> 4;
-    const int64_t c = xcd_block((nch + 3) / 4, remap) * 4 + (threadIdx.x >> 6);
-    if (c >= nch) return;                      // uniform across the wave
-    const int ia = r * 4 + q;                          // A[r][q]
-    const int ib = OPB ? (r * 4 + q) : (q * 4 + r);    // op(B)[q][r]
-    const double cb = OPB ? -1.0 : 1.0;
-    double rr[4] = {0, 0, 0, 0}, ii[4] = {0, 0, 0, 0}, ri[4] = {0, 0, 0, 0}, ir[4] = {0, 0, 0, 0};
-    b4_run_entries<AC, BC, false>(off[c], off[c + 1], 1, ea, eb, ar, ai, br, bi, ia, ib, g, cb, rr, ii, ri, ir);
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-        const int p = cout[c * 16 + 4 * jj + g];
-        if (p >= 0) {
-            const double re = rr[jj] - ii[jj], im = ri[jj] + ir[jj];
-            const int64_t o = (int64_t)p * 16 + q * 4 + r;
-            cr[o] = alr * re - ali * im;
-            if (ci) ci[o] = alr * im + ali * re;
-        }
-    }
-}
+// Below this many runs a product takes the split form (one run per
+// workgroup): a wave per run would leave most of the 1,024 SIMDs idle.  Below
+// kB4Split8Runs the runs are split over 8 waves instead of 4 (16 measured no
+// faster on the 64-atom cluster).
+constexpr int64_t kB4SplitRuns = 4096, kB4Split8Runs = 1024;
+
+bool b4_split_form(int64_t nch) { return nch < kB4SplitRuns; }
 
 // FP64 b = 4 product over row runs of 16 outputs from operands whose lanes
 // take 16 bytes: A row-major, B with every block transposed (bt), so that
@@ -1545,31 +1484,27 @@ __global__ __launch_bounds__(256) void k_spgemm_b4j(
 // order: A tau 2.8, U K 6.5 ms).  32,768 atoms, R_K 12, ms per launch, 8-byte
 // loads -> now: A tau 4.3 -> 2.6 (0.2 of it the transposition of tau),
 // U K 7.5 -> 5.3 (0.3 transposing K), W U^dagger 7.5 -> 5.0.
-template <bool AC, bool BC, int CJB, int OUT>
-__global__ __launch_bounds__(256) void k_spgemm_b4p(
-    int64_t nch, const int64_t *__restrict__ off, const int32_t *__restrict__ ea,
-    const int32_t *__restrict__ eb, const int32_t *__restrict__ cout, const double *__restrict__ ar,
-    const double *__restrict__ ai, const double *__restrict__ br, const double *__restrict__ bi,
-    double *__restrict__ cr, double *__restrict__ ci, double alr, double ali, double *__restrict__ u,
-    double u_sign, int u_store, int remap)
+//
+// b4p_entries: the pairs of entries e0, e0 + stride, ... below e1 into the sums
+// rr, ii, ri, ir of the wave's 16 outputs; PIPE: the next pair's operands are
+// requested before this pair's products (else only its indices).
+template <bool AC, bool BC, bool PIPE>
+__device__ inline void b4p_entries(int64_t e0, int64_t e1, int stride, const int32_t *__restrict__ ea,
+                                   const int32_t *__restrict__ eb, const double *__restrict__ ar,
+                                   const double *__restrict__ ai, const double *__restrict__ br,
+                                   const double *__restrict__ bi, double (&rr)[4], double (&ii)[4], double (&ri)[4],
+                                   double (&ir)[4])
 {
     const int lane = threadIdx.x & 63;
     const int g = (lane >> 2) & 3, r = lane & 3, q = lane >> 4;
-    const int64_t c = xcd_block((nch + 3) / 4, remap) * 4 + (threadIdx.x >> 6);
-    if (c >= nch) return;                      // uniform across the wave
     const int lo = r * 4 + 2 * (q & 1), eo = q >> 1, slot = g * 4 + r;
     typedef double d2 __attribute__((ext_vector_type(2)));
-    // four sums per complex output: adding the imaginary products to the real
-    // ones' sum as they come doubled its roundings (error of a product against
-    // 64-bit arithmetic 6.0e-16 -> 8.5e-16) for 0 - 4 % of the time
-    double rr[4] = {0, 0, 0, 0}, ri[4] = {0, 0, 0, 0}, ii[4] = {0, 0, 0, 0}, ir[4] = {0, 0, 0, 0};
     struct Ops {
         d2 xar, xai, xbr[4], xbi[4];
     };
     struct Idx {
         int a, b;
     };
-    const int64_t e0 = off[c], e1 = off[c + 1];
     auto load_idx = [&](int64_t e) {
         Idx x{-1, -1};
         if (e + eo < e1) {
@@ -1608,53 +1543,141 @@ __global__ __launch_bounds__(256) void k_spgemm_b4p(
     };
     auto products = [&](const Ops &o) {
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) mma1(o.xar.x, o.xai.x, o.xbr[jj].x, o.xbi[jj].x, rr[jj], ri[jj], ii[jj], ir[jj]);
+        for (int jj = 0; jj < 4; ++jj)
+            mma1(o.xar.x, o.xai.x, o.xbr[jj].x, o.xbi[jj].x, rr[jj], ri[jj], ii[jj], ir[jj]);
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) mma1(o.xar.y, o.xai.y, o.xbr[jj].y, o.xbi[jj].y, rr[jj], ri[jj], ii[jj], ir[jj]);
+        for (int jj = 0; jj < 4; ++jj)
+            mma1(o.xar.y, o.xai.y, o.xbr[jj].y, o.xbi[jj].y, rr[jj], ri[jj], ii[jj], ir[jj]);
     };
-    if constexpr (!(AC && BC)) {
-        // the next pair's operands in flight while this pair's products run
+    if constexpr (PIPE) {
         Ops cur, nxt;
-        Idx n1 = load_idx(e0 + 2);
+        Idx n1 = load_idx(e0 + stride);
         load_ops(load_idx(e0), cur);
-        for (int64_t e = e0; e < e1; e += 2) {
-            const Idx n2 = load_idx(e + 4);
+        for (int64_t e = e0; e < e1; e += stride) {
+            const Idx n2 = load_idx(e + 2 * stride);
             load_ops(n1, nxt);
             products(cur);
             cur = nxt;
             n1 = n2;
         }
     } else {
-        // complex x complex: the second set of operands costs waves per SIMD
-        // (32,768 atoms, R 12: U K 5.0 -> 5.5 ms), so only the indices run ahead
         Idx n1 = load_idx(e0);
-        for (int64_t e = e0; e < e1; e += 2) {
+        for (int64_t e = e0; e < e1; e += stride) {
             Ops o;
             load_ops(n1, o);
-            n1 = load_idx(e + 2);
+            n1 = load_idx(e + stride);
             products(o);
         }
     }
+}
+
+// One element of output block p: alpha times the sums, row-major or with the
+// block transposed (OUT), and into the fused sum u.
+template <int CJB, int OUT>
+__device__ inline void b4p_store(int p, double rr, double ii, double ri, double ir, double *__restrict__ cr,
+                                 double *__restrict__ ci, double alr, double ali, double *__restrict__ u,
+                                 double u_sign, int u_store)
+{
+    const int lane = threadIdx.x & 63, r = lane & 3, q = lane >> 4;
+    const int64_t rm = (int64_t)p * 16 + q * 4 + r, tr = (int64_t)p * 16 + r * 4 + q;
+    constexpr double sb = CJB ? -1.0 : 1.0;
+    const double vr = rr - sb * ii, vi = sb * ri + ir;
+    const double re = alr * vr - ali * vi;
+    if (u) u[rm] = u_store ? u_sign * re : u[rm] + u_sign * re;
+    if (cr) cr[OUT ? tr : rm] = re;
+    if (ci) ci[OUT ? tr : rm] = alr * vi + ali * vr;
+}
+
+// One wave per run.  Complex x complex does not pipeline: a second set of
+// operands costs waves per SIMD (32,768 atoms, R 12: U K 5.0 -> 5.5 ms).  Four
+// sums per complex output: adding the imaginary products to the real ones' sum
+// as they come doubled its roundings (error of a product against 64-bit
+// arithmetic 6.0e-16 -> 8.5e-16) for 0 - 4 % of the time.
+template <bool AC, bool BC, int CJB, int OUT>
+__global__ __launch_bounds__(256) void k_spgemm_b4p(
+    int64_t nch, const int64_t *__restrict__ off, const int32_t *__restrict__ ea,
+    const int32_t *__restrict__ eb, const int32_t *__restrict__ cout, const double *__restrict__ ar,
+    const double *__restrict__ ai, const double *__restrict__ br, const double *__restrict__ bi,
+    double *__restrict__ cr, double *__restrict__ ci, double alr, double ali, double *__restrict__ u,
+    double u_sign, int u_store, int remap)
+{
+    const int64_t c = xcd_block((nch + 3) / 4, remap) * 4 + (threadIdx.x >> 6);
+    if (c >= nch) return;                      // uniform across the wave
+    const int g = (threadIdx.x >> 2) & 3;
+    double rr[4] = {0, 0, 0, 0}, ii[4] = {0, 0, 0, 0}, ri[4] = {0, 0, 0, 0}, ir[4] = {0, 0, 0, 0};
+    b4p_entries<AC, BC, !(AC && BC)>(off[c], off[c + 1], 2, ea, eb, ar, ai, br, bi, rr, ii, ri, ir);
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {
         const int p = cout[c * 16 + 4 * jj + g];
-        if (p >= 0) {
-            const int64_t rm = (int64_t)p * 16 + q * 4 + r, tr = (int64_t)p * 16 + r * 4 + q;
-            constexpr double sb = CJB ? -1.0 : 1.0;
-            const double vr = rr[jj] - sb * ii[jj], vi = sb * ri[jj] + ir[jj];
-            const double re = alr * vr - ali * vi;
-            if (u) u[rm] = u_store ? u_sign * re : u[rm] + u_sign * re;
-            if (cr) cr[OUT ? tr : rm] = re;
-            if (ci) ci[OUT ? tr : rm] = alr * vi + ali * vr;
-        }
+        if (p >= 0) b4p_store<CJB, OUT>(p, rr[jj], ii[jj], ri[jj], ir[jj], cr, ci, alr, ali, u, u_sign, u_store);
     }
+}
+
+// The same for products with few runs (small systems): one workgroup of W
+// waves per run, wave w taking the pairs of entries w, w + W, ..., the waves'
+// partial sums added in LDS, wave jj those of outputs 4 jj .. 4 jj + 3, in the
+// fixed order w = 0, 1, ...  Bound: with a run per compute unit still the
+// address unit (62 entries of 170 cycles at 8 bytes a lane, 80 at 16), then
+// the launch and its chain of loads.  64-atom cluster, us per launch, 8-byte
+// loads of one entry after the other -> now: U K 11.8 -> 8.8, W U^dagger
+// 13.7 -> 8.5.
+template <bool AC, bool BC, int CJB, int OUT, int W>
+__global__ __launch_bounds__(64 * W) void k_spgemm_b4ps(
+    int64_t nch, const int64_t *__restrict__ off, const int32_t *__restrict__ ea,
+    const int32_t *__restrict__ eb, const int32_t *__restrict__ cout, const double *__restrict__ ar,
+    const double *__restrict__ ai, const double *__restrict__ br, const double *__restrict__ bi,
+    double *__restrict__ cr, double *__restrict__ ci, double alr, double ali, double *__restrict__ u,
+    double u_sign, int u_store)
+{
+    static_assert(W >= 4, "one wave per four outputs adds the partial sums");
+    constexpr int NACC = 1 + (AC && BC) + BC + AC;   // sums per output: rr, ii, ri, ir
+    __shared__ double part[W][4][NACC][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t c = blockIdx.x;              // grid = nch: uniform across the workgroup
+    const int p = cout[c * 16 + 4 * (wv & 3) + ((lane >> 2) & 3)];   // output of the sums below
+    double rr[4] = {0, 0, 0, 0}, ii[4] = {0, 0, 0, 0}, ri[4] = {0, 0, 0, 0}, ir[4] = {0, 0, 0, 0};
+    b4p_entries<AC, BC, true>(off[c] + 2 * wv, off[c + 1], 2 * W, ea, eb, ar, ai, br, bi, rr, ii, ri, ir);
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+        int k = 0;
+        part[wv][jj][k++][lane] = rr[jj];
+        if (AC && BC) part[wv][jj][k++][lane] = ii[jj];
+        if (BC) part[wv][jj][k++][lane] = ri[jj];
+        if (AC) part[wv][jj][k++][lane] = ir[jj];
+    }
+    __syncthreads();
+    if (wv >= 4 || p < 0) return;
+    double sum[NACC];
+#pragma unroll
+    for (int k = 0; k < NACC; ++k) {
+        sum[k] = part[0][wv][k][lane];
+#pragma unroll
+        for (int w = 1; w < W; ++w) sum[k] += part[w][wv][k][lane];
+    }
+    constexpr bool CC = AC && BC;
+    b4p_store<CJB, OUT>(p, sum[0], CC ? sum[CC ? 1 : 0] : 0.0, BC ? sum[CC ? 2 : BC ? 1 : 0] : 0.0,
+                        AC ? sum[NACC - 1] : 0.0, cr, ci, alr, ali, u, u_sign, u_store);
 }
 
 template <bool AC, bool BC, int CJB, int OUT>
 static void launch_b4p_as(hipStream_t s, const SpgemmArgs &a, const SumInto &u)
 {
+#define RT_B4PS(W)                                                                                                  \
+    hipLaunchKernelGGL((k_spgemm_b4ps<AC, BC, CJB, OUT, W>), dim3((unsigned)a.nch), dim3(64 * W), 0, s, a.nch, a.ch_off, \
+                       a.ch_a, a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re, a.alpha_im, u.p,   \
+                       u.sign, u.store)
+    if (a.nch < kB4Split8Runs) {
+        RT_B4PS(8);
+        return;
+    }
+    if (a.nch < kB4SplitRuns) {
+        RT_B4PS(4);
+        return;
+    }
+#undef RT_B4PS
     const int remap = xcd_chunk_for((a.nch + 3) / 4);
-    hipLaunchKernelGGL((k_spgemm_b4p<AC, BC, CJB, OUT>), dim3(xcd_grid((a.nch + 3) / 4, remap)), dim3(256), 0, s, a.nch, a.ch_off, a.ch_a, a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re,
+    hipLaunchKernelGGL((k_spgemm_b4p<AC, BC, CJB, OUT>), dim3(xcd_grid((a.nch + 3) / 4, remap)), dim3(256), 0, s, a.nch,
+                       a.ch_off, a.ch_a, a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re,
                        a.alpha_im, u.p, u.sign, u.store, remap);
 }
 
@@ -1683,7 +1706,8 @@ void launch_spgemm_b4t(hipStream_t s, const SpgemmArgs &a, int conj_b, int out_t
     RT_HIP(hipGetLastError());
 }
 
-// The same product for products with few runs (small systems): one
+// FP64 b = 4 product over row runs with few runs (small systems) whose right
+// operand is by rows: one
 // workgroup of W waves per run, wave w taking the entries w, w + W, ..., so
 // that a run's chain of dependent loads is 1/W as long and W times as many
 // waves share the chip.  The waves' partial sums are added in LDS in the
@@ -1704,7 +1728,7 @@ __global__ __launch_bounds__(64 * W) void k_spgemm_b4js(
     const int ib = OPB ? (r * 4 + q) : (q * 4 + r);
     const double cb = OPB ? -1.0 : 1.0;
     double rr[4] = {0, 0, 0, 0}, ii[4] = {0, 0, 0, 0}, ri[4] = {0, 0, 0, 0}, ir[4] = {0, 0, 0, 0};
-    b4_run_entries<AC, BC, true>(off[c] + wv, off[c + 1], W, ea, eb, ar, ai, br, bi, ia, ib, g, cb, rr, ii, ri, ir);
+    b4_run_entries<AC, BC>(off[c] + wv, off[c + 1], W, ea, eb, ar, ai, br, bi, ia, ib, g, cb, rr, ii, ri, ir);
     auto pack = [&](double (*dst)[64]) {
         int k = 0;
 #pragma unroll
@@ -1741,14 +1765,6 @@ __global__ __launch_bounds__(64 * W) void k_spgemm_b4js(
     }
 }
 
-// Below this many runs a product takes the split form (one run per
-// workgroup): a wave per run would leave most of the 1,024 SIMDs idle.  Below
-// kB4Split8Runs the runs are split over 8 waves instead of 4 (16 measured no
-// faster on the 64-atom cluster).
-constexpr int64_t kB4SplitRuns = 4096, kB4Split8Runs = 1024;
-
-bool b4_split_form(int64_t nch) { return nch < kB4SplitRuns; }
-
 template <bool AC, bool BC, int OB>
 static void launch_b4j(hipStream_t s, const SpgemmArgs &a)
 {
@@ -1759,16 +1775,9 @@ static void launch_b4j(hipStream_t s, const SpgemmArgs &a)
                            a.alpha_im);
         return;
     }
-    if (a.nch < kB4SplitRuns) {
-        hipLaunchKernelGGL((k_spgemm_b4js<AC, BC, OB, 4>), dim3((unsigned)a.nch), dim3(256), 0, s, a.nch,
-                           a.ch_off, a.ch_a, a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re,
-                           a.alpha_im);
-        return;
-    }
-    const int remap = b4_chunk();
-    hipLaunchKernelGGL((k_spgemm_b4j<AC, BC, OB>), dim3(xcd_grid((a.nch + 3) / 4, remap)), dim3(256), 0, s,
-                       a.nch, a.ch_off, a.ch_a, a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re,
-                       a.alpha_im, remap);
+    RT_CHECK(a.nch < kB4SplitRuns, RTDM_E_ARG, "larger b = 4 products take transposed right operands");
+    hipLaunchKernelGGL((k_spgemm_b4js<AC, BC, OB, 4>), dim3((unsigned)a.nch), dim3(256), 0, s, a.nch, a.ch_off, a.ch_a,
+                       a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re, a.alpha_im);
 }
 
 template <bool AC, bool BC, int OB>

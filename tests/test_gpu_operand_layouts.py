@@ -84,12 +84,24 @@ def test_transposed_right_operand_b4(ranges, kind):
     """b = 4 over enough runs of 16 (at least 4,096) for the kernel that reads
     A by rows and B with transposed blocks, two entries at a time: short rows
     (one partly filled run each), odd numbers of entries, rows of several runs."""
-    n = {11.0: 1400}.get(ranges[2], 4200)
+    _check(4, _grid({11.0: 1400}.get(ranges[2], 4200)), ranges, kind)
+
+
+@pytest.mark.parametrize("kind", ["WU", "UK"])
+@pytest.mark.parametrize("n", [1, 2, 33, 64, 330, 900])
+def test_split_runs_b4(n, kind):
+    """The split form of few runs (8 waves a run below 1,024 runs, 4 below
+    4,096): a conjugate-transposed right operand two entries at a time, a plain
+    one by rows; runs of fewer pairs of entries than waves."""
+    _check(4, _grid(n), (5.0, 9.0, 8.0), kind)
+
+
+def _grid(n):
     rng = np.random.default_rng(3)
     g = DENSITY ** (-1.0 / 3.0)
     m = int(np.ceil(n ** (1.0 / 3.0)))
     p = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3)[:n] * g
-    _check(4, np.ascontiguousarray(p + rng.uniform(-0.4, 0.4, size=p.shape)), ranges, kind)
+    return np.ascontiguousarray(p + rng.uniform(-0.4, 0.4, size=p.shape))
 
 
 DENSITY = synth.CLUSTER_DENSITY
