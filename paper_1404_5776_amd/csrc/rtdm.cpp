@@ -3398,9 +3398,8 @@ void multiply(rtdm_ctx *c, rtdm_mat Cm, rtdm_mat Am, rtdm_mat Bm, int op_a, int 
                 if (op_b) alloc_like(c, Bcm, B);
                 if (ccm) alloc_like(c, Ccm, C);
             }
-            // pair layout as in a step; the static scratch holds no right pairs, so the call without
-            // allocations keeps the column-major copies
-            const bool pairs = !scratch && (A.cplx || B.cplx ? c->pairs_cplx : c->pairs_real) && runs_of_2(c, prod);
+            // pair layout as in a step (right pairs in the context's own Bp)
+            const bool pairs = (A.cplx || B.cplx ? c->pairs_cplx : c->pairs_real) && runs_of_2(c, prod);
             auto left = [&](const Mat &M, Mat &out) {
                 if (pairs) pack_planes(c, M, out, kPackLeft, s);
                 else transpose_into(c, M, out, s);
