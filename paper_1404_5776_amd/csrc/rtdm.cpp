@@ -324,6 +324,11 @@ struct rtdm_ctx {
     // left pairs of the left operand of a product without a kept copy (ETRS and
     // Magnus propagators at b = 13: U E1, the commutator, M T_k); allocated with them
     Mat Lp;
+    // Bp and Lp serve one product at a time.  Their last user: a product of rtdm_multiply
+    // (relay_ev recorded behind it) or a step, on relay_stream (take_relay)
+    hipEvent_t relay_ev = nullptr;
+    hipStream_t relay_stream = nullptr;
+    bool relay_used = false, relay_recorded = false;
     // FP32 copies for the reduced-precision Taylor terms (b = 13)
     DBuf<float> Ac32, tau32[2], zero32;
     DBuf<double> scratch;       // block inverse scratch and staging
@@ -933,6 +938,40 @@ void left_copy(rtdm_ctx *c, int prod, const Mat &M, Mat &out, hipStream_t s)
     else transpose_into(c, M, out, s);
 }
 
+bool is_capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (s) RT_HIP(hipStreamIsCapturing(s, &st));
+    return st != hipStreamCaptureStatusNone;
+}
+
+// Makes s the stream that uses Bp and Lp next.  Products that share no slot may be
+// issued on several streams of the caller's without an order of their own; what
+// shares these two buffers still has to run one after the other.  A step leaves
+// no event behind (it would cost each call a barrier, and the case is rare), so a
+// change of stream after one waits for the device.  Within a capture the caller's
+// graph has the order.
+void take_relay(rtdm_ctx *c, hipStream_t s)
+{
+    if (!c->Bp.re.p) return;
+    if (c->relay_used && c->relay_stream != s && !is_capturing(s)) {
+        if (c->relay_recorded) RT_HIP(hipStreamWaitEvent(s, c->relay_ev, 0));
+        else RT_HIP(hipDeviceSynchronize());
+    }
+    c->relay_used = true;
+    c->relay_recorded = false;
+    c->relay_stream = s;
+}
+
+// Behind a product issued by the caller on s: what a later user on another stream waits for.
+void leave_relay(rtdm_ctx *c, hipStream_t s)
+{
+    if (!c->Bp.re.p || is_capturing(s)) return;
+    if (!c->relay_ev) RT_HIP(hipEventCreateWithFlags(&c->relay_ev, hipEventDisableTiming));
+    RT_HIP(hipEventRecord(c->relay_ev, s));
+    c->relay_recorded = true;
+}
+
 // The right pairs of M, in Bp (valid until the next call).
 const Mat &right_pairs(rtdm_ctx *c, const Mat &M, hipStream_t s)
 {
@@ -1504,6 +1543,7 @@ int rtdm_destroy(rtdm_ctx *c)
     (void)hipDeviceSynchronize();
     for (auto e : c->events) (void)hipEventDestroy(e);
     drop_graph(c);
+    if (c->relay_ev) (void)hipEventDestroy(c->relay_ev);
     if (c->gstream) (void)hipStreamDestroy(c->gstream);
     delete c;
     return RTDM_OK;
@@ -2541,6 +2581,7 @@ int rtdm_step(rtdm_ctx *c, double dt, int64_t n_steps, void *stream)
         if (!c->gstream) RT_HIP(hipStreamCreate(&c->gstream));
         s = c->gstream;
     }
+    take_relay(c, s);
     StepCall sc = step_begin(c, dt, n_steps, s);
     eager_prefix(sc);
     if (sc.k < n_steps && c->opt.use_graph) {
@@ -2671,6 +2712,7 @@ int rtdm_batch_step(rtdm_batch *bt, double dt, int64_t n_steps, void *stream)
     calls.reserve(bt->ctx.size());
     for (auto *c : bt->ctx) {
         DevMemScope scope(&c->mem);
+        take_relay(c, s);
         calls.push_back(step_begin(c, dt, n_steps, s));
         eager_prefix(calls.back());
     }
@@ -3354,6 +3396,7 @@ void multiply(rtdm_ctx *c, rtdm_mat Cm, rtdm_mat Am, rtdm_mat Bm, int op_a, int 
              "no schedule of this product kind yet (the allocation-free call builds none): call rtdm_multiply once");
     const bool cres = A.cplx || B.cplx || ali != 0.0;
     RT_CHECK(C.cplx || !cres, RTDM_E_UNSUPPORTED, "complex result for a real matrix slot");
+    take_relay(c, s);
     c->prec = all_products_prec(c);
     try {
         // The step products of the b = 13 column-major path run exactly as in a
@@ -3423,6 +3466,7 @@ void multiply(rtdm_ctx *c, rtdm_mat Cm, rtdm_mat Am, rtdm_mat Bm, int op_a, int 
         } else {
             product(c, prod, A, B, C, alr, ali, s);
         }
+        leave_relay(c, s);
     } catch (...) {
         c->prec = RTDM_PREC_FP64;
         throw;

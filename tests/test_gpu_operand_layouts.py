@@ -96,6 +96,42 @@ def test_split_runs_b4(n, kind):
     _check(4, _grid(n), (5.0, 9.0, 8.0), kind)
 
 
+@pytest.mark.parametrize("b,n", [(4, 4200), (13, 300)])
+def test_products_issued_on_two_streams(b, n):
+    """Two products of one context that share no slot, on two streams without
+    an order of the caller's: both lay their right operand out in the same
+    buffer, so the library orders them; bytes as when issued one by one."""
+    import torch
+
+    xyz, (R_HS, R_P, R_K) = _grid(n), (5.0, 6.5, 6.5)
+    slot_r = {"S": R_HS, "X": R_P, "U": R_P, "K": R_K}
+    ctx = rtdm.Context(0)
+    try:
+        rtdm.rtdm_set_geometry(ctx.h, xyz, np.full(n, b, dtype=np.int32))
+        rtdm.rtdm_set_ranges(ctx.h, R_HS, R_P, R_K)
+        rng = np.random.default_rng(23)
+        for m in ("S", "X", "U", "K"):
+            v = rng.uniform(-1, 1, size=(O.pattern(xyz, slot_r[m]).nnzb, b, b))
+            rtdm.rtdm_upload(ctx.h, m, v + 1j * v[::-1] if m in "UK" else v)
+        jobs = [("A", "S", "X"), ("W", "U", "K")]      # the kinds S X and U K
+        ref = []
+        for j in jobs:
+            rtdm.rtdm_multiply(ctx.h, *j, 0, 0)
+            torch.cuda.synchronize()
+            ref.append(rtdm.rtdm_download(ctx.h, j[0], b))
+        streams = [torch.cuda.Stream() for _ in jobs]
+        for rep in range(8):
+            print(f"[gpu] two streams b={b} n={n} rep={rep}", flush=True)
+            for _ in range(4):
+                for j, st in zip(jobs, streams):
+                    rtdm.rtdm_multiply(ctx.h, *j, 0, 0, 1.0, st)
+            torch.cuda.synchronize()
+            for j, r in zip(jobs, ref):
+                assert np.array_equal(rtdm.rtdm_download(ctx.h, j[0], b), r), (j, rep)
+    finally:
+        ctx.close()
+
+
 def _grid(n):
     rng = np.random.default_rng(3)
     g = DENSITY ** (-1.0 / 3.0)
