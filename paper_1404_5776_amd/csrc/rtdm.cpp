@@ -242,7 +242,8 @@ bool build_runs(Sched &S, const Pattern &A, const Pattern &B, const Pattern &C, 
     R->order.alloc(std::max<int64_t>(nch, 1));
     RT_HIP(hipMemcpy(R->off.p, off.data(), off.size() * sizeof(int64_t), hipMemcpyHostToDevice));
     launch_run_fill(nullptr, nch, d_row.p, d_p0.p, C.d_rowptr.p, C.d_col.p, A.d_rowptr.p, A.d_col.p, B.d_rowptr.p,
-                    B.d_col.p, B.d_trans.p, op_b, nj, inter4, R->off.p, R->a.p, R->b.p, R->out.p, segmented);
+                    B.d_col.p, B.d_trans.p, op_b, nj, inter4, R->off.p, R->a.p, R->b.p, R->out.p,
+                    segmented ? R->seg.p : nullptr);
     const std::vector<int32_t> ord = run_order(*R, tile_i);
     if (!ord.empty())
         RT_HIP(hipMemcpy(R->order.p, ord.data(), ord.size() * sizeof(int32_t), hipMemcpyHostToDevice));

@@ -82,7 +82,12 @@ __global__ void k_sym_fill(int64_t nout, const int32_t *__restrict__ c_rowof,
 // entry is a k present for at least one output.  Slot of output t in an
 // entry: t, or (t % 4) * 4 + t / 4 with `inter4` (the lane order of the b = 4
 // kernel, whose lane group g reads outputs g, g + 4, g + 8, g + 12).
-constexpr int kMaxRun = 16;
+constexpr int kMaxRun = 16, kRunThreads = 128;
+
+// Set of outputs (a bit mask) of the u-th group of a segmented run of 2: both, first, second.
+constexpr int kRunClasses = 3;
+__device__ inline int run_class(int u) { return (0x213 >> (4 * u)) & 15; }
+
 template <bool FILL>
 __global__ void k_run_sym(int64_t nch, const int32_t *__restrict__ run_row, const int64_t *__restrict__ run_p0,
                           const int64_t *__restrict__ c_ptr, const int32_t *__restrict__ c_col,
@@ -90,7 +95,7 @@ __global__ void k_run_sym(int64_t nch, const int32_t *__restrict__ run_row, cons
                           const int64_t *__restrict__ b_ptr, const int32_t *__restrict__ b_col,
                           const int32_t *__restrict__ b_trans, int op_b, int nj, int inter4,
                           int64_t *__restrict__ cnt, const int64_t *__restrict__ off, int32_t *__restrict__ ea,
-                          int32_t *__restrict__ eb, int32_t *__restrict__ rout, int segd, int32_t *__restrict__ seg)
+                          int32_t *__restrict__ eb, int32_t *__restrict__ rout, int32_t *__restrict__ seg)
 {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= nch) return;
@@ -105,45 +110,47 @@ __global__ void k_run_sym(int64_t nch, const int32_t *__restrict__ run_row, cons
     }
     if (FILL)
         for (int t = 0; t < nj; ++t) rout[c * nj + t] = t < m ? (int32_t)(p0 + t) : -1;
-    // With `seg` (runs of 2): the entries feeding both outputs first, then
-    // those feeding only the first, then only the second (each in ascending
-    // k); the count pass records the sizes of the first two segments.
-    const int passes = segd ? 3 : 1;
-    const int want[3] = {3, 1, 2};
+    // Segmented runs (seg, runs of 2): the entries grouped by the set of outputs
+    // they feed (run_class order), each group in ascending k, so that a kernel
+    // issues only present products; seg holds the sizes of the first two groups.
+    // One walk counts (or places) every group, its counters (or cursors) in LDS.
+    __shared__ int32_t cur[kRunThreads][kRunClasses + 1];
+    int32_t *my = cur[threadIdx.x];
+    if (seg) {
+        int32_t at = 0;
+        for (int u = 0; u < kRunClasses; ++u) {
+            my[run_class(u)] = FILL ? at : 0;
+            if (FILL && u < 2) at += seg[2 * c + u];
+        }
+    }
     int64_t n = 0, o = FILL ? off[c] : 0;
-    int64_t nseg[3] = {0, 0, 0};
-    for (int pass = 0; pass < passes; ++pass) {
-        for (int t = 0; t < m; ++t) pb[t] = b_ptr[c_col[p0 + t]];
-        for (int64_t pa = a_ptr[i]; pa < a_ptr[i + 1]; ++pa) {
-            const int k = a_col[pa];
-            int mask = 0;
-            for (int t = 0; t < m; ++t) {
-                while (pb[t] < eb_end[t] && b_col[pb[t]] < k) ++pb[t];
-                if (pb[t] < eb_end[t] && b_col[pb[t]] == k) mask |= 1 << t;
-            }
-            if (!mask || (segd && mask != want[pass])) continue;
-            ++nseg[pass];
-            if (FILL) {
-                ea[o] = (int32_t)pa;
-                for (int t = 0; t < nj; ++t) {
-                    const int slot = inter4 ? (t & 3) * 4 + (t >> 2) : t;
-                    int32_t v = -1;
-                    // op(B)_kj: block (k, j) = trans of (j, k), or (j, k) itself for the conjugate transpose
-                    if ((mask >> t) & 1) v = op_b ? (int32_t)pb[t] : b_trans[pb[t]];
-                    eb[o * nj + slot] = v;
-                }
-                ++o;
-            } else {
-                ++n;
-            }
+    for (int64_t pa = a_ptr[i]; pa < a_ptr[i + 1]; ++pa) {
+        const int k = a_col[pa];
+        int mask = 0;
+        for (int t = 0; t < m; ++t) {
+            while (pb[t] < eb_end[t] && b_col[pb[t]] < k) ++pb[t];
+            if (pb[t] < eb_end[t] && b_col[pb[t]] == k) mask |= 1 << t;
+        }
+        if (!mask) continue;
+        if (!FILL) {
+            ++n;
+            if (seg) ++my[mask];
+            continue;
+        }
+        const int64_t e = seg ? off[c] + my[mask]++ : o++;
+        ea[e] = (int32_t)pa;
+        for (int t = 0; t < nj; ++t) {
+            const int slot = inter4 ? (t & 3) * 4 + (t >> 2) : t;
+            int32_t v = -1;
+            // op(B)_kj: block (k, j) = trans of (j, k), or (j, k) itself for the conjugate transpose
+            if ((mask >> t) & 1) v = op_b ? (int32_t)pb[t] : b_trans[pb[t]];
+            eb[e * nj + slot] = v;
         }
     }
     if (!FILL) {
         cnt[c] = n;
-        if (seg) {
-            seg[2 * c] = (int32_t)nseg[0];
-            seg[2 * c + 1] = (int32_t)nseg[1];
-        }
+        if (seg)
+            for (int u = 0; u < 2; ++u) seg[2 * c + u] = my[run_class(u)];
     }
 }
 
@@ -154,23 +161,23 @@ void launch_run_count(hipStream_t s, int64_t nch, const int32_t *run_row, const 
     if (nch == 0) return;
     RT_CHECK(nj >= 1 && nj <= kMaxRun, RTDM_E_ARG, "row runs hold 1..16 outputs");
     RT_CHECK(!seg || nj == 2, RTDM_E_ARG, "segmented row runs hold 2 outputs");
-    hipLaunchKernelGGL(k_run_sym<false>, dim3((unsigned)((nch + 127) / 128)), dim3(128), 0, s, nch, run_row, run_p0,
-                       c_ptr, c_col, a_ptr, a_col, b_ptr, b_col, nullptr, 0, nj, 0, cnt, nullptr, nullptr, nullptr,
-                       nullptr, seg ? 1 : 0, seg);
+    hipLaunchKernelGGL(k_run_sym<false>, dim3((unsigned)((nch + kRunThreads - 1) / kRunThreads)), dim3(kRunThreads), 0, s,
+                       nch, run_row, run_p0, c_ptr, c_col, a_ptr, a_col, b_ptr, b_col, nullptr, 0, nj, 0, cnt, nullptr,
+                       nullptr, nullptr, nullptr, seg);
     RT_HIP(hipGetLastError());
 }
 
 void launch_run_fill(hipStream_t s, int64_t nch, const int32_t *run_row, const int64_t *run_p0, const int64_t *c_ptr,
                      const int32_t *c_col, const int64_t *a_ptr, const int32_t *a_col, const int64_t *b_ptr,
                      const int32_t *b_col, const int32_t *b_trans, int op_b, int nj, int inter4, const int64_t *off,
-                     int32_t *ea, int32_t *eb, int32_t *rout, int segmented)
+                     int32_t *ea, int32_t *eb, int32_t *rout, int32_t *seg)
 {
     if (nch == 0) return;
     RT_CHECK(nj >= 1 && nj <= kMaxRun, RTDM_E_ARG, "row runs hold 1..16 outputs");
-    RT_CHECK(!segmented || (nj == 2 && !inter4), RTDM_E_ARG, "segmented row runs hold 2 outputs");
-    hipLaunchKernelGGL(k_run_sym<true>, dim3((unsigned)((nch + 127) / 128)), dim3(128), 0, s, nch, run_row, run_p0,
-                       c_ptr, c_col, a_ptr, a_col, b_ptr, b_col, b_trans, op_b, nj, inter4, nullptr, off, ea, eb,
-                       rout, segmented ? 1 : 0, nullptr);
+    RT_CHECK(!seg || (nj == 2 && !inter4), RTDM_E_ARG, "segmented row runs hold 2 outputs");
+    hipLaunchKernelGGL(k_run_sym<true>, dim3((unsigned)((nch + kRunThreads - 1) / kRunThreads)), dim3(kRunThreads), 0, s,
+                       nch, run_row, run_p0, c_ptr, c_col, a_ptr, a_col, b_ptr, b_col, b_trans, op_b, nj, inter4, nullptr,
+                       off, ea, eb, rout, seg);
     RT_HIP(hipGetLastError());
 }
 
