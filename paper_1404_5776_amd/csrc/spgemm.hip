@@ -610,18 +610,23 @@ __global__ __launch_bounds__(256, MINW) void k_spgemm_q4j(
 // cores busy 52 %.  The pair layout brings two contraction steps per load:
 // 7 loads per operand block instead of 13.  Lanes 13..15 of a row group read
 // row 12 again: they only feed rows and columns of the tile that are not
-// stored.  What holds it now is the service of L2 misses: three waves per
-// SIMD with up to 168 registers (more loads of one wave in flight, fewer
-// outputs sharing an L2) beat four by 8 % and five by 18 % on the real
-// product.  4,096 atoms, R 16, ms per launch, 8-byte loads at four waves ->
-// now: A tau 19.9 -> 15.8, U K 49.7 -> 45.8, W U^dagger 48.3 -> 45.7.
+// stored.  The complex products are then held by the matrix cores (91 % busy,
+// 13 of 16 rows and columns of a tile useful); the real one, with half the
+// operations per byte, by operand blocks from beyond the XCD's L2 (512 atoms:
+// its loads alone take 1.10 ms of 1.23, 0.86 if the L2 held them all; its
+// matrix instructions alone 0.95).  Fewer outputs sharing an L2 are better
+// there: three waves per SIMD beat four by 8 % and five by 18 %, and with the
+// next group's loads issued behind this one's matrix instructions two beat
+// three by 4 %.  4,096 atoms, R 16, ms per launch, 8-byte loads at four waves
+// -> now: A tau 19.9 -> 15.7, U K 49.7 -> 45.8, W U^dagger 48.3 -> 45.7.
+// Complex products have no registers to load a group ahead.
 // OUT: 0 row-major output, 1 left pairs, 2 right pairs.  u (real products,
 // nullable): u = u_sign * output (u_store) or u += u_sign * output, row-major:
 // the Taylor sum, whose own pass would read the term again.
 typedef double pd2 __attribute__((ext_vector_type(2), aligned(8)));
 typedef __attribute__((address_space(1))) const pd2 gpd2;
 template <int B, bool AC, bool BC, int CJB, int OUT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_spgemm_q4p(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AC || BC ? 3 : 2, AC || BC ? 3 : 2))) void k_spgemm_q4p(
     int64_t nch, const int64_t *__restrict__ off, const int32_t *__restrict__ ea,
     const int32_t *__restrict__ eb, const int32_t *__restrict__ cout,
     const double *__restrict__ ar, const double *__restrict__ ai, const double *__restrict__ br,
@@ -658,6 +663,65 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     if (ne > 0) fetch(0);
     auto groups = [&](int gb, int ge, auto act) {
         constexpr int ACT = decltype(act)::value;
+        if constexpr (!AC && !BC) {
+            // slice h of the next group is loaded into the registers that slice h of
+            // this one has just left, so a group's loads have its matrix
+            // instructions' time to arrive
+            if (gb >= ge) return;
+            const gdouble *pa = gz, *pb[NJ] = {gz, gz};
+            pd2 xa[B / 2], xb[NJ][B / 2];
+            double ya = 0, yb[NJ] = {0, 0};
+            auto point = [&](int g) {
+                const bool on = g + q < ge;
+                pa = on ? (const gdouble *)(ar + (int64_t)na * BB + 2 * r) : gz;
+#pragma unroll
+                for (int t = 0; t < NJ; ++t)
+                    if ((ACT >> t) & 1) pb[t] = on ? (const gdouble *)(br + (int64_t)nb[t] * BB + 2 * r) : gz;
+                fetch(min(g + 4, ge));
+            };
+            auto load = [&](int h) {
+                xa[h] = *(const gpd2 *)(pa + 2 * B * h);
+#pragma unroll
+                for (int t = 0; t < NJ; ++t)
+                    if ((ACT >> t) & 1) xb[t][h] = *(const gpd2 *)(pb[t] + 2 * B * h);
+            };
+            auto load_last = [&]() {                   // the unpaired contraction index
+                const int o = B * (B - 1) - r;
+                ya = pa[o];
+#pragma unroll
+                for (int t = 0; t < NJ; ++t)
+                    if ((ACT >> t) & 1) yb[t] = pb[t][o];
+            };
+            auto mma = [&](double va, double v0, double v1) {
+                if (ACT & 1) rr[0] = Mfma16<double>::step(va, v0, rr[0]);
+                if (ACT & 2) rr[1] = Mfma16<double>::step(va, v1, rr[1]);
+            };
+            point(gb);
+#pragma unroll
+            for (int h = 0; h < B / 2; ++h) load(h);
+            load_last();
+            __builtin_amdgcn_sched_barrier(0);
+            for (int g = gb + 4; g < ge; g += 4) {
+                point(g);
+#pragma unroll
+                for (int h = 0; h < B / 2; ++h) {
+                    mma(xa[h].x, xb[0][h].x, xb[1][h].x);
+                    mma(xa[h].y, xb[0][h].y, xb[1][h].y);
+                    load(h);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                mma(ya, yb[0], yb[1]);
+                load_last();
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int h = 0; h < B / 2; ++h) {
+                mma(xa[h].x, xb[0][h].x, xb[1][h].x);
+                mma(xa[h].y, xb[0][h].y, xb[1][h].y);
+            }
+            mma(ya, yb[0], yb[1]);
+            return;
+        }
         for (int g = gb; g < ge; g += 4) {
             const gdouble *pa = gz, *pai = gz;
             const gdouble *pb[NJ], *pbi[NJ];
