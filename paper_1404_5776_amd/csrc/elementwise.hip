@@ -863,6 +863,40 @@ void launch_red_diff2(hipStream_t s, int64_t n, const double *x, const double *y
     RT_HIP(hipGetLastError());
 }
 
+// End of an inverse iteration whose products read pair layout (b = 13):
+// X' = 2 X - X W (into xw), its left and right pairs for the next products, and
+// the partial sums of k_red_diff2, in the same order.  Bound: memory; two
+// matrices read and three written where axpby, the sums and both re-layouts
+// moved nine and W was laid out in two more.  Inverse of 1,000 atoms, R_K 16:
+// 22.8 -> 21.8 ms.
+__global__ __launch_bounds__(kT) void k_newton_update13(int64_t n, const double *__restrict__ x,
+                                                        double *__restrict__ xw, double *__restrict__ left,
+                                                        double *__restrict__ right, double *__restrict__ partials)
+{
+    constexpr int B = 13, BB = B * B;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < n; e += (int64_t)kRedBlocks * kT) {
+        const int64_t p = e / BB;
+        const int w = (int)(e - p * BB), r = w / B, c = w - r * B;
+        const double old = x[e], now = 2.0 * old - xw[e];
+        xw[e] = now;
+        left[p * BB + pair_at(B, r, c)] = now;
+        right[p * BB + pair_at(B, c, r)] = now;
+        const double d = now - old;
+        v[0] += d * d;
+        v[1] += now * now;
+        v[3] = fmax(v[3], fabs(d));
+    }
+    write_partials(v, partials);
+}
+
+void launch_newton_update13(hipStream_t s, int64_t n, const double *x, double *xw, double *left, double *right,
+                            double *partials)
+{
+    hipLaunchKernelGGL(k_newton_update13, dim3(kRedBlocks), dim3(kT), 0, s, n, x, xw, left, right, partials);
+    RT_HIP(hipGetLastError());
+}
+
 __global__ __launch_bounds__(kT) void k_red_unitarity(int64_t nnzb_p, int b,
                                                       const int32_t *__restrict__ p_to_hs,
                                                       const double *__restrict__ sv,

@@ -2047,6 +2047,7 @@ int rtdm_build_inverse(rtdm_ctx *c, void *stream, int *iters, double *residual)
     set_device(c);
     require(c->ranges_set && c->uploaded[RTDM_MAT_S], "upload S first");
     hipStream_t s = (hipStream_t)stream;
+    take_relay(c, s);
     Mat &S = c->mats[RTDM_MAT_S];
     Mat &X = c->mats[RTDM_MAT_X];
     const Pattern &ps = pat_of(c, R_HS), &pp = pat_of(c, R_P);
@@ -2078,18 +2079,32 @@ int rtdm_build_inverse(rtdm_ctx *c, void *stream, int *iters, double *residual)
     // Returns 1 converged, 0 diverged, -1 hit the cap.
     auto run = [&](int &k_out, double &r_out) -> int {
         std::vector<double> res;
+        const bool pr = cm && c->pairs_real;
+        ProductOut w_right;
+        if (pr) {
+            // pair layout: the products of an iteration read X in Xc and Bp, laid out by the last
+            // one's update, and W as the first product writes it
+            w_right.layout = kOutRight;
+            left_copy(c, RTDM_PROD_AT, X, c->Xc, s);
+            right_pairs(c, X, s);
+        }
         for (int k = 0; k < c->opt.inv_max_iter; ++k) {
-            if (cm) {
-                const bool pr = c->pairs_real;
-                product_cm(c, RTDM_PROD_SX, Sc, right_copy(c, RTDM_PROD_SX, X, s), c->Wh, 0, 0, 1.0, s, pr);  // W = P_P(S X)
-                left_copy(c, RTDM_PROD_AT, X, c->Xc, s);
-                product_cm(c, RTDM_PROD_AT, c->Xc, right_copy(c, RTDM_PROD_AT, c->Wh, s), c->Xn, 0, 0, 1.0, s, pr);  // P_P(X W)
+            if (pr) {
+                product_cm(c, RTDM_PROD_SX, Sc, c->Bp, c->Wh, 0, 0, 1.0, s, true, w_right);   // W = P_P(S X)
+                product_cm(c, RTDM_PROD_AT, c->Xc, c->Wh, c->Xn, 0, 0, 1.0, s, true);         // P_P(X W)
+                launch_newton_update13(s, ne, X.re.p, c->Xn.re.p, c->Xc.re.p, c->Bp.re.p, c->partials.p);
             } else {
-                product(c, RTDM_PROD_SX, S, X, c->Wh, 1.0, 0.0, s);       // W = P_P(S X)
-                product(c, RTDM_PROD_AT, X, c->Wh, c->Xn, 1.0, 0.0, s);   // P_P(X W)
+                if (cm) {
+                    product_cm(c, RTDM_PROD_SX, Sc, X, c->Wh, 0, 0, 1.0, s, false);
+                    left_copy(c, RTDM_PROD_AT, X, c->Xc, s);
+                    product_cm(c, RTDM_PROD_AT, c->Xc, c->Wh, c->Xn, 0, 0, 1.0, s, false);
+                } else {
+                    product(c, RTDM_PROD_SX, S, X, c->Wh, 1.0, 0.0, s);
+                    product(c, RTDM_PROD_AT, X, c->Wh, c->Xn, 1.0, 0.0, s);
+                }
+                launch_axpby(s, ne, 2.0, X.re.p, -1.0, c->Xn.re.p, c->Xn.re.p);  // X' = 2X - XW
+                launch_red_diff2(s, ne, c->Xn.re.p, X.re.p, c->partials.p);
             }
-            launch_axpby(s, ne, 2.0, X.re.p, -1.0, c->Xn.re.p, c->Xn.re.p);  // X' = 2X - XW
-            launch_red_diff2(s, ne, c->Xn.re.p, X.re.p, c->partials.p);
             reduce_finish(c, s, c->hot_sums.p);
             double h[4];
             read_scalars(h, c->hot_sums.p, 4, s);
@@ -2148,7 +2163,7 @@ int rtdm_build_inverse(rtdm_ctx *c, void *stream, int *iters, double *residual)
     c->X_valid = (st == 1);
     c->Xc_valid = false;
     if (cm && st == 1) {
-        left_copy(c, RTDM_PROD_XH, X, c->Xc, s);   // the column-major copy of the converged X
+        if (!c->pairs_real) left_copy(c, RTDM_PROD_XH, X, c->Xc, s);   // the column-major copy of the converged X
         c->Xc_valid = true;
     }
     c->U_valid = false;
@@ -2784,6 +2799,7 @@ int rtdm_ground_state(rtdm_ctx *c, double n_occ, double tol, int max_iter, void 
     RT_CHECK(n_occ > 0 && std::isfinite(n_occ) && tol > 0 && max_iter >= 1 && max_iter <= 64, RTDM_E_ARG,
              "bad ground-state arguments (max_iter 1..64)");
     hipStream_t s = (hipStream_t)stream;
+    take_relay(c, s);
     c->prec = RTDM_PREC_FP64;
     Mat &A = c->mats[RTDM_MAT_A], &X = c->mats[RTDM_MAT_X], &K = c->mats[RTDM_MAT_K];
     const Pattern &pp = pat_of(c, R_P), &pk = pat_of(c, R_K);
@@ -3175,6 +3191,7 @@ int rtdm_autotune(rtdm_ctx *c, void *stream, int *wpb_out, int *tile_out)
     set_device(c);
     require(c->ranges_set, "set_ranges first");
     hipStream_t s = (hipStream_t)stream;
+    take_relay(c, s);
     if (c->b == 13) {
         const int wpbs[3] = {4, 8, 16}, tiles[3] = {64, 256, 1024};
         // events and the context's timing flag are restored however the sweep ends
@@ -3323,6 +3340,7 @@ int rtdm_unitarity(rtdm_ctx *c, double out[3], void *stream)
     require(c->ranges_set && c->U_valid && c->uploaded[RTDM_MAT_S], "no propagator yet");
     RT_CHECK(out, RTDM_E_ARG, "null output");
     hipStream_t s = (hipStream_t)stream;
+    take_relay(c, s);
     unitarity_sums(c, s);
     double u[4], s2[4];
     read_scalars(u, c->unit_sums.p, 4, s);
@@ -3341,6 +3359,7 @@ int rtdm_inverse_error(rtdm_ctx *c, double out[3], void *stream)
     require(c->ranges_set && c->X_valid && c->uploaded[RTDM_MAT_S], "build or upload the inverse first");
     RT_CHECK(out, RTDM_E_ARG, "null output");
     hipStream_t s = (hipStream_t)stream;
+    take_relay(c, s);
     product(c, RTDM_PROD_XH, c->mats[RTDM_MAT_X], c->mats[RTDM_MAT_S], c->Wh, 1.0, 0.0, s);
     const Pattern &pp = pat_of(c, R_P);
     launch_red_minus_identity(s, pp.nnzb, c->b, pp.d_rowof.p, pp.d_col.p, c->Wh.re.p, c->partials.p);

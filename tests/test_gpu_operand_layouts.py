@@ -96,6 +96,48 @@ def test_split_runs_b4(n, kind):
     _check(4, _grid(n), (5.0, 9.0, 8.0), kind)
 
 
+@pytest.mark.parametrize("n", [1, 2, 5, 23])
+def test_inverse_iteration_b13(n):
+    """The b = 13 iteration that makes X' and both its operand forms in one pass,
+    with ranges that keep every pair: X is the inverse of S.  The last step
+    forms 2 X - X (S X) with sums of N products each, so its rounding is at
+    most 2 (N + 2) eps (1 + |X||S|) |X|; its own error is the square of the
+    one before (below 1e-10).   X H0 then reads the same X."""
+    b, xyz = 13, synth.cluster_positions(n, np.random.default_rng(n)) if n > 1 else np.zeros((1, 3))
+    print(f"[gpu] inverse b={b} n={n}", flush=True)
+    R = 200.0
+    pat = O.pattern(xyz, R)
+    rng = np.random.default_rng(41)
+    N = n * b
+    off = rng.uniform(-1, 1, size=(N, N))
+    S = np.eye(N) + 0.3 / N * (off + off.T)
+    blocks = S.reshape(n, b, n, b).transpose(0, 2, 1, 3).reshape(n * n, b, b)
+    ctx = rtdm.Context(0)
+    try:
+        rtdm.rtdm_set_geometry(ctx.h, xyz, np.full(n, b, dtype=np.int32))
+        rtdm.rtdm_set_ranges(ctx.h, R, R, R)
+        ctx.b = b
+        assert pat.nnzb == n * n
+        rtdm.rtdm_upload(ctx.h, "S", np.ascontiguousarray(blocks))
+        _, res = rtdm.rtdm_build_inverse(ctx.h)
+        X = np.real(rtdm.rtdm_download(ctx.h, "X", b)).reshape(n, n, b, b).transpose(0, 2, 1, 3).reshape(N, N)
+        want = np.linalg.inv(S)
+        nx = np.linalg.norm(want, 2)
+        bound = (2.0 * (N + 2) * np.finfo(float).eps * (1.0 + N * nx * np.linalg.norm(S, 2)) + 1e-20) * nx
+        assert res < 1e-10
+        assert np.linalg.norm(X - want, 2) <= bound, (np.linalg.norm(X - want, 2), bound)
+        # the left form of X: X H0 as a product
+        H = rng.uniform(-1, 1, size=(n * n, b, b))
+        rtdm.rtdm_upload(ctx.h, "H0", H)
+        rtdm.rtdm_multiply(ctx.h, "A", "X", "H0", 0, 0)
+        A = np.real(rtdm.rtdm_download(ctx.h, "A", b))
+        ref, _ = O.spgemm(O.BSM(pat, b, X.reshape(n, b, n, b).transpose(0, 2, 1, 3).reshape(n * n, b, b).astype(complex)),
+                          O.BSM(pat, b, H.astype(complex)), pat, 1.0, 0, 0)
+        assert np.abs(A - ref.val.real).max() <= 4.0 * (N + 2) * np.finfo(float).eps * N * nx
+    finally:
+        ctx.close()
+
+
 @pytest.mark.parametrize("b,n", [(4, 4200), (13, 300)])
 def test_products_issued_on_two_streams(b, n):
     """Two products of one context that share no slot, on two streams without
