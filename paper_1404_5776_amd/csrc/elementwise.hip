@@ -167,12 +167,12 @@ void launch_kick(hipStream_t s, int64_t nnzb, int b, const int32_t *rowof, const
 // (transposed blocks, right pairs), written here instead of by a pass of its
 // own over K before the product.
 template <int B, typename I>
-__global__ __launch_bounds__(kT) void k_hermitize(I n, int b, const int32_t *__restrict__ trans,
-                                                  const double *__restrict__ knr,
-                                                  const double *__restrict__ kni,
-                                                  double *__restrict__ kr, double *__restrict__ ki,
-                                                  double *__restrict__ kr_t, double *__restrict__ ki_t,
-                                                  double *__restrict__ partials)
+__device__ __forceinline__ void hermitize_block(I n, int b, const int32_t *__restrict__ trans,
+                                                const double *__restrict__ knr,
+                                                const double *__restrict__ kni,
+                                                double *__restrict__ kr, double *__restrict__ ki,
+                                                double *__restrict__ kr_t, double *__restrict__ ki_t,
+                                                double *__restrict__ partials)
 {
     const I bs = B ? B : b, bb = bs * bs;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
@@ -194,6 +194,17 @@ __global__ __launch_bounds__(kT) void k_hermitize(I n, int b, const int32_t *__r
         v[1] += xr * xr + xi * xi;
     }
     write_partials(v, partials);
+}
+
+template <int B, typename I>
+__global__ __launch_bounds__(kT) void k_hermitize(I n, int b, const int32_t *__restrict__ trans,
+                                                  const double *__restrict__ knr,
+                                                  const double *__restrict__ kni,
+                                                  double *__restrict__ kr, double *__restrict__ ki,
+                                                  double *__restrict__ kr_t, double *__restrict__ ki_t,
+                                                  double *__restrict__ partials)
+{
+    hermitize_block<B, I>(n, b, trans, knr, kni, kr, ki, kr_t, ki_t, partials);
 }
 
 void launch_hermitize(hipStream_t s, int64_t nnzb, int b, const int32_t *trans, const double *knr,
@@ -226,21 +237,22 @@ void launch_hermitize(hipStream_t s, int64_t nnzb, int b, const int32_t *trans, 
 // of 50 us.
 // prev (nullable) receives the old q_i (keep_old) or the new one, ref
 // (nullable) the new one of the first K.
-template <int B, int W>
-__global__ __launch_bounds__(kT) void k_mulliken(int n_atoms, int n_k, int b, const int64_t *__restrict__ s_ptr,
-                                                 const int32_t *__restrict__ s_trans,
-                                                 const int32_t *__restrict__ s_to_k, const double *__restrict__ sv,
-                                                 KPlanes kp, double *__restrict__ q, double *__restrict__ prev,
-                                                 int keep_old, double *__restrict__ ref)
+// The charges of a workgroup's atoms; block_at(kk, kb, w, a, c) gives element w = (a, c)
+// of block kb of the real part of kick set kk's K.
+template <int B, int W, typename F>
+__device__ __forceinline__ void mulliken_block(int blk, int n_atoms, int n_k, int b, const int64_t *__restrict__ s_ptr,
+                                               const int32_t *__restrict__ s_trans,
+                                               const int32_t *__restrict__ s_to_k, const double *__restrict__ sv,
+                                               double *__restrict__ q, double *__restrict__ prev, int keep_old,
+                                               double *__restrict__ ref, F block_at)
 {
     __shared__ double part[kT / 64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     constexpr int PER = kT / 64 / W;           // atoms per workgroup
-    const int x0 = blockIdx.x * PER + wv / W;  // (kick, atom) of this wave
+    const int x0 = blk * PER + wv / W;         // (kick, atom) of this wave
     const bool live = x0 < n_atoms * n_k;
     const int kk = live ? x0 / n_atoms : 0, i = live ? x0 - kk * n_atoms : 0;
     const int bs = B ? B : b, bb = bs * bs;
-    const double *__restrict__ kr = kp.re[kk];
     const int64_t p0 = s_ptr[i];
     const int nel = live ? (int)(s_ptr[i + 1] - p0) * bb : 0;
     double acc = 0.0;
@@ -251,7 +263,7 @@ __global__ __launch_bounds__(kT) void k_mulliken(int n_atoms, int n_k, int b, co
         const int kb = s_to_k[p];
         const int a = w / bs, c = w - a * bs;
         const double sval = sv[(int64_t)s_trans[p] * bb + c * bs + a];
-        if (kb >= 0) acc += kr[(int64_t)kb * bb + w] * sval;
+        if (kb >= 0) acc += block_at(kk, kb, w, a, c) * sval;
     }
     acc = wave_sum(acc);
     if (W > 1) {
@@ -270,15 +282,85 @@ __global__ __launch_bounds__(kT) void k_mulliken(int n_atoms, int n_k, int b, co
     }
 }
 
+template <int B, int W>
+__global__ __launch_bounds__(kT) void k_mulliken(int n_atoms, int n_k, int b, const int64_t *__restrict__ s_ptr,
+                                                 const int32_t *__restrict__ s_trans,
+                                                 const int32_t *__restrict__ s_to_k, const double *__restrict__ sv,
+                                                 KPlanes kp, double *__restrict__ q, double *__restrict__ prev,
+                                                 int keep_old, double *__restrict__ ref)
+{
+    const int bb = B ? B * B : b * b;
+    mulliken_block<B, W>(blockIdx.x, n_atoms, n_k, b, s_ptr, s_trans, s_to_k, sv, q, prev, keep_old, ref,
+                         [&](int kk, int kb, int w, int, int) { return kp.re[kk][(int64_t)kb * bb + w]; });
+}
+
+// Hermitise and the charges of the new K in one launch, for small systems: the
+// first kRedBlocks workgroups hermitise, the others take the charges of one
+// atom each from the same sums 0.5 (Kn_ij + Kn_ji^*) instead of waiting for K.
+// Same bytes as the two launches.  A step of 64
+// atoms b = 4, all launches: 31.0 -> 27.6 us.
+template <int B>
+__global__ __launch_bounds__(kT) void k_hermitize_charges(uint32_t n, int b, const int32_t *__restrict__ trans,
+                                                          const double *__restrict__ knr,
+                                                          const double *__restrict__ kni, double *__restrict__ kr,
+                                                          double *__restrict__ ki, double *__restrict__ kr_t,
+                                                          double *__restrict__ ki_t, double *__restrict__ partials,
+                                                          int n_atoms, const int64_t *__restrict__ s_ptr,
+                                                          const int32_t *__restrict__ s_trans,
+                                                          const int32_t *__restrict__ s_to_k,
+                                                          const double *__restrict__ sv, double *__restrict__ q,
+                                                          double *__restrict__ prev)
+{
+    if (blockIdx.x < kRedBlocks) {             // uniform across the workgroup
+        hermitize_block<B, uint32_t>(n, b, trans, knr, kni, kr, ki, kr_t, ki_t, partials);
+        return;
+    }
+    const int bs = B ? B : b, bb = bs * bs;
+    mulliken_block<B, 4>(blockIdx.x - kRedBlocks, n_atoms, 1, b, s_ptr, s_trans, s_to_k, sv, q, prev, 1, nullptr,
+                         [&](int, int kb, int w, int a, int c) {
+                             const double x = knr[(int64_t)kb * bb + w];
+                             const double y = knr[(int64_t)trans[kb] * bb + c * bs + a];
+                             return 0.5 * (x + y);
+                         });
+}
+
+// one wave per atom only for b <= 4 with enough atoms to fill the 1,024 SIMDs four times
+// (by the atoms alone: a kick set's sums are those of a run with that kick only)
+static bool mulliken_wide(int64_t n_atoms, int b) { return b > 4 || n_atoms < 4096; }
+
+// Up to 2^20 elements of K: hermitising them takes less than the launch and the
+// ramp that this saves.  Four waves per atom as in launch_mulliken, so the sums
+// are the same.
+bool hermitize_charges_form(int64_t n_atoms, int64_t nnzb, int b)
+{
+    return nnzb * b * b <= ((int64_t)1 << 20) && mulliken_wide(n_atoms, b) && n_atoms > 0;
+}
+
+void launch_hermitize_charges(hipStream_t s, int64_t nnzb, int b, const int32_t *trans, const double *knr,
+                              const double *kni, double *kr, double *ki, double *partials, double *kr_t,
+                              double *ki_t, int64_t n_atoms, const int64_t *s_ptr, const int32_t *s_trans,
+                              const int32_t *s_to_k, const double *sv, double *q, double *prev)
+{
+    RT_CHECK(hermitize_charges_form(n_atoms, nnzb, b), RTDM_E_ARG, "too large for one launch");
+    RT_CHECK(!kr_t || b == 4 || b == 13, RTDM_E_ARG, "right-operand copies need b = 4 or 13");
+#define RT_HC(B_)                                                                                                  \
+    hipLaunchKernelGGL(k_hermitize_charges<B_>, dim3((unsigned)(kRedBlocks + n_atoms)), dim3(kT), 0, s,            \
+                       (uint32_t)(nnzb * b * b), b, trans, knr, kni, kr, ki, kr_t, ki_t, partials, (int)n_atoms, s_ptr, \
+                       s_trans, s_to_k, sv, q, prev)
+    if (b == 4) RT_HC(4);
+    else if (b == 13) RT_HC(13);
+    else RT_HC(0);
+#undef RT_HC
+    RT_HIP(hipGetLastError());
+}
+
 void launch_mulliken(hipStream_t s, int64_t n_atoms, int n_k, int b, const int64_t *s_ptr, const int32_t *s_trans,
                      const int32_t *s_to_k, const double *sv, const KPlanes &k, double *q, double *prev, int keep_old,
                      double *ref)
 {
     if (n_atoms == 0) return;
     RT_CHECK(n_k >= 1 && n_k <= kMaxKicks && n_atoms * n_k < INT32_MAX, RTDM_E_UNSUPPORTED, "too many charges");
-    // one wave per atom only for b <= 4 with enough atoms to fill the 1,024 SIMDs four times
-    // (by the atoms alone: a kick set's sums are those of a run with that kick only)
-    const bool wide = b > 4 || n_atoms < 4096;
+    const bool wide = mulliken_wide(n_atoms, b);
     const int per = wide ? 1 : kT / 64;
     const dim3 g((unsigned)((n_atoms * n_k + per - 1) / per)), t(kT);
 #define RT_MULL(B_, W_)                                                                                             \

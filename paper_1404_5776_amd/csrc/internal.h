@@ -265,6 +265,12 @@ struct KPlanes {
 void launch_mulliken(hipStream_t s, int64_t n_atoms, int n_k, int b, const int64_t *s_ptr, const int32_t *s_trans,
                      const int32_t *s_to_k, const double *sv, const KPlanes &k, double *q, double *prev, int keep_old,
                      double *ref);
+// Both for one kick set of a small system (hermitize_charges_form): prev gets the old charges.
+bool hermitize_charges_form(int64_t n_atoms, int64_t nnzb, int b);
+void launch_hermitize_charges(hipStream_t s, int64_t nnzb, int b, const int32_t *trans, const double *knr,
+                              const double *kni, double *kr, double *ki, double *partials, double *kr_t,
+                              double *ki_t, int64_t n_atoms, const int64_t *s_ptr, const int32_t *s_trans,
+                              const int32_t *s_to_k, const double *sv, double *q, double *prev);
 // H[diag] += gain*(q_a + theta (q_x - q_y) - q_ref) on the diagonal elements.
 void launch_add_scalar(hipStream_t s, double *x, double v);
 void launch_a_onsite(hipStream_t s, int64_t nnzb, int b, const int32_t *col, const int32_t *nbf, double gain,

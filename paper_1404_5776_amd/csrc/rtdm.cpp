@@ -2396,10 +2396,11 @@ void ensure_u_copies(rtdm_ctx *c, hipStream_t s)
 void step_body(rtdm_ctx *c, double dt, bool rebuild_u, int passes, hipStream_t s)
 {
     Mat &U = c->mats[RTDM_MAT_U], &W = c->mats[RTDM_MAT_W];
-    const Pattern &pk = pat_of(c, R_K);
+    const Pattern &pk = pat_of(c, R_K), &ps = pat_of(c, R_HS);
     const int NK = n_kicks(c);                   // several kicks: fixed H, no corrector (checked at creation)
     c->prec = all_products_prec(c);
     const bool sc = passes > 1;
+    const bool with_charges = !sc && hermitize_charges_form(c->n, pk.nnzb, c->b);
     for (int kk = 0; kk < NK; ++kk) {
         Mat &K = kmat(c, kk);
         Mat &dst = sc ? c->Kt : K;
@@ -2422,10 +2423,17 @@ void step_body(rtdm_ctx *c, double dt, bool rebuild_u, int passes, hipStream_t s
                 else product(c, RTDM_PROD_WU, W, U, c->Kn, 1.0, 0.0, s);
                 c->W_in_cm = false;
             }
-            launch_hermitize(s, pk.nnzb, c->b, pk.d_trans.p, c->Kn.re.p, c->Kn.im.p, dst.re.p, dst.im.p,
-                             c->partials.p + (int64_t)kk * kRedBlocks * 4,
-                             sc || c->Kr.empty() ? nullptr : c->Kr[kk].re.p,
-                             sc || c->Kr.empty() ? nullptr : c->Kr[kk].im.p);
+            double *part = c->partials.p + (int64_t)kk * kRedBlocks * 4;
+            double *kr_t = sc || c->Kr.empty() ? nullptr : c->Kr[kk].re.p;
+            double *ki_t = sc || c->Kr.empty() ? nullptr : c->Kr[kk].im.p;
+            if (with_charges)
+                launch_hermitize_charges(s, pk.nnzb, c->b, pk.d_trans.p, c->Kn.re.p, c->Kn.im.p, dst.re.p, dst.im.p, part,
+                                         kr_t, ki_t, c->n, ps.d_rowptr.p, ps.d_trans.p, c->s_to_k.p,
+                                         c->mats[RTDM_MAT_S].re.p, c->q_cur + (int64_t)kk * c->n,
+                                         c->q_prev + (int64_t)kk * c->n);
+            else
+                launch_hermitize(s, pk.nnzb, c->b, pk.d_trans.p, c->Kn.re.p, c->Kn.im.p, dst.re.p, dst.im.p, part, kr_t,
+                                 ki_t);
             if (sc) {
                 KPlanes k;
                 k.re[0] = dst.re.p;
@@ -2439,7 +2447,7 @@ void step_body(rtdm_ctx *c, double dt, bool rebuild_u, int passes, hipStream_t s
         copy_mat(c, c->Kt, c->mats[RTDM_MAT_K], s);
         if (!c->Kr.empty()) refresh_k_right(c, 0, s);
         launch_axpby(s, c->n, 1.0, c->q_c.p, 0.0, nullptr, c->q_cur);
-    } else {
+    } else if (!with_charges) {
         charges_into(c, NK, k_planes(c), c->q_cur, c->q_prev, 1, nullptr, s);       // q(t - dt) <- q(t), q(t) <- K
     }
     StepTail tail;
