@@ -36,11 +36,11 @@ sys.path.insert(0, ROOT)
 FP64_PEAK_TFLOPS = 78.6      # MI355X dense FP64 (matrix and vector)
 # Identifies the product kernel build whose HBM traffic profiles/traffic.json holds;
 # change it whenever the kernel changes so that a stale figure is not reported.
-KERNEL_TAG = "q4j-b13-nj2seg-xcdchunk128-tile256-v1"
+KERNEL_TAG = "q4p-b13-pairs-real2waves-tile512-v1"
 
 
 # The same for the real b = 4 run kernel on the 32,768-atom lattice at R_K 12.
-KERNEL_TAG_B4 = "b4j-runs16-pipelined-real-v1"
+KERNEL_TAG_B4 = "b4p-runs16-16byte-real-v1"
 
 
 def measured_traffic(dom, name="traffic.json", tag=KERNEL_TAG, workload=None):
@@ -342,7 +342,7 @@ def b4_leg(args):
         dom = max(stats, key=lambda k: stats[k][1])
         n_l, ms, fl = stats[dom]
         ach = fl / n_l / (ms / 1e3 / n_l) / 1e12
-        roof = {"bound": "mfma", "kernel": f"k_spgemm_b4j ({dom} product)", "achieved": ach,
+        roof = {"bound": "mfma", "kernel": f"k_spgemm_b4p ({dom} product)", "achieved": ach,
                 "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": ach / FP64_PEAK_TFLOPS,
                 "avg_launch_ms": ms / n_l, "flops_per_launch": fl / n_l,
                 "traffic": measured_traffic(dom, "traffic_b4.json", KERNEL_TAG_B4, key),
@@ -618,7 +618,7 @@ def main():
     flops_per_step = tot_fl / args.steps
 
     traffic = measured_traffic(dom)
-    roofline = {"bound": "mfma", "kernel": f"k_spgemm_q4j<13, NJ=2> ({dom} product)", "achieved": achieved,
+    roofline = {"bound": "mfma", "kernel": f"k_spgemm_q4p<13> ({dom} product)", "achieved": achieved,
                 "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / FP64_PEAK_TFLOPS,
                 "traffic": traffic, "traffic_unit": "bytes per launch",
                 "avg_launch_ms": avg_s * 1e3, "flops_per_launch": fl / n_l}

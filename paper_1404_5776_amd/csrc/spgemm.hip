@@ -610,9 +610,9 @@ __global__ __launch_bounds__(256, MINW) void k_spgemm_q4j(
 // cores busy 52 %.  The pair layout brings two contraction steps per load:
 // 7 loads per operand block instead of 13.  Lanes 13..15 of a row group read
 // row 12 again: they only feed rows and columns of the tile that are not
-// stored.  The complex products are then held by the matrix cores (91 % busy,
-// 13 of 16 rows and columns of a tile useful); the real one, with half the
-// operations per byte, by operand blocks from beyond the XCD's L2 (512 atoms:
+// stored.  The complex products are then held by the matrix cores (84 % of
+// all cycles busy, 13 of 16 rows and columns of a tile useful); the real one,
+// with half the operations per byte, by operand blocks from beyond the XCD's L2 (512 atoms:
 // its loads alone take 1.10 ms of 1.23, 0.86 if the L2 held them all; its
 // matrix instructions alone 0.95).  Fewer outputs sharing an L2 are better
 // there: three waves per SIMD beat four by 8 % and five by 18 %, and with the
