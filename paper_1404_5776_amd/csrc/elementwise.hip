@@ -925,45 +925,29 @@ void launch_step_begin(hipStream_t s, int64_t *st, double *tt, double t0, double
 
 // ----------------------------------------------------------------- reductions
 
-__global__ __launch_bounds__(kT) void k_red_diff2(int64_t n, const double *__restrict__ x,
-                                                  const double *__restrict__ y,
-                                                  double *__restrict__ partials)
+// End of an inverse iteration: X' = 2 X - X W (into xw), the sums of ||X' - X||^2,
+// ||X'||^2 and the largest change, and X' as an operand of the next products: B = 13
+// left and right pairs, B = 4 transposed blocks (right), B = 0 neither.  Bound:
+// memory; two matrices read and up to three written, where the update, the
+// sums and the re-layouts in passes of their own moved nine and W was laid out
+// in two more.  Inverse of 1,000 atoms b = 13, R_K 16: 22.8 -> 21.8 ms; of
+// 32,768 atoms b = 4, R_K 12: 28.6 -> 25.9 ms.
+template <int B>
+__global__ __launch_bounds__(kT) void k_newton_update(int64_t n, const double *__restrict__ x,
+                                                      double *__restrict__ xw, double *__restrict__ left,
+                                                      double *__restrict__ right, double *__restrict__ partials)
 {
+    constexpr int BB = B * B;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
     for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < n; e += (int64_t)kRedBlocks * kT) {
-        const double d = x[e] - y[e];
-        v[0] += d * d;
-        v[1] += x[e] * x[e];
-        v[3] = fmax(v[3], fabs(d));
-    }
-    write_partials(v, partials);
-}
-
-void launch_red_diff2(hipStream_t s, int64_t n, const double *x, const double *y, double *partials)
-{
-    hipLaunchKernelGGL(k_red_diff2, dim3(kRedBlocks), dim3(kT), 0, s, n, x, y, partials);
-    RT_HIP(hipGetLastError());
-}
-
-// End of an inverse iteration whose products read pair layout (b = 13):
-// X' = 2 X - X W (into xw), its left and right pairs for the next products, and
-// the partial sums of k_red_diff2, in the same order.  Bound: memory; two
-// matrices read and three written where axpby, the sums and both re-layouts
-// moved nine and W was laid out in two more.  Inverse of 1,000 atoms, R_K 16:
-// 22.8 -> 21.8 ms.
-__global__ __launch_bounds__(kT) void k_newton_update13(int64_t n, const double *__restrict__ x,
-                                                        double *__restrict__ xw, double *__restrict__ left,
-                                                        double *__restrict__ right, double *__restrict__ partials)
-{
-    constexpr int B = 13, BB = B * B;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < n; e += (int64_t)kRedBlocks * kT) {
-        const int64_t p = e / BB;
-        const int w = (int)(e - p * BB), r = w / B, c = w - r * B;
         const double old = x[e], now = 2.0 * old - xw[e];
         xw[e] = now;
-        left[p * BB + pair_at(B, r, c)] = now;
-        right[p * BB + pair_at(B, c, r)] = now;
+        if (B) {
+            const int64_t p = e / (B ? BB : 1);
+            const int w = (int)(e - p * BB), r = w / (B ? B : 1), c = w - r * B;
+            if (B == 13) left[p * BB + pair_at(B, r, c)] = now;
+            right[p * BB + (B == 4 ? c * 4 + r : pair_at(B, c, r))] = now;
+        }
         const double d = now - old;
         v[0] += d * d;
         v[1] += now * now;
@@ -972,10 +956,16 @@ __global__ __launch_bounds__(kT) void k_newton_update13(int64_t n, const double 
     write_partials(v, partials);
 }
 
-void launch_newton_update13(hipStream_t s, int64_t n, const double *x, double *xw, double *left, double *right,
-                            double *partials)
+void launch_newton_update(hipStream_t s, int64_t n, int b, const double *x, double *xw, double *left, double *right,
+                          double *partials)
 {
-    hipLaunchKernelGGL(k_newton_update13, dim3(kRedBlocks), dim3(kT), 0, s, n, x, xw, left, right, partials);
+    RT_CHECK(!right || (b == 13 && left) || (b == 4 && !left), RTDM_E_ARG, "operand forms of b = 4 or 13");
+#define RT_NEWTON(B_) \
+    hipLaunchKernelGGL(k_newton_update<B_>, dim3(kRedBlocks), dim3(kT), 0, s, n, x, xw, left, right, partials)
+    if (right && b == 13) RT_NEWTON(13);
+    else if (right) RT_NEWTON(4);
+    else RT_NEWTON(0);
+#undef RT_NEWTON
     RT_HIP(hipGetLastError());
 }
 

@@ -314,10 +314,10 @@ void launch_row_abs_max(hipStream_t s, int64_t n_atoms, int b, const int64_t *s_
 
 // Deterministic reductions: partials[G][4] then finish -> out[4].
 constexpr int kRedBlocks = 512;
-void launch_red_diff2(hipStream_t s, int64_t n, const double *x, const double *y, double *partials);
-// ... with X' = 2 X - xw made in the same pass (in xw, and as left and right pairs; b = 13 blocks)
-void launch_newton_update13(hipStream_t s, int64_t n, const double *x, double *xw, double *left, double *right,
-                            double *partials);
+// [0] sum |X' - X|^2, [1] sum |X'|^2, [3] max |X' - X| of X' = 2 X - xw, formed in xw and, where
+// right is set, as operands (b = 13: left and right pairs; b = 4: right, transposed blocks)
+void launch_newton_update(hipStream_t s, int64_t n, int b, const double *x, double *xw, double *left, double *right,
+                          double *partials);
 void launch_red_unitarity(hipStream_t s, int64_t nnzb_p, int b, const int32_t *p_to_hs,
                           const double *sv, const double *zr, const double *zi, double *partials);
 // sums of |v - I| over a pattern's elements: [0] sum |d|^2, [1] sum |d|, [3] max |d|

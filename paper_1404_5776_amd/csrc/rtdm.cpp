@@ -2079,32 +2079,41 @@ int rtdm_build_inverse(rtdm_ctx *c, void *stream, int *iters, double *residual)
     // Returns 1 converged, 0 diverged, -1 hit the cap.
     auto run = [&](int &k_out, double &r_out) -> int {
         std::vector<double> res;
+        // The products of an iteration read X in the forms the last one's update wrote (Xc, Bp) and
+        // W as the first product writes it: pair layout at b = 13, transposed blocks where both
+        // b = 4 products take those in any case
         const bool pr = cm && c->pairs_real;
+        const bool tr = !cm && c->prec == RTDM_PREC_FP64 && b4_transposed(c, schedule(c, RTDM_PROD_SX)) &&
+                        b4_transposed(c, schedule(c, RTDM_PROD_AT));
         ProductOut w_right;
         if (pr) {
-            // pair layout: the products of an iteration read X in Xc and Bp, laid out by the last
-            // one's update, and W as the first product writes it
             w_right.layout = kOutRight;
             left_copy(c, RTDM_PROD_AT, X, c->Xc, s);
             right_pairs(c, X, s);
+        } else if (tr) {
+            w_right.layout = 1;
+            c->Bp.pat = X.pat;
+            c->Bp.cplx = false;
+            launch_transpose_blocks(s, pp.nnzb, 4, X.re.p, c->Bp.re.p);
         }
         for (int k = 0; k < c->opt.inv_max_iter; ++k) {
+            // W = P_P(S X), P_P(X W), X' = 2 X - X W
             if (pr) {
-                product_cm(c, RTDM_PROD_SX, Sc, c->Bp, c->Wh, 0, 0, 1.0, s, true, w_right);   // W = P_P(S X)
-                product_cm(c, RTDM_PROD_AT, c->Xc, c->Wh, c->Xn, 0, 0, 1.0, s, true);         // P_P(X W)
-                launch_newton_update13(s, ne, X.re.p, c->Xn.re.p, c->Xc.re.p, c->Bp.re.p, c->partials.p);
+                product_cm(c, RTDM_PROD_SX, Sc, c->Bp, c->Wh, 0, 0, 1.0, s, true, w_right);
+                product_cm(c, RTDM_PROD_AT, c->Xc, c->Wh, c->Xn, 0, 0, 1.0, s, true);
+            } else if (tr) {
+                product_key(c, RTDM_PROD_SX, prod_key(c, RTDM_PROD_SX), S, c->Bp, c->Wh, 1.0, 0.0, s, true, w_right);
+                product_key(c, RTDM_PROD_AT, prod_key(c, RTDM_PROD_AT), X, c->Wh, c->Xn, 1.0, 0.0, s, true);
+            } else if (cm) {
+                product_cm(c, RTDM_PROD_SX, Sc, X, c->Wh, 0, 0, 1.0, s, false);
+                left_copy(c, RTDM_PROD_AT, X, c->Xc, s);
+                product_cm(c, RTDM_PROD_AT, c->Xc, c->Wh, c->Xn, 0, 0, 1.0, s, false);
             } else {
-                if (cm) {
-                    product_cm(c, RTDM_PROD_SX, Sc, X, c->Wh, 0, 0, 1.0, s, false);
-                    left_copy(c, RTDM_PROD_AT, X, c->Xc, s);
-                    product_cm(c, RTDM_PROD_AT, c->Xc, c->Wh, c->Xn, 0, 0, 1.0, s, false);
-                } else {
-                    product(c, RTDM_PROD_SX, S, X, c->Wh, 1.0, 0.0, s);
-                    product(c, RTDM_PROD_AT, X, c->Wh, c->Xn, 1.0, 0.0, s);
-                }
-                launch_axpby(s, ne, 2.0, X.re.p, -1.0, c->Xn.re.p, c->Xn.re.p);  // X' = 2X - XW
-                launch_red_diff2(s, ne, c->Xn.re.p, X.re.p, c->partials.p);
+                product(c, RTDM_PROD_SX, S, X, c->Wh, 1.0, 0.0, s);
+                product(c, RTDM_PROD_AT, X, c->Wh, c->Xn, 1.0, 0.0, s);
             }
+            launch_newton_update(s, ne, c->b, X.re.p, c->Xn.re.p, pr ? c->Xc.re.p : nullptr,
+                                 pr || tr ? c->Bp.re.p : nullptr, c->partials.p);
             reduce_finish(c, s, c->hot_sums.p);
             double h[4];
             read_scalars(h, c->hot_sums.p, 4, s);

@@ -17,6 +17,7 @@ import pytest
 
 from oracle import oracle as O
 from paper_1404_5776_amd import rtdm, synth
+from tests._common import TOL, rel
 
 pytestmark = pytest.mark.gpu
 
@@ -134,6 +135,39 @@ def test_inverse_iteration_b13(n):
         ref, _ = O.spgemm(O.BSM(pat, b, X.reshape(n, b, n, b).transpose(0, 2, 1, 3).reshape(n * n, b, b).astype(complex)),
                           O.BSM(pat, b, H.astype(complex)), pat, 1.0, 0, 0)
         assert np.abs(A - ref.val.real).max() <= 4.0 * (N + 2) * np.finfo(float).eps * N * nx
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("b,n", [(4, 30), (4, 4200), (5, 30), (13, 60)])
+def test_inverse_iteration_matches_oracle(b, n):
+    """The truncated iteration against the oracle's: at b = 4 with enough runs
+    W and X' are written as the transposed blocks that the products read, below
+    that (and at other block sizes) by rows.  Same number of iterations; X at
+    the 1e-10 relative Frobenius bar of the parity tests."""
+    print(f"[gpu] inverse b={b} n={n}", flush=True)
+    xyz, (R_HS, R_P, R_K) = _grid(n), (5.0, 6.5, 6.5)
+    pat = O.pattern(xyz, R_HS)
+    rng = np.random.default_rng(43)
+    S = np.zeros((pat.nnzb, b, b))
+    row = np.repeat(np.arange(n), np.diff(pat.row_ptr))
+    S[:] = 0.01 * rng.uniform(-1, 1, size=S.shape)
+    at = {(i, j): p for p, (i, j) in enumerate(zip(row, pat.col))}
+    for (i, j), p in at.items():
+        if i < j:
+            S[at[(j, i)]] = S[p].T
+        elif i == j:
+            S[p] = np.eye(b) + 0.5 * (S[p] + S[p].T)
+    ctx = rtdm.Context(0)
+    try:
+        rtdm.rtdm_set_geometry(ctx.h, xyz, np.full(n, b, dtype=np.int32))
+        rtdm.rtdm_set_ranges(ctx.h, R_HS, R_P, R_K)
+        rtdm.rtdm_upload(ctx.h, "S", S)
+        it, _ = rtdm.rtdm_build_inverse(ctx.h)
+        X = rtdm.rtdm_download(ctx.h, "X", b)
+        ref = O.hotelling(O.BSM(pat, b, S.astype(np.complex128)), O.pattern(xyz, R_P))
+        assert it == ref.iters
+        assert rel(X, ref.X.val) <= TOL
     finally:
         ctx.close()
 
