@@ -509,7 +509,7 @@ int rtdm_multiply(rtdm_ctx *ctx, rtdm_mat C, rtdm_mat A, rtdm_mat B, int op_a, i
 /* For callers that cannot allocate device memory during the call (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * rtdm_multiply with the same arguments and results, whose b = 13
- * column-major operand copies live in a static device array of
+ * operand copies (column-major or pair layout) live in a static device array of
  * 128 MiB per GPU (held from the library's first use on that GPU until the
  * process ends) instead of fresh allocations.  It calls no hipMalloc or
  * hipFree and does not synchronise (it is asynchronous on hip_stream).
