@@ -395,7 +395,9 @@ struct rtdm_ctx {
     bool field_on = false;
     double field_E0[3] = {0.0, 0.0, 0.0}, field_t0 = 0.0, field_sigma = 1.0;
     DBuf<double> d_centre, d_centre_all;   // centres of the groups, of all atoms
-    DBuf<double> f16_max;       // operand maxima of the FP16 split products
+    // operand maxima of the FP16 split products and their partials (of their own:
+    // those of a kick's Hermitisation wait in `partials` while the next kick's products run)
+    DBuf<double> f16_max, f16_part;
     bool timing = false;
     std::vector<hipEvent_t> events;
     std::vector<TRec> recs;
@@ -759,11 +761,11 @@ void product_key(rtdm_ctx *c, int prod, const std::tuple<int, int, int, int, int
         const Mat *ops[2] = {&A, &B};
         for (int k = 0; k < 2; ++k) {
             const int64_t ne = elems(c, *ops[k]);
-            launch_red_max(s, ne, ops[k]->re.p, c->partials.p);
-            launch_red_finish(s, c->partials.p, c->f16_max.p + 8 * k);
+            launch_red_max(s, ne, ops[k]->re.p, c->f16_part.p);
+            launch_red_finish(s, c->f16_part.p, c->f16_max.p + 8 * k);
             if (ops[k]->cplx) {
-                launch_red_max(s, ne, ops[k]->im.p, c->partials.p);
-                launch_red_finish(s, c->partials.p, c->f16_max.p + 8 * k + 4);
+                launch_red_max(s, ne, ops[k]->im.p, c->f16_part.p);
+                launch_red_finish(s, c->f16_part.p, c->f16_max.p + 8 * k + 4);
             } else {
                 launch_fill(s, 4, 0.0, c->f16_max.p + 8 * k + 4);
             }
@@ -897,8 +899,8 @@ void product_cm(rtdm_ctx *c, int prod, const Mat &Acm, const Mat &B, Mat &C, int
         // max |x| of both (real) operands for the power-of-two scales
         const Mat *ops[2] = {&Acm, &B};
         for (int k = 0; k < 2; ++k) {
-            launch_red_max(s, elems(c, *ops[k]), ops[k]->re.p, c->partials.p);
-            launch_red_finish(s, c->partials.p, c->f16_max.p + 8 * k);
+            launch_red_max(s, elems(c, *ops[k]), ops[k]->re.p, c->f16_part.p);
+            launch_red_finish(s, c->f16_part.p, c->f16_max.p + 8 * k);
             launch_fill(s, 4, 0.0, c->f16_max.p + 8 * k + 4);
         }
         a.maxabs = c->f16_max.p;
@@ -1521,6 +1523,7 @@ int rtdm_create(rtdm_ctx **out, int hip_device, const rtdm_options *opt)
     c->hot_sums.alloc(4);
     c->obs_tmp.alloc(8);
     c->f16_max.alloc(16);
+    c->f16_part.alloc((size_t)kRedBlocks * 4);
     c->zero.alloc(256);
     RT_HIP(hipMemset(c->zero.p, 0, c->zero.bytes()));
     *out = c;
