@@ -1322,7 +1322,45 @@ void upload_planes(rtdm_ctx *c, int m, const double *re, const double *im, hipSt
     RT_HIP(hipStreamSynchronize(s));
 }
 
-void after_upload(rtdm_ctx *c, int m)
+// K of kick kk as a right operand (Kr).
+void refresh_k_right(rtdm_ctx *c, int kk, hipStream_t s)
+{
+    const Mat &K = kmat(c, kk);
+    Mat &R = c->Kr[kk];
+    if (c->b == 13) {
+        pack_planes(c, K, R, kPackRight, s);
+        return;
+    }
+    const int64_t nb = c->pats[K.pat]->nnzb;
+    launch_transpose_blocks(s, nb, 4, K.re.p, R.re.p);
+    launch_transpose_blocks(s, nb, 4, K.im.p, R.im.p);
+}
+
+// Kr before the steps of a call (outside a captured step of the context's own):
+// each step's Hermitisation keeps it.  Steps recorded into a caller's graph
+// start from whatever K holds at a replay, so they always make it, and what is
+// recorded says nothing about Kr now.
+void ensure_k_right(rtdm_ctx *c, hipStream_t s)
+{
+    if (c->Kr.empty()) return;
+    const bool recorded = is_capturing(s);
+    if (c->K_right_valid && !recorded) return;
+    for (int k = 0; k < n_kicks(c); ++k) refresh_k_right(c, k, s);
+    if (!recorded) c->K_right_valid = true;
+}
+
+// K was written on s.  A write recorded into a caller's graph happens at every
+// replay: Kr is then made behind it in the graph.
+void k_written(rtdm_ctx *c, hipStream_t s)
+{
+    if (c->Kr.empty()) return;
+    if (!is_capturing(s)) c->K_right_valid = false;
+    else
+        for (int k = 0; k < n_kicks(c); ++k) refresh_k_right(c, k, s);
+}
+
+// Host state after slot m was written on s.
+void after_upload(rtdm_ctx *c, int m, hipStream_t s)
 {
     c->uploaded[m] = true;
     switch (m) {
@@ -1337,7 +1375,6 @@ void after_upload(rtdm_ctx *c, int m)
     case RTDM_MAT_H0: c->U_valid = false; c->A0_valid = false; break;
     case RTDM_MAT_X: c->X_valid = true; c->U_valid = false; c->Xc_valid = false; c->A0_valid = false; break;
     case RTDM_MAT_K:
-        c->K_right_valid = false;
         for (int k = 1; k < n_kicks(c); ++k) {   // every kick starts from the uploaded K
             const int64_t ne = elems(c, c->mats[RTDM_MAT_K]);
             RT_HIP(hipMemcpy(c->Kx[k - 1].re.p, c->mats[RTDM_MAT_K].re.p, ne * sizeof(double),
@@ -1345,6 +1382,7 @@ void after_upload(rtdm_ctx *c, int m)
             RT_HIP(hipMemcpy(c->Kx[k - 1].im.p, c->mats[RTDM_MAT_K].im.p, ne * sizeof(double),
                              hipMemcpyDeviceToDevice));
         }
+        k_written(c, s);
         c->charges_valid = false;
         c->q_ref_valid = false;
         c->obs_reset_pending = true;
@@ -1909,7 +1947,7 @@ int rtdm_upload(rtdm_ctx *c, rtdm_mat mat, const void *data, int is_complex, int
             RT_CHECK(h[3] == 0.0, RTDM_E_UNSUPPORTED, "complex data for a real matrix slot");
         }
     }
-    after_upload(c, mat);
+    after_upload(c, mat, s);
     API_END(c)
 }
 
@@ -1943,7 +1981,7 @@ int rtdm_upload_coo(rtdm_ctx *c, rtdm_mat mat, int64_t nnzb, const int32_t *rows
     }
     pad_identity(c, mat, P, re);
     upload_planes(c, mat, re.data(), M.cplx ? im.data() : nullptr, (hipStream_t)stream);
-    after_upload(c, mat);
+    after_upload(c, mat, (hipStream_t)stream);
     API_END(c)
 }
 
@@ -2010,11 +2048,12 @@ void kick_k(rtdm_ctx *c, int k, const double *kappa, bool groups, hipStream_t s)
                 right ? c->Kr[k].re.p : nullptr, right ? c->Kr[k].im.p : nullptr);
 }
 
-// Host state after a kick on every K: a new trace and charge history.
-void after_kick(rtdm_ctx *c)
+// Host state after a kick on every K (and its right-operand copy) on s: a new
+// trace and charge history.
+void after_kick(rtdm_ctx *c, hipStream_t s)
 {
     c->charges_valid = false;
-    c->K_right_valid = !c->Kr.empty();
+    if (!is_capturing(s)) c->K_right_valid = !c->Kr.empty();
     c->obs_rows = 0;
     c->obs_reset_pending = true;
     c->t_now = 0.0;
@@ -2039,7 +2078,7 @@ int rtdm_apply_kick(rtdm_ctx *c, const double kappa[3], void *stream)
         ensure_charges(c, s);
     }
     for (int k = 0; k < n_kicks(c); ++k) kick_k(c, k, kappa, false, s);
-    after_kick(c);
+    after_kick(c, s);
     API_END(c)
 }
 
@@ -2358,28 +2397,6 @@ void build_u(rtdm_ctx *c, double dt, bool corr, hipStream_t s)
         launch_conj_move(s, pp.nnzb, c->b, pp.d_trans.p, U.re.p, U.im.p, c->Uh.re.p, c->Uh.im.p);
     }
     c->u_copies_valid = true;
-}
-
-// K of every kick as a right operand (Kr) after an upload or a kick, made
-// before the steps, outside any capture: each step's Hermitisation keeps them.
-void refresh_k_right(rtdm_ctx *c, int kk, hipStream_t s)
-{
-    const Mat &K = kmat(c, kk);
-    Mat &R = c->Kr[kk];
-    if (c->b == 13) {
-        pack_planes(c, K, R, kPackRight, s);
-        return;
-    }
-    const int64_t nb = c->pats[K.pat]->nnzb;
-    launch_transpose_blocks(s, nb, 4, K.re.p, R.re.p);
-    launch_transpose_blocks(s, nb, 4, K.im.p, R.im.p);
-}
-
-void ensure_k_right(rtdm_ctx *c, hipStream_t s)
-{
-    if (c->K_right_valid || c->Kr.empty()) return;
-    for (int k = 0; k < n_kicks(c); ++k) refresh_k_right(c, k, s);
-    c->K_right_valid = true;
 }
 
 // After an upload of U: its column-major copy (b = 13) and U^dagger (b = 4),
@@ -2877,7 +2894,7 @@ int rtdm_ground_state(rtdm_ctx *c, double n_occ, double tol, int max_iter, void 
     launch_fill(s, elems(c, c->Kn), 0.0, c->Kn.im.p);
     launch_hermitize(s, pk.nnzb, c->b, pk.d_trans.p, c->Kn.re.p, c->Kn.im.p, K.re.p, K.im.p, c->partials.p);
     RT_HIP(hipStreamSynchronize(s));
-    after_upload(c, RTDM_MAT_K);
+    after_upload(c, RTDM_MAT_K, s);
     API_END(c)
 }
 
@@ -3136,7 +3153,7 @@ int rtdm_apply_kick_groups(rtdm_ctx *c, const double *kappa, void *stream)
         for (int k = 0; k < n_kicks(c); ++k) kick_k(c, k, nullptr, true, s);
         RT_HIP(hipStreamSynchronize(s));
     }
-    after_kick(c);
+    after_kick(c, s);
     API_END(c)
 }
 
@@ -3154,7 +3171,7 @@ int rtdm_apply_kicks(rtdm_ctx *c, const double *kappa, void *stream)
         ensure_charges(c, s);
     }
     for (int k = 0; k < n_kicks(c); ++k) kick_k(c, k, kappa + 3 * k, false, s);
-    after_kick(c);
+    after_kick(c, s);
     API_END(c)
 }
 
@@ -3512,7 +3529,7 @@ void multiply(rtdm_ctx *c, rtdm_mat Cm, rtdm_mat Am, rtdm_mat Bm, int op_a, int 
         throw;
     }
     c->prec = RTDM_PREC_FP64;
-    after_upload(c, Cm);
+    after_upload(c, Cm, s);
 }
 
 }  // namespace
