@@ -190,6 +190,9 @@ int rtdm_default_options(rtdm_options *opt);
  *   RTDM_RUN_CPLX   the same for the complex ones (1 to 4; default 2)
  *   RTDM_RUN_B4     b = 4 products over row runs of 16 outputs (16, default) or per-output lists (1)
  *   RTDM_ROW_TILE   rows per output tile of the b = 13 processing order (default 512)
+ *   RTDM_RUN_REFUSE product kinds whose row runs rtdm_set_ranges leaves out, as where they do not fit
+ *                   (bits 1 << RTDM_PROD_*, bit 7: W U^dagger over a stored U^dagger; default 0; read when
+ *                   the products are scheduled)
  * A run length outside these values fails with RTDM_E_ARG. */
 int rtdm_create(rtdm_ctx **out, int hip_device, const rtdm_options *opt);
 

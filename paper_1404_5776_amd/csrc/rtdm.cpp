@@ -23,6 +23,7 @@
 #include <new>
 #include <numeric>
 #include <random>
+#include <set>
 #include <tuple>
 #include <vector>
 
@@ -143,8 +144,11 @@ struct Sched {
     DBuf<int64_t> off;
     DBuf<int2> trip;
     DBuf<int32_t> order;   // processing order of the output blocks (row tiles, then columns)
-    // row runs of this schedule (SpgemmArgs::ch_*), by run length
+    // row runs of this schedule (SpgemmArgs::ch_*), by run length, and the lengths
+    // that were asked for: runs that did not fit are not tried again, since which
+    // buffers and copies exist was decided with them
     std::map<int, std::unique_ptr<Runs>> runs;
+    std::set<int> asked;
 };
 
 // Processing order of the output blocks of pattern C: rows are cut into
@@ -189,6 +193,14 @@ std::vector<int32_t> run_order(const Runs &R, int tile_i)
 }
 
 constexpr size_t kRunReserve = size_t(16) << 30;   // device memory row runs leave free
+
+// Product kinds whose row runs RTDM_RUN_REFUSE leaves out (bit RTDM_PROD_COUNT:
+// W U^dagger over a stored U^dagger).
+bool run_refused(int kind)
+{
+    const char *e = getenv("RTDM_RUN_REFUSE");
+    return e && ((strtol(e, nullptr, 0) >> kind) & 1);
+}
 
 // Row runs of schedule S for op(A) = A: the outputs of each row of C cut into
 // runs of nj consecutive columns; the entries of a run are the k of row i of
@@ -624,9 +636,10 @@ Sched &schedule_key(rtdm_ctx *c, int prod, const std::tuple<int, int, int, int, 
                                                                                       : c->run_real)
                    : c->b == 4 ? c->run_b4
                                : 1;
+    const int kind = prod == RTDM_PROD_WU && std::get<4>(key) == 0 ? RTDM_PROD_COUNT : prod;
     auto runs_for = [&](Sched &S) {
         // (every kind is scheduled when the ranges are set, so this never runs during a capture)
-        if (nj > 1)
+        if (nj > 1 && S.asked.insert(nj).second && !run_refused(kind))
             build_runs(S, *c->pats[std::get<0>(key)], *c->pats[std::get<1>(key)], *c->pats[std::get<2>(key)],
                        std::get<4>(key), nj, c->b == 4, c->row_tile);
     };
@@ -676,12 +689,12 @@ bool b4_takes_transposed(rtdm_ctx *c, const Sched &S)
     return r != S.runs.end() && r->second->nch > 0;
 }
 
-// ... and do so for an operand by rows too, transposed into Bp first: where the
-// runs fill the chip.  In the split form of small systems that launch would
+// ... and do so for an operand by rows too, transposed into Bp first: where there
+// is a Bp and the runs fill the chip.  In the split form of small systems that launch would
 // cost more than the narrower loads of k_spgemm_b4js.
 bool b4_transposed(rtdm_ctx *c, const Sched &S)
 {
-    return b4_takes_transposed(c, S) && !b4_split_form(S.runs.find(16)->second->nch);
+    return c->Bp.re.p && b4_takes_transposed(c, S) && !b4_split_form(S.runs.find(16)->second->nch);
 }
 
 // Whether schedule S has segmented row runs of 2 (b = 13).
@@ -1649,6 +1662,7 @@ int rtdm_set_ranges(rtdm_ctx *c, double R_hs, double R_p, double R_k)
              RTDM_E_ARG, "bad ranges");
     if (R_p <= 0) R_p = std::max(R_hs, R_k);
     RT_HIP(hipDeviceSynchronize());
+    c->prec = RTDM_PREC_FP64;   // (a step that failed may have left another)
     c->scheds.clear();
     c->pats.clear();
     const double r[3] = {R_hs, R_p, R_k};
@@ -1776,8 +1790,13 @@ int rtdm_set_ranges(rtdm_ctx *c, double R_hs, double R_p, double R_k)
         c->Uh_on = c->b == 4 && c->run_b4 == 16 && all_products_prec(c) == RTDM_PREC_FP64 && r != uk.runs.end() &&
                    r->second->nch > 0 && !b4_split_form(r->second->nch);
         if (c->Uh_on) {
+            // (its own lists: their runs may not fit where those of U K do)
+            const bool shared = c->scheds.count(wuh_key(c)) > 0;
+            c->Uh_on = b4_takes_transposed(c, schedule_key(c, RTDM_PROD_WU, wuh_key(c)));
+            if (!c->Uh_on && !shared) c->scheds.erase(wuh_key(c));
+        }
+        if (c->Uh_on) {
             alloc_mat(c, c->Uh, R_P, true);
-            schedule_key(c, RTDM_PROD_WU, wuh_key(c));
         } else {
             c->Uh.re.release();
             c->Uh.im.release();

@@ -1558,8 +1558,10 @@ bool b4_split_form(int64_t nch) { return nch < kB4SplitRuns; }
 //
 // b4p_entries: the pairs of entries e0, e0 + stride, ... below e1 into the sums
 // rr, ii, ri, ir of the wave's 16 outputs; PIPE: the next pair's operands are
-// requested before this pair's products (else only its indices).
-template <bool AC, bool BC, bool PIPE>
+// requested before this pair's products (else only its indices).  BROWS: B's
+// blocks by rows, two 8-byte loads in place of one of 16, for products without a
+// buffer to transpose B into; the same products in the same order.
+template <bool AC, bool BC, bool PIPE, bool BROWS = false>
 __device__ inline void b4p_entries(int64_t e0, int64_t e1, int stride, const int32_t *__restrict__ ea,
                                    const int32_t *__restrict__ eb, const double *__restrict__ ar,
                                    const double *__restrict__ ai, const double *__restrict__ br,
@@ -1570,6 +1572,10 @@ __device__ inline void b4p_entries(int64_t e0, int64_t e1, int stride, const int
     const int g = (lane >> 2) & 3, r = lane & 3, q = lane >> 4;
     const int lo = r * 4 + 2 * (q & 1), eo = q >> 1, slot = g * 4 + r;
     typedef double d2 __attribute__((ext_vector_type(2)));
+    const int lob = BROWS ? 8 * (q & 1) + r : lo;
+    auto pair_of = [&](const double *m, int64_t p) {
+        return BROWS ? d2{m[p], m[p + 4]} : *reinterpret_cast<const d2 *>(m + p);
+    };
     struct Ops {
         d2 xar, xai, xbr[4], xbi[4];
     };
@@ -1600,9 +1606,9 @@ __device__ inline void b4p_entries(int64_t e0, int64_t e1, int stride, const int
         for (int jj = 0; jj < 4; ++jj) {
             o.xbr[jj] = o.xbi[jj] = d2{0, 0};
             if (kb[jj] >= 0) {
-                const int64_t pb = (int64_t)kb[jj] * 16 + lo;
-                o.xbr[jj] = *reinterpret_cast<const d2 *>(br + pb);
-                if (BC) o.xbi[jj] = *reinterpret_cast<const d2 *>(bi + pb);
+                const int64_t pb = (int64_t)kb[jj] * 16 + lob;
+                o.xbr[jj] = pair_of(br, pb);
+                if (BC) o.xbi[jj] = pair_of(bi, pb);
             }
         }
     };
@@ -1664,7 +1670,7 @@ __device__ inline void b4p_store(int p, double rr, double ii, double ri, double 
 // sums per complex output: adding the imaginary products to the real ones' sum
 // as they come doubled its roundings (error of a product against 64-bit
 // arithmetic 6.0e-16 -> 8.5e-16) for 0 - 4 % of the time.
-template <bool AC, bool BC, int CJB, int OUT>
+template <bool AC, bool BC, int CJB, int OUT, bool BROWS = false>
 __global__ __launch_bounds__(256) void k_spgemm_b4p(
     int64_t nch, const int64_t *__restrict__ off, const int32_t *__restrict__ ea,
     const int32_t *__restrict__ eb, const int32_t *__restrict__ cout, const double *__restrict__ ar,
@@ -1676,7 +1682,7 @@ __global__ __launch_bounds__(256) void k_spgemm_b4p(
     if (c >= nch) return;                      // uniform across the wave
     const int g = (threadIdx.x >> 2) & 3;
     double rr[4] = {0, 0, 0, 0}, ii[4] = {0, 0, 0, 0}, ri[4] = {0, 0, 0, 0}, ir[4] = {0, 0, 0, 0};
-    b4p_entries<AC, BC, !(AC && BC)>(off[c], off[c + 1], 2, ea, eb, ar, ai, br, bi, rr, ii, ri, ir);
+    b4p_entries<AC, BC, !(AC && BC), BROWS>(off[c], off[c + 1], 2, ea, eb, ar, ai, br, bi, rr, ii, ri, ir);
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {
         const int p = cout[c * 16 + 4 * jj + g];
@@ -1730,6 +1736,15 @@ __global__ __launch_bounds__(64 * W) void k_spgemm_b4ps(
                         AC ? sum[NACC - 1] : 0.0, cr, ci, alr, ali, u, u_sign, u_store);
 }
 
+template <bool AC, bool BC, int CJB, int OUT, bool BROWS = false>
+static void launch_b4p_runs(hipStream_t s, const SpgemmArgs &a, const SumInto &u)
+{
+    const int remap = xcd_chunk_for((a.nch + 3) / 4);
+    hipLaunchKernelGGL((k_spgemm_b4p<AC, BC, CJB, OUT, BROWS>), dim3(xcd_grid((a.nch + 3) / 4, remap)), dim3(256), 0, s,
+                       a.nch, a.ch_off, a.ch_a, a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re,
+                       a.alpha_im, u.p, u.sign, u.store, remap);
+}
+
 template <bool AC, bool BC, int CJB, int OUT>
 static void launch_b4p_as(hipStream_t s, const SpgemmArgs &a, const SumInto &u)
 {
@@ -1746,10 +1761,7 @@ static void launch_b4p_as(hipStream_t s, const SpgemmArgs &a, const SumInto &u)
         return;
     }
 #undef RT_B4PS
-    const int remap = xcd_chunk_for((a.nch + 3) / 4);
-    hipLaunchKernelGGL((k_spgemm_b4p<AC, BC, CJB, OUT>), dim3(xcd_grid((a.nch + 3) / 4, remap)), dim3(256), 0, s, a.nch,
-                       a.ch_off, a.ch_a, a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re,
-                       a.alpha_im, u.p, u.sign, u.store, remap);
+    launch_b4p_runs<AC, BC, CJB, OUT>(s, a, u);
 }
 
 // b = 4 FP64 product over runs of 16 from a row-major left operand and a right
@@ -1846,7 +1858,10 @@ static void launch_b4j(hipStream_t s, const SpgemmArgs &a)
                            a.alpha_im);
         return;
     }
-    RT_CHECK(a.nch < kB4SplitRuns, RTDM_E_ARG, "larger b = 4 products take transposed right operands");
+    if (a.nch >= kB4SplitRuns) {
+        launch_b4p_runs<AC, BC, OB, 0, OB == 0>(s, a, SumInto());
+        return;
+    }
     hipLaunchKernelGGL((k_spgemm_b4js<AC, BC, OB, 4>), dim3((unsigned)a.nch), dim3(256), 0, s, a.nch, a.ch_off, a.ch_a,
                        a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re, a.alpha_im);
 }
