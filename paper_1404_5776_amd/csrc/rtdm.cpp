@@ -337,11 +337,10 @@ struct rtdm_ctx {
     // left pairs of the left operand of a product without a kept copy (ETRS and
     // Magnus propagators at b = 13: U E1, the commutator, M T_k); allocated with them
     Mat Lp;
-    // Bp and Lp serve one product at a time.  Their last user: a product of rtdm_multiply
-    // (relay_ev recorded behind it) or a step, on relay_stream (take_relay)
-    hipEvent_t relay_ev = nullptr;
-    hipStream_t relay_stream = nullptr;
-    bool relay_used = false, relay_recorded = false;
+    // Bp and Lp serve one call at a time (Turn): the event behind the last one and its stream
+    hipEvent_t turn_ev = nullptr;
+    hipStream_t turn_stream = nullptr;
+    bool turn_left = false;
     // FP32 copies for the reduced-precision Taylor terms (b = 13)
     DBuf<float> Ac32, tau32[2], zero32;
     DBuf<double> scratch;       // block inverse scratch and staging
@@ -961,32 +960,37 @@ bool is_capturing(hipStream_t s)
     return st != hipStreamCaptureStatusNone;
 }
 
-// Makes s the stream that uses Bp and Lp next.  Products that share no slot may be
-// issued on several streams of the caller's without an order of their own; what
-// shares these two buffers still has to run one after the other.  A step leaves
-// no event behind (it would cost each call a barrier, and the case is rare), so a
-// change of stream after one waits for the device.  Within a capture the caller's
-// graph has the order.
-void take_relay(rtdm_ctx *c, hipStream_t s)
-{
-    if (!c->Bp.re.p) return;
-    if (c->relay_used && c->relay_stream != s && !is_capturing(s)) {
-        if (c->relay_recorded) RT_HIP(hipStreamWaitEvent(s, c->relay_ev, 0));
-        else RT_HIP(hipDeviceSynchronize());
+// The turn of a call on stream s at Bp and Lp.  Calls that share no slot may be
+// issued on several streams without an order of the caller's, and what shares
+// these two buffers still has to run one after the other: a call waits (on the
+// GPU) for the event behind the last one and leaves its own.  Always, whatever
+// the streams' handles say (the handle of a destroyed stream comes back), but
+// for two that live as long as the context.  Calls recorded into a caller's graph
+// neither wait nor leave anything: their turn comes at the replays.
+struct Turn {
+    rtdm_ctx *c;
+    hipStream_t s;
+    bool on;
+    Turn(rtdm_ctx *ctx, hipStream_t stream) : c(ctx), s(stream), on(ctx->Bp.re.p && !is_capturing(stream))
+    {
+        if (!on) return;
+        if (!c->turn_ev) RT_HIP(hipEventCreateWithFlags(&c->turn_ev, hipEventDisableTiming));
+        const bool same = c->turn_stream == s && (!s || s == c->gstream);
+        if (c->turn_left && !same) RT_HIP(hipStreamWaitEvent(s, c->turn_ev, 0));
     }
-    c->relay_used = true;
-    c->relay_recorded = false;
-    c->relay_stream = s;
-}
-
-// Behind a product issued by the caller on s: what a later user on another stream waits for.
-void leave_relay(rtdm_ctx *c, hipStream_t s)
-{
-    if (!c->Bp.re.p || is_capturing(s)) return;
-    if (!c->relay_ev) RT_HIP(hipEventCreateWithFlags(&c->relay_ev, hipEventDisableTiming));
-    RT_HIP(hipEventRecord(c->relay_ev, s));
-    c->relay_recorded = true;
-}
+    Turn(const Turn &) = delete;
+    Turn &operator=(const Turn &) = delete;
+    ~Turn()
+    {
+        if (!on) return;
+        c->turn_stream = s;
+        c->turn_left = hipEventRecord(c->turn_ev, s) == hipSuccess;
+        if (!c->turn_left) {                   // no event to wait for: wait here
+            (void)hipGetLastError();
+            (void)hipDeviceSynchronize();
+        }
+    }
+};
 
 // The right pairs of M, in Bp (valid until the next call).
 const Mat &right_pairs(rtdm_ctx *c, const Mat &M, hipStream_t s)
@@ -1598,7 +1602,7 @@ int rtdm_destroy(rtdm_ctx *c)
     (void)hipDeviceSynchronize();
     for (auto e : c->events) (void)hipEventDestroy(e);
     drop_graph(c);
-    if (c->relay_ev) (void)hipEventDestroy(c->relay_ev);
+    if (c->turn_ev) (void)hipEventDestroy(c->turn_ev);
     if (c->gstream) (void)hipStreamDestroy(c->gstream);
     delete c;
     return RTDM_OK;
@@ -2108,7 +2112,7 @@ int rtdm_build_inverse(rtdm_ctx *c, void *stream, int *iters, double *residual)
     set_device(c);
     require(c->ranges_set && c->uploaded[RTDM_MAT_S], "upload S first");
     hipStream_t s = (hipStream_t)stream;
-    take_relay(c, s);
+    const Turn turn(c, s);
     Mat &S = c->mats[RTDM_MAT_S];
     Mat &X = c->mats[RTDM_MAT_X];
     const Pattern &ps = pat_of(c, R_HS), &pp = pat_of(c, R_P);
@@ -2653,7 +2657,7 @@ int rtdm_step(rtdm_ctx *c, double dt, int64_t n_steps, void *stream)
         if (!c->gstream) RT_HIP(hipStreamCreate(&c->gstream));
         s = c->gstream;
     }
-    take_relay(c, s);
+    const Turn turn(c, s);
     StepCall sc = step_begin(c, dt, n_steps, s);
     eager_prefix(sc);
     if (sc.k < n_steps && c->opt.use_graph) {
@@ -2782,9 +2786,10 @@ int rtdm_batch_step(rtdm_batch *bt, double dt, int64_t n_steps, void *stream)
     }
     std::vector<StepCall> calls;
     calls.reserve(bt->ctx.size());
+    std::vector<std::unique_ptr<Turn>> turns;
     for (auto *c : bt->ctx) {
         DevMemScope scope(&c->mem);
-        take_relay(c, s);
+        turns.push_back(std::make_unique<Turn>(c, s));
         calls.push_back(step_begin(c, dt, n_steps, s));
         eager_prefix(calls.back());
     }
@@ -2855,7 +2860,7 @@ int rtdm_ground_state(rtdm_ctx *c, double n_occ, double tol, int max_iter, void 
     RT_CHECK(n_occ > 0 && std::isfinite(n_occ) && tol > 0 && max_iter >= 1 && max_iter <= 64, RTDM_E_ARG,
              "bad ground-state arguments (max_iter 1..64)");
     hipStream_t s = (hipStream_t)stream;
-    take_relay(c, s);
+    const Turn turn(c, s);
     c->prec = RTDM_PREC_FP64;
     Mat &A = c->mats[RTDM_MAT_A], &X = c->mats[RTDM_MAT_X], &K = c->mats[RTDM_MAT_K];
     const Pattern &pp = pat_of(c, R_P), &pk = pat_of(c, R_K);
@@ -3247,7 +3252,7 @@ int rtdm_autotune(rtdm_ctx *c, void *stream, int *wpb_out, int *tile_out)
     set_device(c);
     require(c->ranges_set, "set_ranges first");
     hipStream_t s = (hipStream_t)stream;
-    take_relay(c, s);
+    const Turn turn(c, s);
     if (c->b == 13) {
         const int wpbs[3] = {4, 8, 16}, tiles[3] = {64, 256, 1024};
         // events and the context's timing flag are restored however the sweep ends
@@ -3396,7 +3401,7 @@ int rtdm_unitarity(rtdm_ctx *c, double out[3], void *stream)
     require(c->ranges_set && c->U_valid && c->uploaded[RTDM_MAT_S], "no propagator yet");
     RT_CHECK(out, RTDM_E_ARG, "null output");
     hipStream_t s = (hipStream_t)stream;
-    take_relay(c, s);
+    const Turn turn(c, s);
     unitarity_sums(c, s);
     double u[4], s2[4];
     read_scalars(u, c->unit_sums.p, 4, s);
@@ -3415,7 +3420,7 @@ int rtdm_inverse_error(rtdm_ctx *c, double out[3], void *stream)
     require(c->ranges_set && c->X_valid && c->uploaded[RTDM_MAT_S], "build or upload the inverse first");
     RT_CHECK(out, RTDM_E_ARG, "null output");
     hipStream_t s = (hipStream_t)stream;
-    take_relay(c, s);
+    const Turn turn(c, s);
     product(c, RTDM_PROD_XH, c->mats[RTDM_MAT_X], c->mats[RTDM_MAT_S], c->Wh, 1.0, 0.0, s);
     const Pattern &pp = pat_of(c, R_P);
     launch_red_minus_identity(s, pp.nnzb, c->b, pp.d_rowof.p, pp.d_col.p, c->Wh.re.p, c->partials.p);
@@ -3472,7 +3477,7 @@ void multiply(rtdm_ctx *c, rtdm_mat Cm, rtdm_mat Am, rtdm_mat Bm, int op_a, int 
              "no schedule of this product kind yet (the allocation-free call builds none): call rtdm_multiply once");
     const bool cres = A.cplx || B.cplx || ali != 0.0;
     RT_CHECK(C.cplx || !cres, RTDM_E_UNSUPPORTED, "complex result for a real matrix slot");
-    take_relay(c, s);
+    const Turn turn(c, s);
     c->prec = all_products_prec(c);
     try {
         // The step products of the b = 13 column-major path run exactly as in a
@@ -3542,7 +3547,6 @@ void multiply(rtdm_ctx *c, rtdm_mat Cm, rtdm_mat Am, rtdm_mat Bm, int op_a, int 
         } else {
             product(c, prod, A, B, C, alr, ali, s);
         }
-        leave_relay(c, s);
     } catch (...) {
         c->prec = RTDM_PREC_FP64;
         throw;
