@@ -3312,6 +3312,7 @@ int rtdm_observables(rtdm_ctx *c, double out[6], void *stream)
     require(c->ranges_set && c->uploaded[RTDM_MAT_K] && c->uploaded[RTDM_MAT_S], "upload S and K first");
     RT_CHECK(out, RTDM_E_ARG, "null output");
     hipStream_t s = (hipStream_t)stream;
+    const Turn turn(c, s);
     ensure_charges(c, s);
     launch_observables(s, c->n, c->d_xyz.p, c->d_centre_all.p, qcur(c, c->kick_sel),
                        c->herm_valid ? herm_of(c, c->kick_sel) : nullptr, c->t_now, c->obs_tmp.p);

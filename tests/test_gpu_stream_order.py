@@ -182,3 +182,29 @@ def test_a_recorded_product_leaves_the_turn_of_those_in_flight():
     assert np.array_equal(rtdm.rtdm_download(ctx.h, "W", s.b), W)
     del graphs
     ctx.close()
+
+
+@pytest.mark.parametrize("call", ["observables", "unitarity", "inverse_error"])
+def test_a_measurement_behind_a_product_on_another_stream_waits_its_turn(call):
+    """The products of the measures lay their right operand out where the one
+    in flight does; the calls return host values, so the other is complete."""
+    import torch
+    s, ctx = _b4()
+    measure = getattr(rtdm, "rtdm_" + call)
+    want = measure(ctx.h)
+    rtdm.rtdm_multiply(ctx.h, "A", "X", "H0")
+    A = rtdm.rtdm_download(ctx.h, "A", s.b)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    print(f"[gpu] {call} behind a product on another stream", flush=True)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(streams[0]):
+        torch.cuda._sleep(HOLD)
+    rtdm.rtdm_multiply(ctx.h, "A", "X", "H0", 0, 0, 1.0, streams[0])
+    done = torch.cuda.Event()
+    done.record(streams[0])
+    assert not done.query()
+    got = measure(ctx.h, streams[1])
+    assert done.query()
+    assert np.array_equal(got, want)
+    assert np.array_equal(rtdm.rtdm_download(ctx.h, "A", s.b), A)
+    ctx.close()
