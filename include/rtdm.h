@@ -36,6 +36,12 @@
  * - `hip_stream` is a hipStream_t (NULL = the device's null stream).  Calls
  *   that take a stream enqueue work on it and return without waiting, except
  *   those documented as synchronising (they return host scalars).
+ * - Calls of one context on several streams: the library orders (on the GPU)
+ *   what shares its internal operand buffers; calls that share a slot are the
+ *   caller's to order.  A call recorded into a caller's graph is outside that
+ *   order at its replays: a recorded rtdm_multiply or rtdm_multiply_noalloc uses
+ *   no operand buffer of the context's; replays of any other call have to be
+ *   ordered by the caller against every other call on the context.
  */
 #ifndef RTDM_H
 #define RTDM_H

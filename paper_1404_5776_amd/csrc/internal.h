@@ -190,8 +190,9 @@ struct SumInto {
 // layout (launch_pack_pairs): op(B) from right pairs, or with conj_b from the
 // left pairs of the conjugate-transposed matrix; the output row-major, as left
 // pairs or (real products) as right pairs, a.cr null when only the sum u is wanted.
+// rows: both operands (and the output) by rows instead, bit for bit the same product.
 enum { kOutRows = 0, kOutLeft = 1, kOutRight = 2 };
-void launch_spgemm_pairs(hipStream_t s, const SpgemmArgs &a, int conj_b, int out, const SumInto &u);
+void launch_spgemm_pairs(hipStream_t s, const SpgemmArgs &a, int conj_b, int out, const SumInto &u, bool rows = false);
 // tau = dt A as a right operand (b = 4: transposed blocks, b = 13: right pairs),
 // u_im = -dt A and, at b = 13, ap = the left pairs of A.
 void launch_taylor_start(hipStream_t s, int64_t nblocks, int b, double dt, const double *a, double *tau, double *u_im,

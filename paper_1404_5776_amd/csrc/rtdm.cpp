@@ -341,6 +341,9 @@ struct rtdm_ctx {
     hipEvent_t turn_ev = nullptr;
     hipStream_t turn_stream = nullptr;
     bool turn_left = false;
+    // the product being issued is recorded into a caller's graph, whose replays take no
+    // turn: its operands are read by rows, without Bp and Lp
+    bool recorded = false;
     // FP32 copies for the reduced-precision Taylor terms (b = 13)
     DBuf<float> Ac32, tau32[2], zero32;
     DBuf<double> scratch;       // block inverse scratch and staging
@@ -689,11 +692,11 @@ bool b4_takes_transposed(rtdm_ctx *c, const Sched &S)
 }
 
 // ... and do so for an operand by rows too, transposed into Bp first: where there
-// is a Bp and the runs fill the chip.  In the split form of small systems that launch would
+// is a Bp to use and the runs fill the chip.  In the split form of small systems that launch would
 // cost more than the narrower loads of k_spgemm_b4js.
 bool b4_transposed(rtdm_ctx *c, const Sched &S)
 {
-    return c->Bp.re.p && b4_takes_transposed(c, S) && !b4_split_form(S.runs.find(16)->second->nch);
+    return c->Bp.re.p && !c->recorded && b4_takes_transposed(c, S) && !b4_split_form(S.runs.find(16)->second->nch);
 }
 
 // Whether schedule S has segmented row runs of 2 (b = 13).
@@ -725,6 +728,7 @@ hipEvent_t event_at(rtdm_ctx *c, size_t k)
 // Where a product's output goes beside (or in place of) row-major blocks of C.
 struct ProductOut {
     int layout = 0;     // b = 13 pair products: kOutRows / kOutLeft / kOutRight; b_t products: 1 transposed blocks
+    bool rows = false;  // b = 13 pair products: operands by rows (launch_spgemm_pairs)
     SumInto u;          // fused sum
     bool drop = false;  // C itself is not wanted
 };
@@ -818,6 +822,10 @@ void product_key(rtdm_ctx *c, int prod, const std::tuple<int, int, int, int, int
     const bool b4t = a.op_a == 0 && (b4_transposed(c, S) || ((b_t || a.op_b) && b4_takes_transposed(c, S)));
     RT_CHECK(!b_t || b4t, RTDM_E_ARG, "transposed right operand outside the b = 4 run kernel");
     auto go = [&]() {
+        if (pairs && c->recorded) {
+            launch_spgemm_pairs(s, a, 0, kOutRows, SumInto(), true);
+            return;
+        }
         if (pairs) {
             pack_planes(c, A, c->Lp, kPackLeft, s);
             pack_planes(c, B, c->Bp, kPackRight, s);
@@ -921,7 +929,7 @@ void product_cm(rtdm_ctx *c, int prod, const Mat &Acm, const Mat &B, Mat &C, int
         if (split) launch_spgemm_cm_split(s, a);
         else if (pairs) {
             if (out.drop) a.cr = nullptr;
-            launch_spgemm_pairs(s, a, conj_b, out.layout ? out.layout : out_cm ? kOutLeft : kOutRows, out.u);
+            launch_spgemm_pairs(s, a, conj_b, out.layout ? out.layout : out_cm ? kOutLeft : kOutRows, out.u, out.rows);
         }
         else launch_spgemm_cm(s, a, conj_b, out_cm);
     };
@@ -3479,8 +3487,18 @@ void multiply(rtdm_ctx *c, rtdm_mat Cm, rtdm_mat Am, rtdm_mat Bm, int op_a, int 
     const bool cres = A.cplx || B.cplx || ali != 0.0;
     RT_CHECK(C.cplx || !cres, RTDM_E_UNSUPPORTED, "complex result for a real matrix slot");
     const Turn turn(c, s);
-    c->prec = all_products_prec(c);
-    try {
+    struct Issue {             // arithmetic and operand form of the product, whatever ends it
+        rtdm_ctx *c;
+        ~Issue()
+        {
+            c->prec = RTDM_PREC_FP64;
+            c->recorded = false;
+        }
+    };
+    {
+        const Issue issue{c};
+        c->prec = all_products_prec(c);
+        c->recorded = is_capturing(s);
         // The step products of the b = 13 column-major path run exactly as in a
         // step: column-major copies of A (and of B when it is conjugate-
         // transposed), the row-run kernels, and U K written column-major.
@@ -3525,6 +3543,13 @@ void multiply(rtdm_ctx *c, rtdm_mat Cm, rtdm_mat Am, rtdm_mat Bm, int op_a, int 
             }
             // pair layout as in a step (right pairs in the context's own Bp)
             const bool pairs = (A.cplx || B.cplx ? c->pairs_cplx : c->pairs_real) && runs_of_2(c, prod);
+            if (pairs && c->recorded && scratch && !op_b) {
+                ProductOut by_rows;
+                by_rows.rows = true;
+                product_cm(c, prod, A, B, C, 0, 0, alr, s, true, by_rows);
+                after_upload(c, Cm, s);
+                return;
+            }
             auto left = [&](const Mat &M, Mat &out) {
                 if (pairs) pack_planes(c, M, out, kPackLeft, s);
                 else transpose_into(c, M, out, s);
@@ -3548,11 +3573,7 @@ void multiply(rtdm_ctx *c, rtdm_mat Cm, rtdm_mat Am, rtdm_mat Bm, int op_a, int 
         } else {
             product(c, prod, A, B, C, alr, ali, s);
         }
-    } catch (...) {
-        c->prec = RTDM_PREC_FP64;
-        throw;
     }
-    c->prec = RTDM_PREC_FP64;
     after_upload(c, Cm, s);
 }
 

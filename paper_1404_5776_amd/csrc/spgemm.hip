@@ -622,10 +622,13 @@ __global__ __launch_bounds__(256, MINW) void k_spgemm_q4j(
 // Complex products have no registers to load a group ahead.
 // OUT: 0 row-major output, 1 left pairs, 2 right pairs.  u (real products,
 // nullable): u = u_sign * output (u_store) or u += u_sign * output, row-major:
-// the Taylor sum, whose own pass would read the term again.
+// the Taylor sum, whose own pass would read the term again.  ROWS: both operands
+// by rows as they are stored, for products recorded into a caller's graph, which
+// may use no buffer of the context's: A in the same 16-byte loads, 104 bytes from
+// lane to lane, B in two 8-byte ones; the same products in the same order.
 typedef double pd2 __attribute__((ext_vector_type(2), aligned(8)));
 typedef __attribute__((address_space(1))) const pd2 gpd2;
-template <int B, bool AC, bool BC, int CJB, int OUT>
+template <int B, bool AC, bool BC, int CJB, int OUT, bool ROWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AC || BC ? 3 : 2, AC || BC ? 3 : 2))) void k_spgemm_q4p(
     int64_t nch, const int64_t *__restrict__ off, const int32_t *__restrict__ ea,
     const int32_t *__restrict__ eb, const int32_t *__restrict__ cout,
@@ -635,6 +638,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AC || BC ? 
     const int32_t *__restrict__ seg, double *__restrict__ u, double u_sign, int u_store)
 {
     static_assert(B >= 5 && B <= 15 && (B & 1), "odd block sizes");
+    static_assert(!ROWS || !CJB, "a conjugated right operand has its pair layout");
     constexpr int BB = B * B, NJ = 2;
     const int lane = threadIdx.x & 63;
     const int64_t w = xcd_block((nch + 3) / 4, remap) * 4 + (threadIdx.x >> 6);
@@ -643,6 +647,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AC || BC ? 
     const int q = lane >> 4, r = min(lane & 15, B - 1);
     const int64_t e0 = off[c];
     const int ne = (int)(off[c + 1] - e0);
+    // a lane's first pair in an operand block, its pair h, and its last, unpaired element
+    const int fa = ROWS ? r * B : 2 * r, fb = ROWS ? r : 2 * r;
+    auto last_left = [&]() { return ROWS ? B - 1 : B * (B - 1) - r; };
+    auto last_right = [&]() { return ROWS ? B * (B - 1) : B * (B - 1) - r; };
+    auto left_pair = [](const gdouble *p, int h) { return *(const gpd2 *)(p + (ROWS ? 2 : 2 * B) * h); };
+    auto right_pair = [](const gdouble *p, int h) {
+        return ROWS ? pd2{p[2 * B * h], p[2 * B * h + B]} : *(const gpd2 *)(p + 2 * B * h);
+    };
     typedef Mfma16<double>::acc_t acc_t;
     // four sums per complex output (two, with the sign folded into an operand, were
     // no faster at three waves and doubled the roundings of the real part: K of the
@@ -673,24 +685,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AC || BC ? 
             double ya = 0, yb[NJ] = {0, 0};
             auto point = [&](int g) {
                 const bool on = g + q < ge;
-                pa = on ? (const gdouble *)(ar + (int64_t)na * BB + 2 * r) : gz;
+                pa = on ? (const gdouble *)(ar + (int64_t)na * BB + fa) : gz;
 #pragma unroll
                 for (int t = 0; t < NJ; ++t)
-                    if ((ACT >> t) & 1) pb[t] = on ? (const gdouble *)(br + (int64_t)nb[t] * BB + 2 * r) : gz;
+                    if ((ACT >> t) & 1) pb[t] = on ? (const gdouble *)(br + (int64_t)nb[t] * BB + fb) : gz;
                 fetch(min(g + 4, ge));
             };
             auto load = [&](int h) {
-                xa[h] = *(const gpd2 *)(pa + 2 * B * h);
+                xa[h] = left_pair(pa, h);
 #pragma unroll
                 for (int t = 0; t < NJ; ++t)
-                    if ((ACT >> t) & 1) xb[t][h] = *(const gpd2 *)(pb[t] + 2 * B * h);
+                    if ((ACT >> t) & 1) xb[t][h] = right_pair(pb[t], h);
             };
             auto load_last = [&]() {                   // the unpaired contraction index
-                const int o = B * (B - 1) - r;
-                ya = pa[o];
+                ya = pa[last_left()];
 #pragma unroll
                 for (int t = 0; t < NJ; ++t)
-                    if ((ACT >> t) & 1) yb[t] = pb[t][o];
+                    if ((ACT >> t) & 1) yb[t] = pb[t][last_right()];
             };
             auto mma = [&](double va, double v0, double v1) {
                 if (ACT & 1) rr[0] = Mfma16<double>::step(va, v0, rr[0]);
@@ -728,13 +739,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AC || BC ? 
 #pragma unroll
             for (int t = 0; t < NJ; ++t) pb[t] = pbi[t] = gz;
             if (g + q < ge) {
-                const int64_t oa = (int64_t)na * BB + 2 * r;
+                const int64_t oa = (int64_t)na * BB + fa;
                 pa = (const gdouble *)(ar + oa);
                 if (AC) pai = (const gdouble *)(ai + oa);
 #pragma unroll
                 for (int t = 0; t < NJ; ++t) {
                     if (!((ACT >> t) & 1)) continue;
-                    const int64_t ob = (int64_t)nb[t] * BB + 2 * r;   // present: segmented entries
+                    const int64_t ob = (int64_t)nb[t] * BB + fb;   // present: segmented entries
                     pb[t] = (const gdouble *)(br + ob);
                     if (BC) pbi[t] = (const gdouble *)(bi + ob);
                 }
@@ -752,15 +763,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AC || BC ? 
             };
 #pragma unroll
             for (int h = 0; h < B / 2; ++h) {
-                const pd2 xa = *(const gpd2 *)(pa + 2 * B * h);
-                const pd2 xai = AC ? *(const gpd2 *)(pai + 2 * B * h) : pd2{0, 0};
+                const pd2 xa = left_pair(pa, h);
+                const pd2 xai = AC ? left_pair(pai, h) : pd2{0, 0};
                 pd2 xb[NJ], xbi[NJ];
 #pragma unroll
                 for (int t = 0; t < NJ; ++t) {
                     xb[t] = xbi[t] = pd2{0, 0};
                     if (!((ACT >> t) & 1)) continue;
-                    xb[t] = *(const gpd2 *)(pb[t] + 2 * B * h);
-                    if (BC) xbi[t] = *(const gpd2 *)(pbi[t] + 2 * B * h);
+                    xb[t] = right_pair(pb[t], h);
+                    if (BC) xbi[t] = right_pair(pbi[t], h);
                 }
                 const double b0[NJ] = {xb[0].x, xb[1].x}, b0i[NJ] = {xbi[0].x, xbi[1].x};
                 const double b1[NJ] = {xb[0].y, xb[1].y}, b1i[NJ] = {xbi[0].y, xbi[1].y};
@@ -768,14 +779,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AC || BC ? 
                 mma(xa.y, xai.y, b1, b1i);
             }
             {
-                const int o = B * (B - 1) - r;         // the last, unpaired contraction index
-                const double xa = pa[o], xai = AC ? pai[o] : 0.0;
+                const int oa = last_left(), ob = last_right();
+                const double xa = pa[oa], xai = AC ? pai[oa] : 0.0;
                 double xb[NJ] = {0, 0}, xbi[NJ] = {0, 0};
 #pragma unroll
                 for (int t = 0; t < NJ; ++t) {
                     if (!((ACT >> t) & 1)) continue;
-                    xb[t] = pb[t][o];
-                    if (BC) xbi[t] = pbi[t][o];
+                    xb[t] = pb[t][ob];
+                    if (BC) xbi[t] = pbi[t][ob];
                 }
                 mma(xa, xai, xb, xbi);
             }
@@ -877,26 +888,36 @@ void launch_taylor_start(hipStream_t s, int64_t nblocks, int b, double dt, const
     RT_HIP(hipGetLastError());
 }
 
-template <bool AC, bool BC, int CJB, int OUT>
+template <bool AC, bool BC, int CJB, int OUT, bool ROWS = false>
 static void launch_q4p(hipStream_t s, const SpgemmArgs &a, const SumInto &u)
 {
     const int remap = xcd_chunk_for((a.nch + 3) / 4);
     const unsigned grid = xcd_grid((a.nch + 3) / 4, remap);
-    hipLaunchKernelGGL((k_spgemm_q4p<13, AC, BC, CJB, OUT>), dim3(grid), dim3(256), 0, s, a.nch,
+    hipLaunchKernelGGL((k_spgemm_q4p<13, AC, BC, CJB, OUT, ROWS>), dim3(grid), dim3(256), 0, s, a.nch,
                        a.ch_off, a.ch_a, a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re,
                        a.alpha_im, a.zero, a.ch_order, remap, a.ch_seg, u.p, u.sign, u.store);
 }
 
 // Products over row runs of 2 with both operands in pair layout (b = 13, FP64;
 // a conjugated right operand U^dagger is the left pairs of U): conj_b, out
-// (kOut*; right pairs and the fused sum u for real products only).
-void launch_spgemm_pairs(hipStream_t s, const SpgemmArgs &a, int conj_b, int out, const SumInto &u)
+// (kOut*; right pairs and the fused sum u for real products only).  rows: both
+// operands and the output by rows.
+void launch_spgemm_pairs(hipStream_t s, const SpgemmArgs &a, int conj_b, int out, const SumInto &u, bool rows)
 {
     RT_CHECK(a.b == 13 && a.precision == RTDM_PREC_FP64 && a.nj == 2 && a.nch > 0 && a.ch_seg && a.zero, RTDM_E_ARG,
              "pair-layout products need b = 13, FP64 and segmented runs of 2");
     const bool ac = a.ai != nullptr, bc = a.bi != nullptr;
     const bool real = !ac && !bc && !a.ci;
     RT_CHECK(real || (!u.p && out != kOutRight), RTDM_E_ARG, "right pairs and the fused sum need real operands");
+    if (rows) {
+        RT_CHECK(!conj_b && out == kOutRows && !u.p, RTDM_E_ARG, "operands by rows give a plain product by rows");
+        if (ac && bc) launch_q4p<true, true, 0, 0, true>(s, a, u);
+        else if (ac) launch_q4p<true, false, 0, 0, true>(s, a, u);
+        else if (bc) launch_q4p<false, true, 0, 0, true>(s, a, u);
+        else launch_q4p<false, false, 0, 0, true>(s, a, u);
+        RT_HIP(hipGetLastError());
+        return;
+    }
     if (real && out == kOutRight) {
         launch_q4p<false, false, 0, 2>(s, a, u);
         RT_HIP(hipGetLastError());

@@ -152,3 +152,47 @@ def test_a_kick_that_was_only_recorded_has_not_been_applied(b):
     assert np.array_equal(got, want), float(np.abs(got - want).max())
     del g
     ctx.close()
+
+
+# (recorded product, product issued eagerly on another stream meanwhile): they share no slot that either writes
+PRODUCTS = [(("A", "X", "H0", 0, 0, 1.0), ("W", "U", "K", 0, 0, 1.0)),
+            (("W", "U", "K", 0, 0, 1.0), ("A", "X", "H0", 0, 0, 1.0)),
+            (("K", "W", "U", 0, 1, 1.0), ("A", "X", "H0", 0, 0, 1.0)),
+            (("U", "A", "X", 0, 0, 0.5j), ("W", "X", "K", 0, 0, 1.0)),
+            (("W", "X", "K", 0, 0, 0.5j), ("U", "A", "X", 0, 0, 1.0))]
+
+
+@pytest.mark.parametrize("which", ["b4", "b13", "b13_etrs"])
+@pytest.mark.parametrize("job,other", PRODUCTS)
+def test_a_replayed_product_shares_no_buffer_with_eager_ones(which, job, other):
+    """Replays of a recorded product overlap eager products on another stream:
+    every result is bit for bit that of the call by itself.  Recorded products
+    read their operands by rows instead of laying them out in a buffer of the
+    context's (b = 4: row runs that fill the chip; b = 13: pair layout)."""
+    import torch
+    s = (synth.diamond_lattice((6, 6, 6), 4, 10.0, 12.0, seed=83, h_model="fixed") if which == "b4" else
+         synth.diamond_lattice((2, 2, 2), 13, 10.0, 16.0, seed=84, k0="local", h_model="fixed"))
+    ctx = gpu_context(s, h_model="fixed", propagator="etrs" if which == "b13_etrs" else "em")
+    rtdm.rtdm_build_inverse(ctx.h)
+    rtdm.rtdm_step(ctx.h, DT, 1)
+    W = rtdm.rtdm_download(ctx.h, "W", s.b)
+    rtdm.rtdm_upload(ctx.h, "W", W)
+    want = []
+    for j in (job, other):
+        rtdm.rtdm_multiply(ctx.h, *j)
+        want.append(rtdm.rtdm_download(ctx.h, j[0], s.b))
+    a, c = torch.cuda.Stream(), torch.cuda.Stream()
+    g = _record(a, lambda: rtdm.rtdm_multiply_noalloc(ctx.h, *job, a))
+    for rep in range(4):
+        print(f"[gpu] {which} recorded {job[0]} = {job[1]} {job[2]} rep={rep}", flush=True)
+        for j in (job, other):
+            rtdm.rtdm_upload(ctx.h, j[0], np.zeros_like(want[0] if j is job else want[1]))
+        torch.cuda.synchronize()
+        for _ in range(4):
+            with torch.cuda.stream(a):
+                g.replay()
+            rtdm.rtdm_multiply(ctx.h, *other, c)
+        torch.cuda.synchronize()
+        for j, w in zip((job, other), want):
+            assert np.array_equal(rtdm.rtdm_download(ctx.h, j[0], s.b), w), (j, rep)
+    ctx.close()
