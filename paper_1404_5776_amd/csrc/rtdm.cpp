@@ -1853,8 +1853,9 @@ int rtdm_set_ranges(rtdm_ctx *c, double R_hs, double R_p, double R_k)
             if (c->pairs_cplx || b4) c->Bp.im.alloc(ne);
         }
     }
-    // the unitarity product too when steps check it, so that rtdm_step allocates nothing
-    if (c->opt.unit_check_every > 0 && !unitarity_by_rows(c)) schedule(c, RTDM_PROD_UV);
+    // the unitarity product too when steps check it, so that rtdm_step allocates nothing and the
+    // allocation-free product takes the kind (the check itself may run by rows, without these lists)
+    if (c->opt.unit_check_every > 0) schedule(c, RTDM_PROD_UV);
     RT_HIP(hipDeviceSynchronize());
     API_END(c)
 }
