@@ -45,6 +45,10 @@ struct DevMem {
     void *(*ext_alloc)(size_t bytes, void *user) = nullptr;   // the caller's allocator, if set
     void (*ext_free)(void *ptr, void *user) = nullptr;
     void *ext_user = nullptr;
+    // what the context can do without, given back before an allocation fails (null: nothing);
+    // true where it held anything
+    bool (*reclaim)(void *user) = nullptr;
+    void *reclaim_user = nullptr;
 };
 // The context of the API call in progress on this thread (null outside calls).
 extern thread_local DevMem *g_devmem;
@@ -361,7 +365,7 @@ void launch_mlp_delta(hipStream_t s, int64_t n, int out, const int32_t *idx, con
                       const float *hid, const __half *w2, float *dy, float *dh, float *sqerr);
 void launch_mlp_grad(hipStream_t s, int64_t n, int in, int out, const int32_t *idx, const float *x,
                      const float *hid, const float *dy, const float *dh, float *part, float *grad);
-// chunks of samples whose partial gradients launch_mlp_grad writes to part (one: none)
+// chunks of samples whose partial gradients launch_mlp_grad writes to part (null or one chunk: none)
 int64_t mlp_grad_chunks(int64_t n);
 void launch_adam(hipStream_t s, int64_t np, int64_t nw1, int64_t nb1, int64_t nw2, const float *grad, float *w,
                  float *m, float *v, float lr, double beta1, double beta2, float eps, int step, __half *w1h,

@@ -244,9 +244,9 @@ void launch_mlp_grad(hipStream_t s, int64_t n, int in, int out, const int32_t *i
                      const float *hid, const float *dy, const float *dh, float *part, float *grad)
 {
     const int64_t np = (int64_t)kMlpT * in + kMlpT + (int64_t)out * kMlpT + out;
-    const int64_t chunks = mlp_grad_chunks(n);
+    const int64_t chunk = part ? grad_chunk(n) : n, chunks = part ? mlp_grad_chunks(n) : 1;
     hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)((np + 255) / 256), (unsigned)std::max<int64_t>(chunks, 1)), dim3(256),
-                       0, s, n, grad_chunk(n), in, out, idx, x, hid, dy, dh, chunks > 1 ? part : grad);
+                       0, s, n, chunk, in, out, idx, x, hid, dy, dh, chunks > 1 ? part : grad);
     if (chunks > 1)
         hipLaunchKernelGGL(k_mlp_grad_sum, dim3((unsigned)((np + 63) / 64)), dim3(64), 0, s, np, (int)chunks, part,
                            grad);

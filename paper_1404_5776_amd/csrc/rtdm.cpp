@@ -37,6 +37,7 @@ void *devmem_alloc(DBufBase *b, size_t bytes)
 {
     DevMem *m = g_devmem;
     void *p = nullptr;
+    auto reclaimed = [&]() { return m && m->reclaim && m->reclaim(m->reclaim_user); };
     if (m && m->base) {
         const size_t off = devmem_align(m->used);
         RT_CHECK(off + bytes <= m->cap, RTDM_E_OOM,
@@ -46,6 +47,7 @@ void *devmem_alloc(DBufBase *b, size_t bytes)
         b->in_ws = true;
     } else if (m && m->ext_alloc) {
         p = m->ext_alloc(bytes, m->ext_user);
+        if (!p && reclaimed()) p = m->ext_alloc(bytes, m->ext_user);
         RT_CHECK(p, RTDM_E_OOM, "the caller's allocator refused " + std::to_string(bytes) + " bytes");
         RT_CHECK((reinterpret_cast<uintptr_t>(p) & 255) == 0, RTDM_E_ARG,
                  "the caller's allocator returned memory that is not 256-byte aligned");
@@ -53,6 +55,10 @@ void *devmem_alloc(DBufBase *b, size_t bytes)
         b->ext = true;
     } else {
         hipError_t e = hipMalloc(&p, bytes);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            if (reclaimed()) e = hipMalloc(&p, bytes);
+        }
         if (e != hipSuccess) {
             (void)hipGetLastError();
             throw Error(RTDM_E_OOM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
@@ -329,11 +335,12 @@ struct rtdm_ctx {
     bool Xc_valid = false, W_in_cm = false;
     // b = 13 products with FP64 products over segmented runs of 2 read their
     // operands in pair layout (launch_spgemm_pairs): Xc, Sc (pairs_real), Uc and
-    // Wc (pairs_cplx) then hold left pairs, Ap those of A (Ac stays the
-    // column-major copy the reduced-precision Taylor terms read), Bp the right
+    // Wc (pairs_cplx) then hold left pairs, and so does Ac, or Ap where the
+    // reduced-precision Taylor terms read a column-major Ac; Bp holds the right
     // pairs of the right operand of the product being issued
     bool pairs_real = false, pairs_cplx = false;
     Mat Ap, Bp;
+    bool setting_forms = false;   // set_forms is allocating (nothing to reclaim)
     // left pairs of the left operand of a product without a kept copy (ETRS and
     // Magnus propagators at b = 13: U E1, the commutator, M T_k); allocated with them
     Mat Lp;
@@ -1000,6 +1007,9 @@ struct Turn {
     }
 };
 
+// The left pairs of A (pairs_real).
+Mat &a_left(rtdm_ctx *c) { return c->Ap.re.p ? c->Ap : c->Ac; }
+
 // The right pairs of M, in Bp (valid until the next call).
 const Mat &right_pairs(rtdm_ctx *c, const Mat &M, hipStream_t s)
 {
@@ -1123,7 +1133,7 @@ void build_propagator(rtdm_ctx *c, double dt, hipStream_t s)
         launch_add_identity(s, c->n, c->b, pat_of(c, R_P).d_diag.p, 1.0, U.re.p);
     }
     if (fused) {
-        launch_taylor_start(s, pat_of(c, R_P).nnzb, c->b, dt, A.re.p, c->tau[0].re.p, U.im.p, c->Ap.re.p);
+        launch_taylor_start(s, pat_of(c, R_P).nnzb, c->b, dt, A.re.p, c->tau[0].re.p, U.im.p, a_left(c).re.p);
     } else {
         launch_fill(s, ne, 0.0, U.im.p);
         if (p >= 1) {
@@ -1229,7 +1239,7 @@ void build_propagator(rtdm_ctx *c, double dt, hipStream_t s)
             out.u.store = k == 2 && re_stored;
             out.drop = k == p;
             Mat &src = c->tau[cur], &dst = c->tau[1 - cur];
-            if (c->b == 13) product_cm(c, RTDM_PROD_AT, c->Ap, src, dst, 0, 0, dt / k, s, true, out);
+            if (c->b == 13) product_cm(c, RTDM_PROD_AT, a_left(c), src, dst, 0, 0, dt / k, s, true, out);
             else product_key(c, RTDM_PROD_AT, prod_key(c, RTDM_PROD_AT), A, src, dst, dt / k, 0.0, s, true, out);
             if (out.u.store) launch_add_identity(s, c->n, c->b, pat_of(c, R_P).d_diag.p, 1.0, U.re.p);
         } else {
@@ -1242,7 +1252,7 @@ void build_propagator(rtdm_ctx *c, double dt, hipStream_t s)
                                   (c->opt.precision == RTDM_PREC_BF16X3_TAYLOR ||
                                    c->opt.precision == RTDM_PREC_FP16X2_TAYLOR);
             if (c->pairs_real && c->prec == RTDM_PREC_FP64)
-                product_cm(c, RTDM_PROD_AT, c->Ap, right_copy(c, RTDM_PROD_AT, src, s), dst, 0, 0, dt / k, s, true);
+                product_cm(c, RTDM_PROD_AT, a_left(c), right_copy(c, RTDM_PROD_AT, src, s), dst, 0, 0, dt / k, s, true);
             else if (use_cm(c) || split_cm) product_cm(c, RTDM_PROD_AT, c->Ac, src, dst, 0, 0, dt / k, s, false);
             else product(c, RTDM_PROD_AT, A, src, dst, dt / k, 0.0, s);
             c->prec = saved;
@@ -1299,6 +1309,106 @@ void drop_graph(rtdm_ctx *c)
     c->graph = nullptr;
     c->gexec_multi = nullptr;
     c->graph_multi = nullptr;
+}
+
+// Gives the operand forms back (Kr, Bp, Lp, Ap): the products then read K, right
+// operands and, at b = 13, column-major copies as without pair layout.
+void drop_forms(rtdm_ctx *c)
+{
+    drop_graph(c);
+    if (c->W_in_cm && c->pairs_cplx) {
+        pack_planes(c, c->Wc, c->mats[RTDM_MAT_W], kUnpackLeft, nullptr);
+        RT_HIP(hipDeviceSynchronize());
+        c->W_in_cm = false;
+    }
+    c->pairs_real = c->pairs_cplx = false;
+    c->Ap.re.release();
+    c->Bp.re.release();
+    c->Bp.im.release();
+    c->Lp.re.release();
+    c->Lp.im.release();
+    c->Kr.clear();
+    c->K_right_valid = c->Xc_valid = c->u_copies_valid = false;
+}
+
+// Allocates the operand forms that the products' row runs can read: pair layout
+// where every product of a kind runs over segmented runs of 2 (b = 13, FP64), Kr
+// where U K runs over runs of 16 (b = 4), Bp where such runs fill the chip.
+// Optional like the runs themselves: without room for all of them, and for
+// kRunReserve beyond, there are none.
+void set_forms(rtdm_ctx *c)
+{
+    const bool fp64 = all_products_prec(c) == RTDM_PREC_FP64, fp64_13 = c->b == 13 && fp64;
+    auto runs2 = [&](int prod) { return runs_of_2(c, prod); };
+    const bool real = fp64_13 && c->run_real == 2 && runs2(RTDM_PROD_XH) && runs2(RTDM_PROD_AT) && runs2(RTDM_PROD_SX);
+    const bool cplx = fp64_13 && c->run_cplx == 2 && runs2(RTDM_PROD_UK) && runs2(RTDM_PROD_WU);
+    const bool k_right = cplx || (fp64 && b4_takes_transposed(c, schedule(c, RTDM_PROD_UK)));
+    bool b4 = false;         // some b = 4 products over enough runs for transposed right operands
+    if (c->b == 4 && c->run_b4 == 16)
+        for (auto &kv : c->scheds) {
+            auto r = kv.second->runs.find(16);
+            b4 |= r != kv.second->runs.end() && r->second->nch > 0 && !b4_split_form(r->second->nch);
+        }
+    const int64_t bb = (int64_t)c->b * c->b, np = pat_of(c, R_P).nnzb * bb, nk = pat_of(c, R_K).nnzb * bb;
+    const int64_t nb = std::max({pat_of(c, R_HS).nnzb * bb, np, nk});
+    const bool a_both = real && c->opt.precision != RTDM_PREC_FP64, left = real && cplx && c->opt.propagator != RTDM_PROP_EM;
+    const int right = (real || cplx || b4) + (cplx || b4);   // planes of Bp
+    const double need = 8.0 * ((k_right ? 2.0 * n_kicks(c) * nk : 0.0) + (a_both ? np : 0) + (left ? 2.0 * np : 0.0) +
+                               (double)right * nb);
+    if (need == 0.0) return;
+    size_t free_b = 0, total_b = 0;
+    RT_HIP(hipMemGetInfo(&free_b, &total_b));
+    if (need + (double)kRunReserve > (double)free_b) return;
+    c->setting_forms = true;
+    try {
+        if (k_right) {
+            c->Kr.resize(n_kicks(c));
+            for (auto &Km : c->Kr) alloc_like(c, Km, c->mats[RTDM_MAT_K]);
+        }
+        if (a_both) {
+            c->Ap.pat = c->range_pat[R_P];
+            c->Ap.re.alloc(np);
+        }
+        if (left) {
+            c->Lp.re.alloc(np);
+            c->Lp.im.alloc(np);
+        }
+        if (right >= 1) c->Bp.re.alloc(nb);
+        if (right >= 2) c->Bp.im.alloc(nb);
+    } catch (const Error &e) {
+        c->setting_forms = false;
+        drop_forms(c);
+        if (e.code != RTDM_E_OOM) throw;
+        return;
+    }
+    c->setting_forms = false;
+    c->pairs_real = real;
+    c->pairs_cplx = cplx;
+}
+
+// The buffers that drop_forms gives back.
+std::vector<DBufBase *> form_bufs(rtdm_ctx *c)
+{
+    std::vector<DBufBase *> list;
+    for (Mat *m : {&c->Ap, &c->Bp, &c->Lp})
+        for (auto *b : {&m->re, &m->im})
+            if (b->p) list.push_back(b);
+    for (auto &m : c->Kr)
+        for (auto *b : {&m.re, &m.im})
+            if (b->p) list.push_back(b);
+    return list;
+}
+
+// DevMem::reclaim of a context: its operand forms.  Products look at what there is
+// when they are issued, so this may happen at any allocation (none is made while a
+// product is being issued or a step recorded).
+bool reclaim_forms(void *user)
+{
+    rtdm_ctx *c = static_cast<rtdm_ctx *>(user);
+    if (c->setting_forms || form_bufs(c).empty()) return false;
+    RT_HIP(hipDeviceSynchronize());
+    drop_forms(c);
+    return true;
 }
 
 void ensure_obs(rtdm_ctx *c, int64_t rows)
@@ -1462,7 +1572,11 @@ void mlp_work(rtdm_ctx *c, int64_t n)
     M.dy.alloc((size_t)n * M.out);
     M.dh.alloc((size_t)n * kMlpHidden);
     M.sqerr.alloc(n);
-    M.part.alloc((size_t)(std::min<int64_t>(64, (n + 63) / 64) * M.np));   // chunks of any count up to n
+    try {
+        M.part.alloc((size_t)(std::min<int64_t>(64, (n + 63) / 64) * M.np));   // chunks of any count up to n
+    } catch (const Error &e) {                 // optional: without room one chunk takes every sample
+        if (e.code != RTDM_E_OOM) throw;
+    }
     M.work_n = n;
 }
 
@@ -1541,6 +1655,8 @@ int rtdm_create(rtdm_ctx **out, int hip_device, const rtdm_options *opt)
     } catch (...) {
         return RTDM_E_OOM;
     }
+    c->mem.reclaim = reclaim_forms;
+    c->mem.reclaim_user = c;
     API_BEGIN
     int ndev = 0;
     RT_HIP(hipGetDeviceCount(&ndev));
@@ -1639,6 +1755,8 @@ int rtdm_set_geometry(rtdm_ctx *c, int64_t n_atoms, const double *xyz, const int
     }
     for (int64_t e = 0; e < 3 * n_atoms; ++e) RT_CHECK(std::isfinite(xyz[e]), RTDM_E_ARG, "non-finite position");
     RT_HIP(hipDeviceSynchronize());
+    c->W_in_cm = false;
+    drop_forms(c);
     c->scheds.clear();
     c->pats.clear();
     for (auto &m : c->mats) { m.re.release(); m.im.release(); m.pat = -1; }
@@ -1675,6 +1793,8 @@ int rtdm_set_ranges(rtdm_ctx *c, double R_hs, double R_p, double R_k)
     if (R_p <= 0) R_p = std::max(R_hs, R_k);
     RT_HIP(hipDeviceSynchronize());
     c->prec = RTDM_PREC_FP64;   // (a step that failed may have left another)
+    c->W_in_cm = false;
+    drop_forms(c);
     c->scheds.clear();
     c->pats.clear();
     const double r[3] = {R_hs, R_p, R_k};
@@ -1815,47 +1935,10 @@ int rtdm_set_ranges(rtdm_ctx *c, double R_hs, double R_p, double R_k)
         }
         c->u_copies_valid = false;
     }
-    {
-        // pair layout where every product of the kind runs over segmented runs of 2 (FP64 products only)
-        auto runs2 = [&](int prod) { return runs_of_2(c, prod); };
-        const bool fp64 = c->b == 13 && all_products_prec(c) == RTDM_PREC_FP64;
-        c->pairs_real = fp64 && c->run_real == 2 && runs2(RTDM_PROD_XH) && runs2(RTDM_PROD_AT) && runs2(RTDM_PROD_SX);
-        c->pairs_cplx = fp64 && c->run_cplx == 2 && runs2(RTDM_PROD_UK) && runs2(RTDM_PROD_WU);
-        c->Ap.re.release();
-        c->Bp.re.release();
-        c->Bp.im.release();
-        c->Lp.re.release();
-        c->Lp.im.release();
-        c->Kr.clear();
-        c->K_right_valid = false;
-        if (c->pairs_cplx || (all_products_prec(c) == RTDM_PREC_FP64 && b4_takes_transposed(c, schedule(c, RTDM_PROD_UK)))) {
-            c->Kr.resize(n_kicks(c));
-            for (auto &Km : c->Kr) alloc_like(c, Km, c->mats[RTDM_MAT_K]);
-        }
-        if (c->pairs_real) {
-            c->Ap.pat = c->range_pat[R_P];
-            c->Ap.re.alloc(elems(c, c->Ap));
-        }
-        if (c->pairs_real && c->pairs_cplx && c->opt.propagator != RTDM_PROP_EM) {
-            c->Lp.re.alloc(pat_of(c, R_P).nnzb * 169);
-            c->Lp.im.alloc(pat_of(c, R_P).nnzb * 169);
-        }
-        bool b4 = false;         // some b = 4 products over enough runs for transposed right operands
-        if (c->b == 4 && c->run_b4 == 16)
-            for (auto &kv : c->scheds) {
-                auto r = kv.second->runs.find(16);
-                b4 |= r != kv.second->runs.end() && r->second->nch > 0 && !b4_split_form(r->second->nch);
-            }
-        if (c->pairs_real || c->pairs_cplx || b4) {
-            const int64_t ne =
-                std::max({pat_of(c, R_HS).nnzb, pat_of(c, R_P).nnzb, pat_of(c, R_K).nnzb}) * (int64_t)c->b * c->b;
-            c->Bp.re.alloc(ne);
-            if (c->pairs_cplx || b4) c->Bp.im.alloc(ne);
-        }
-    }
     // the unitarity product too when steps check it, so that rtdm_step allocates nothing and the
     // allocation-free product takes the kind (the check itself may run by rows, without these lists)
     if (c->opt.unit_check_every > 0) schedule(c, RTDM_PROD_UV);
+    set_forms(c);
     RT_HIP(hipDeviceSynchronize());
     API_END(c)
 }
@@ -2146,13 +2229,13 @@ int rtdm_build_inverse(rtdm_ctx *c, void *stream, int *iters, double *residual)
     // nothing) for the whole iteration, of X per iteration.
     const bool cm = use_cm(c);
     Mat &Sc = c->Sc;
-    if (cm) left_copy(c, RTDM_PROD_SX, S, Sc, s);
     // X moves between buffers below and Xc is used as scratch: a captured step
     // that reads either must be captured again
     drop_graph(c);
     // Returns 1 converged, 0 diverged, -1 hit the cap.
     auto run = [&](int &k_out, double &r_out) -> int {
         std::vector<double> res;
+        if (cm) left_copy(c, RTDM_PROD_SX, S, Sc, s);
         // The products of an iteration read X in the forms the last one's update wrote (Xc, Bp) and
         // W as the first product writes it: pair layout at b = 13, transposed blocks where both
         // b = 4 products take those in any case
@@ -2337,7 +2420,7 @@ void ensure_a0(rtdm_ctx *c, hipStream_t s)
 void copy_a(rtdm_ctx *c, hipStream_t s)
 {
     const Mat &A = c->mats[RTDM_MAT_A];
-    // (the fused Taylor form makes Ap itself)
+    // (the fused Taylor form makes the left pairs of A itself)
     if (c->pairs_real && c->opt.precision != RTDM_PREC_FP64) pack_planes(c, A, c->Ap, kPackLeft, s);
     if (!c->pairs_real || c->opt.precision != RTDM_PREC_FP64) transpose_into(c, A, c->Ac, s);
 }
@@ -2963,13 +3046,19 @@ int rtdm_bind_workspace(rtdm_ctx *c, void *ptr, size_t bytes)
     RT_CHECK(hipPointerGetAttributes(&attr, ptr) == hipSuccess && attr.type == hipMemoryTypeDevice &&
                  attr.device == c->device,
              RTDM_E_ARG, "the workspace is not device memory of the context's device");
-    std::vector<DBufBase *> list(c->mem.bufs.begin(), c->mem.bufs.end());
-    std::sort(list.begin(), list.end(), [](DBufBase *a, DBufBase *b) { return a->raw() < b->raw(); });
-    size_t need = 0;
-    for (auto *b : list) need += devmem_align(b->nbytes);
-    RT_CHECK(need <= bytes, RTDM_E_OOM, "workspace too small: " + std::to_string(need) + " bytes needed");
+    auto held = [&]() {
+        size_t sum = 0;
+        for (auto *b : c->mem.bufs) sum += devmem_align(b->nbytes);
+        return sum;
+    };
+    size_t forms = 0;
+    for (auto *b : form_bufs(c)) forms += devmem_align(b->nbytes);
+    RT_CHECK(held() - forms <= bytes, RTDM_E_OOM, "workspace too small: " + std::to_string(held()) + " bytes needed");
     RT_HIP(hipDeviceSynchronize());
     drop_graph(c);
+    if (held() > bytes) drop_forms(c);   // a region without room for the operand forms
+    std::vector<DBufBase *> list(c->mem.bufs.begin(), c->mem.bufs.end());
+    std::sort(list.begin(), list.end(), [](DBufBase *a, DBufBase *b) { return a->raw() < b->raw(); });
     const bool cur_a = c->q_cur == c->q_a.p;
     char *base = static_cast<char *>(ptr);
     size_t off = 0;
@@ -3005,17 +3094,24 @@ int rtdm_set_allocator(rtdm_ctx *c, void *(*alloc_fn)(size_t, void *), void (*fr
     RT_HIP(hipDeviceSynchronize());
     drop_graph(c);
     const bool cur_a = c->q_cur == c->q_a.p;
-    // move the buffers allocated so far into the caller's allocations
-    std::vector<DBufBase *> list(c->mem.bufs.begin(), c->mem.bufs.end());
-    std::vector<void *> homes(list.size(), nullptr);
-    for (size_t k = 0; k < list.size(); ++k) {
-        homes[k] = alloc_fn(list[k]->nbytes, user);
-        if (!homes[k] || (reinterpret_cast<uintptr_t>(homes[k]) & 255) != 0) {
+    // move the buffers allocated so far into the caller's allocations (without the
+    // operand forms where the allocator has no room for all)
+    std::vector<DBufBase *> list;
+    std::vector<void *> homes;
+    for (bool placed = false; !placed;) {
+        list.assign(c->mem.bufs.begin(), c->mem.bufs.end());
+        homes.assign(list.size(), nullptr);
+        placed = true;
+        for (size_t k = 0; k < list.size() && placed; ++k) {
+            homes[k] = alloc_fn(list[k]->nbytes, user);
+            if (homes[k] && (reinterpret_cast<uintptr_t>(homes[k]) & 255) == 0) continue;
+            placed = false;
+            const bool refused = !homes[k];
             for (void *h : homes)
                 if (h) free_fn(h, user);
-            throw Error(homes[k] ? RTDM_E_ARG : RTDM_E_OOM,
-                        homes[k] ? "the allocator returned memory that is not 256-byte aligned"
-                                 : "the allocator refused the context's buffers");
+            RT_CHECK(refused, RTDM_E_ARG, "the allocator returned memory that is not 256-byte aligned");
+            RT_CHECK(!form_bufs(c).empty(), RTDM_E_OOM, "the allocator refused the context's buffers");
+            drop_forms(c);
         }
     }
     for (size_t k = 0; k < list.size(); ++k) {
@@ -3043,29 +3139,33 @@ int rtdm_unbind_workspace(rtdm_ctx *c)
     RT_HIP(hipDeviceSynchronize());
     drop_graph(c);
     const bool cur_a = c->q_cur == c->q_a.p;
-    std::vector<DBufBase *> list(c->mem.bufs.begin(), c->mem.bufs.end());
-    // allocate every new home first, so that a failure leaves the context bound as it was
-    std::vector<void *> homes(list.size(), nullptr);
+    // allocate every new home first, so that a failure leaves the context bound (it gives
+    // its operand forms back before it fails)
+    std::vector<DBufBase *> list;
+    std::vector<void *> homes;
     const bool ext = c->mem.ext_alloc != nullptr;
-    auto give_back = [&]() {
+    for (bool placed = false; !placed;) {
+        list.assign(c->mem.bufs.begin(), c->mem.bufs.end());
+        homes.assign(list.size(), nullptr);
+        placed = true;
+        for (size_t k = 0; k < list.size() && placed; ++k) {
+            if (!list[k]->in_ws) continue;
+            if (ext) {
+                homes[k] = c->mem.ext_alloc(list[k]->nbytes, c->mem.ext_user);
+            } else if (hipMalloc(&homes[k], list[k]->nbytes) != hipSuccess) {
+                (void)hipGetLastError();
+                homes[k] = nullptr;
+            }
+            placed = homes[k] != nullptr;
+        }
+        if (placed) break;
         for (void *h : homes)
             if (h) {
                 if (ext) c->mem.ext_free(h, c->mem.ext_user);
                 else (void)hipFree(h);
             }
-    };
-    for (size_t k = 0; k < list.size(); ++k) {
-        if (!list[k]->in_ws) continue;
-        if (ext) {
-            homes[k] = c->mem.ext_alloc(list[k]->nbytes, c->mem.ext_user);
-        } else if (hipMalloc(&homes[k], list[k]->nbytes) != hipSuccess) {
-            (void)hipGetLastError();
-            homes[k] = nullptr;
-        }
-        if (!homes[k]) {
-            give_back();
-            throw Error(RTDM_E_OOM, "allocation failed while moving out of the workspace");
-        }
+        RT_CHECK(!form_bufs(c).empty(), RTDM_E_OOM, "allocation failed while moving out of the workspace");
+        drop_forms(c);
     }
     for (size_t k = 0; k < list.size(); ++k) {
         if (!homes[k]) continue;
@@ -3290,7 +3390,7 @@ int rtdm_autotune(rtdm_ctx *c, void *stream, int *wpb_out, int *tile_out)
                 product_cm(c, RTDM_PROD_UK, c->Uc, Kr, c->Wc, 0, 1, 1.0, s, c->pairs_cplx);   // warm-up
                 RT_HIP(hipEventRecord(e0, s));
                 product_cm(c, RTDM_PROD_UK, c->Uc, Kr, c->Wc, 0, 1, 1.0, s, c->pairs_cplx);
-                product_cm(c, RTDM_PROD_AT, c->pairs_real ? c->Ap : c->Ac, c->tau[0], c->tau[1], 0, 0, 1.0, s,
+                product_cm(c, RTDM_PROD_AT, c->pairs_real ? a_left(c) : c->Ac, c->tau[0], c->tau[1], 0, 0, 1.0, s,
                            c->pairs_real);
                 RT_HIP(hipEventRecord(e1, s));
                 RT_HIP(hipEventSynchronize(e1));
