@@ -447,11 +447,14 @@ int rtdm_select_kick(rtdm_ctx *ctx, int k);
  * group's centroid.  Synchronises. */
 int rtdm_group_trace(rtdm_ctx *ctx, double *out, int64_t max_rows, int64_t *rows);
 
-/* Time candidate launch shapes of the step's block products (workgroups of
- * 4, 8 or 16 waves for the single-output kernels; output tiles of 64, 256 or
- * 1024 atom rows) on the current matrices and keep the fastest; b = 13 only
- * (other block sizes have one shape).  Overwrites W and the Taylor-term work buffers.  *wpb, *row_tile
- * (may be NULL) receive the choice.  Synchronises. */
+/* Time candidate launch shapes of the step's block products (output tiles of 64,
+ * 256, 512 or 1024 atom rows and the one in use; workgroups of 4, 8 or 16 waves
+ * where the products run on the single-output kernels) on the current matrices
+ * and keep the fastest, the one in use unless another is faster; b = 13 only
+ * (other block sizes have one shape).  Overwrites W and the Taylor-term work
+ * buffers.  *wpb, *row_tile (may be NULL) receive the choice, for the tile the
+ * smallest candidate that gives the order kept (tiles of at least n_atoms rows
+ * all give one).  Synchronises. */
 int rtdm_autotune(rtdm_ctx *ctx, void *hip_stream, int *wpb, int *row_tile);
 
 /* Outcome of the last rtdm_build_inverse: iterations summed over the start

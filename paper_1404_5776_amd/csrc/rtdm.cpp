@@ -3363,7 +3363,18 @@ int rtdm_autotune(rtdm_ctx *c, void *stream, int *wpb_out, int *tile_out)
     hipStream_t s = (hipStream_t)stream;
     const Turn turn(c, s);
     if (c->b == 13) {
-        const int wpbs[3] = {4, 8, 16}, tiles[3] = {64, 256, 1024};
+        const int tiles[4] = {64, 256, 512, 1024};
+        // the row-run kernels have one workgroup shape
+        auto on_runs = [&](int prod, int nj) {
+            const Sched &S = schedule(c, prod);
+            auto r = S.runs.find(nj);
+            return nj > 1 && r != S.runs.end() && r->second->nch > 0;
+        };
+        const std::vector<int> wpbs = on_runs(RTDM_PROD_UK, c->run_cplx) && on_runs(RTDM_PROD_AT, c->run_real)
+                                          ? std::vector<int>{c->wpb}
+                                          : std::vector<int>{4, 8, 16};
+        // tiles of at least n rows give one order
+        auto rows_of = [&](int tile) { return std::min<int64_t>(tile, c->n); };
         // events and the context's timing flag are restored however the sweep ends
         struct Guard {
             rtdm_ctx *c;
@@ -3382,7 +3393,13 @@ int rtdm_autotune(rtdm_ctx *c, void *stream, int *wpb_out, int *tile_out)
         double best = 1e300;
         int bw = c->wpb, bt = c->row_tile;
         c->timing = false;
-        for (int tile : tiles) {
+        // the tile in use first, so that another has to be faster; each order once
+        std::vector<int> order{c->row_tile};
+        for (int tile : tiles)
+            if (std::none_of(order.begin(), order.end(), [&](int t) { return rows_of(t) == rows_of(tile); }))
+                order.push_back(tile);
+        if (order.size() == 1 && wpbs.size() == 1) order.clear();
+        for (int tile : order) {
             set_row_tile(c, tile);
             for (int w : wpbs) {
                 c->wpb = w;
@@ -3404,12 +3421,20 @@ int rtdm_autotune(rtdm_ctx *c, void *stream, int *wpb_out, int *tile_out)
             }
         }
         c->wpb = bw;
-        set_row_tile(c, bt);
-        c->W_in_cm = true;
-        drop_graph(c);
+        if (!order.empty()) {
+            set_row_tile(c, bt);
+            c->W_in_cm = true;
+            drop_graph(c);
+        }
+        if (tile_out) {            // the smallest candidate of the order in use
+            *tile_out = c->row_tile;
+            for (int k = 3; k >= 0; --k)
+                if (rows_of(tiles[k]) == rows_of(c->row_tile)) *tile_out = tiles[k];
+        }
+    } else if (tile_out) {
+        *tile_out = c->row_tile;
     }
     if (wpb_out) *wpb_out = c->wpb;
-    if (tile_out) *tile_out = c->row_tile;
     API_END(c)
 }
 
