@@ -365,7 +365,9 @@ int rtdm_workspace_size(rtdm_ctx *ctx, size_t *bytes);
  * [ptr, ptr + bytes) (device memory of the context's device, 256-byte
  * aligned, e.g. a torch.empty(bytes, dtype=uint8) tensor) and free the
  * library's own allocations; later allocations of the context are slices of
- * the region (RTDM_E_OOM when it is exhausted).  The region stays owned by
+ * the region (RTDM_E_OOM when it is exhausted).  Copies of operands that the
+ * context can do without are kept where the region has room, at its end, and
+ * give way to later allocations.  The region stays owned by
  * the caller and must outlive the context.  Afterwards the geometry and
  * ranges are fixed (RTDM_E_STATE); a captured step graph is rebuilt.  Binding
  * twice is RTDM_E_STATE.  Synchronises the device. */

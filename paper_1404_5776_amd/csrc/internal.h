@@ -41,7 +41,8 @@ struct DBufBase;
 struct DevMem {
     std::unordered_set<DBufBase *> bufs;
     char *base = nullptr;
-    size_t cap = 0, used = 0;
+    size_t cap = 0, used = 0;   // cap: what new slices may use of `size`; the operand forms lie behind it
+    size_t size = 0;
     void *(*ext_alloc)(size_t bytes, void *user) = nullptr;   // the caller's allocator, if set
     void (*ext_free)(void *ptr, void *user) = nullptr;
     void *ext_user = nullptr;

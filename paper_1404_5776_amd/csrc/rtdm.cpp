@@ -40,6 +40,7 @@ void *devmem_alloc(DBufBase *b, size_t bytes)
     auto reclaimed = [&]() { return m && m->reclaim && m->reclaim(m->reclaim_user); };
     if (m && m->base) {
         const size_t off = devmem_align(m->used);
+        if (off + bytes > m->cap) (void)reclaimed();
         RT_CHECK(off + bytes <= m->cap, RTDM_E_OOM,
                  "bound workspace exhausted: " + std::to_string(bytes) + " more bytes needed");
         p = m->base + off;
@@ -1328,6 +1329,7 @@ void drop_forms(rtdm_ctx *c)
     c->Lp.re.release();
     c->Lp.im.release();
     c->Kr.clear();
+    c->mem.cap = c->mem.size;   // a bound region keeps them at its end
     c->K_right_valid = c->Xc_valid = c->u_copies_valid = false;
 }
 
@@ -3067,20 +3069,25 @@ int rtdm_bind_workspace(rtdm_ctx *c, void *ptr, size_t bytes)
     std::vector<DBufBase *> list(c->mem.bufs.begin(), c->mem.bufs.end());
     std::sort(list.begin(), list.end(), [](DBufBase *a, DBufBase *b) { return a->raw() < b->raw(); });
     const bool cur_a = c->q_cur == c->q_a.p;
+    // the operand forms at the region's end: given back later, they leave their room to whatever has grown
+    const std::vector<DBufBase *> optional = form_bufs(c);
     char *base = static_cast<char *>(ptr);
-    size_t off = 0;
+    size_t off = 0, top = bytes / 256 * 256;
     for (auto *b : list) {
-        void *np = base + off;
+        const size_t len = devmem_align(b->nbytes);
+        const bool at_end = std::find(optional.begin(), optional.end(), b) != optional.end();
+        void *np = base + (at_end ? top -= len : off);
         RT_HIP(hipMemcpy(np, b->raw(), b->nbytes, hipMemcpyDeviceToDevice));
         if (b->ext) c->mem.ext_free(b->raw(), c->mem.ext_user);
         else RT_HIP(hipFree(b->raw()));
         b->set_raw(np);
         b->in_ws = true;
         b->ext = false;
-        off += devmem_align(b->nbytes);
+        if (!at_end) off += len;
     }
     c->mem.base = base;
-    c->mem.cap = bytes;
+    c->mem.cap = optional.empty() ? bytes : top;
+    c->mem.size = bytes;
     c->mem.used = off;
     if (c->q_a.p) {
         c->q_cur = cur_a ? c->q_a.p : c->q_b.p;
@@ -3182,7 +3189,7 @@ int rtdm_unbind_workspace(rtdm_ctx *c)
         list[k]->ext = ext;
     }
     c->mem.base = nullptr;
-    c->mem.cap = 0;
+    c->mem.cap = c->mem.size = 0;
     c->mem.used = 0;
     if (c->q_a.p) {
         c->q_cur = cur_a ? c->q_a.p : c->q_b.p;

@@ -139,6 +139,31 @@ def test_a_region_without_room_for_the_copies(which):
     ctx.close()
 
 
+@pytest.mark.parametrize("which", WHICH)
+def test_a_region_that_the_trace_outgrows(which):
+    """A region that holds the copies but not a trace grown by half of their
+    size as well: the copies give way, the steps go on."""
+    import torch
+    s, ctx = _load(which)
+    _run(s, ctx)
+    rtdm.rtdm_step(ctx.h, DT, STEPS)
+    want = _read(s, ctx)
+    ctx.close()
+    s, ctx = _load(which)
+    rtdm.rtdm_build_inverse(ctx.h)
+    rtdm.rtdm_apply_kick(ctx.h, (0.01, 0.0, 0.005))
+    rtdm.rtdm_step(ctx.h, DT, STEPS)
+    copies = COPIES[which] * rtdm.rtdm_pattern(ctx.h, "K")[1].size * s.b * s.b * 8
+    live = rtdm.rtdm_workspace_size(ctx.h) - (64 << 20)
+    grown = 64 << (copies // 2 // 64).bit_length() - 1     # a power of two: the largest trace below half of the copies
+    region = torch.empty(live + grown // 2, dtype=torch.uint8, device="cuda:0")
+    rtdm.rtdm_bind_workspace(ctx.h, region.data_ptr(), region.numel())
+    rtdm.rtdm_reserve_trace(ctx.h, grown // 64)
+    rtdm.rtdm_step(ctx.h, DT, STEPS)
+    _same(_read(s, ctx), want)
+    ctx.close()
+
+
 @pytest.mark.parametrize("n", [65, 700])
 def test_gradient_without_room_for_the_chunks_partial_sums(n):
     """The network's gradient is summed over chunks of samples whose partial
