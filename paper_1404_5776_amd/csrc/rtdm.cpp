@@ -2470,15 +2470,8 @@ void build_u(rtdm_ctx *c, double dt, bool corr, hipStream_t s)
         copy_mat(c, U, c->E1, s);
         make_a(c, 1.0, corr, s);
         build_propagator(c, 0.5 * dt, s);
-        // P(E2 E1) as E2 + P(E2 (E1 - 1)): in the product with E1 itself the 1 on the
-        // diagonal enters in the middle of a sum, and the later terms below half an ulp
-        // of it are lost to one side (216 atoms b = 13: the mean error of U's diagonal
-        // -0.9e-15 in ascending order of k, -1.3e-15 in the row runs' order, now 1e-18;
-        // K of 360 atoms after 3 steps, against 100-bit arithmetic: 0.9e-14, 1.1e-14, 3e-15)
-        launch_add_identity(s, c->n, c->b, pat_of(c, R_P).d_diag.p, -1.0, c->E1.re.p);
         product(c, RTDM_PROD_AT, U, c->E1, c->E2, 1.0, 0.0, s);
-        launch_axpby(s, elems(c, U), 1.0, U.re.p, 1.0, c->E2.re.p, U.re.p);
-        launch_axpby(s, elems(c, U), 1.0, U.im.p, 1.0, c->E2.im.p, U.im.p);
+        copy_mat(c, c->E2, U, s);
         if (use_cm(c)) left_copy(c, RTDM_PROD_UK, U, c->Uc, s);
         break;
     case RTDM_PROP_M4: {
