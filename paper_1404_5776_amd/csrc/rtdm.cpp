@@ -212,12 +212,12 @@ bool run_refused(int kind)
 // Row runs of schedule S for op(A) = A: the outputs of each row of C cut into
 // runs of nj consecutive columns; the entries of a run are the k of row i of
 // A used by any of its outputs, each with op(A)_ik and the op(B)_kj block of
-// every output (-1: no triple for k).  Built on the GPU (k_run_sym); inter4
-// stores the b = 4 kernel's slot order.
-bool build_runs(Sched &S, const Pattern &A, const Pattern &B, const Pattern &C, int op_b, int nj, int inter4,
-                int tile_i)
+// every output (-1: no triple for k), in ascending k or, segmented (runs of 2),
+// those that feed both outputs first, then one.  Built on the GPU (k_run_sym);
+// inter4 stores the b = 4 kernel's slot order.  Null where they do not fit.
+std::unique_ptr<Runs> make_runs(const Pattern &A, const Pattern &B, const Pattern &C, int op_b, int nj, int inter4,
+                                bool segmented, int tile_i)
 {
-    if (S.runs.count(nj)) return false;
     auto R = std::make_unique<Runs>();
     std::vector<int64_t> p0s;
     for (int64_t i = 0; i < C.n; ++i)
@@ -234,8 +234,6 @@ bool build_runs(Sched &S, const Pattern &A, const Pattern &B, const Pattern &C, 
     d_row.alloc(std::max<int64_t>(nch, 1));
     d_p0.alloc(std::max<int64_t>(nch, 1));
     cnt.alloc(std::max<int64_t>(nch, 1));
-    // runs of 2 (b = 13) are stored in segments: entries feeding both outputs, then one
-    const bool segmented = nj == 2 && !inter4;
     if (segmented) R->seg.alloc(std::max<int64_t>(2 * nch, 2));
     std::vector<int64_t> off(nch + 1, 0);
     if (nch) {
@@ -252,7 +250,7 @@ bool build_runs(Sched &S, const Pattern &A, const Pattern &B, const Pattern &C, 
         size_t free_b = 0, total_b = 0;
         RT_HIP(hipMemGetInfo(&free_b, &total_b));
         const double need = (double)ne * 4.0 * (1 + nj) + (double)nch * (8.0 + 4.0 * nj + 4.0);
-        if (need + (double)kRunReserve > (double)free_b) return false;
+        if (need + (double)kRunReserve > (double)free_b) return nullptr;
     }
     R->off.alloc(nch + 1);
     R->a.alloc(std::max<int64_t>(ne, 1));
@@ -267,8 +265,16 @@ bool build_runs(Sched &S, const Pattern &A, const Pattern &B, const Pattern &C, 
     if (!ord.empty())
         RT_HIP(hipMemcpy(R->order.p, ord.data(), ord.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     RT_HIP(hipDeviceSynchronize());   // the temporaries above are freed on return
-    S.runs.emplace(nj, std::move(R));
-    return true;
+    return R;
+}
+
+// The row runs of schedule S (runs of 2 at b = 13 segmented).
+void build_runs(Sched &S, const Pattern &A, const Pattern &B, const Pattern &C, int op_b, int nj, int inter4,
+                int tile_i)
+{
+    if (S.runs.count(nj)) return;
+    auto R = make_runs(A, B, C, op_b, nj, inter4, nj == 2 && !inter4, tile_i);
+    if (R) S.runs.emplace(nj, std::move(R));
 }
 
 struct TRec {
@@ -345,6 +351,8 @@ struct rtdm_ctx {
     // left pairs of the left operand of a product without a kept copy (ETRS and
     // Magnus propagators at b = 13: U E1, the commutator, M T_k); allocated with them
     Mat Lp;
+    // ETRS at b = 13: row runs of U E1 in ascending k (see build_u)
+    std::unique_ptr<Runs> ascending;
     // Bp and Lp serve one call at a time (Turn): the event behind the last one and its stream
     hipEvent_t turn_ev = nullptr;
     hipStream_t turn_stream = nullptr;
@@ -737,6 +745,7 @@ hipEvent_t event_at(rtdm_ctx *c, size_t k)
 struct ProductOut {
     int layout = 0;     // b = 13 pair products: kOutRows / kOutLeft / kOutRight; b_t products: 1 transposed blocks
     bool rows = false;  // b = 13 pair products: operands by rows (launch_spgemm_pairs)
+    bool ascending = false;   // b = 13: the sums in ascending k (rtdm_ctx::ascending, or no runs)
     SumInto u;          // fused sum
     bool drop = false;  // C itself is not wanted
 };
@@ -813,9 +822,10 @@ void product_key(rtdm_ctx *c, int prod, const std::tuple<int, int, int, int, int
     // b = 13, FP64: both operands packed, the row-run kernel of the step products
     const bool pairs = c->b == 13 && c->prec == RTDM_PREC_FP64 && c->Lp.re.p && A.pat == c->range_pat[R_P] && a.op_a == 0 &&
                        a.op_b == 0 &&
-                       (A.cplx || B.cplx ? c->pairs_cplx : c->pairs_real) && segmented_runs(S);
+                       (A.cplx || B.cplx ? c->pairs_cplx : c->pairs_real) &&
+                       (out.ascending ? c->ascending != nullptr : segmented_runs(S));
     if (pairs) {
-        const Runs &R = *S.runs.find(2)->second;
+        const Runs &R = out.ascending ? *c->ascending : *S.runs.find(2)->second;
         a.nj = 2;
         a.nch = R.nch;
         a.ch_off = R.off.p;
@@ -1328,6 +1338,7 @@ void drop_forms(rtdm_ctx *c)
     c->Bp.im.release();
     c->Lp.re.release();
     c->Lp.im.release();
+    c->ascending.reset();
     c->Kr.clear();
     c->mem.cap = c->mem.size;   // a bound region keeps them at its end
     c->K_right_valid = c->Xc_valid = c->u_copies_valid = false;
@@ -1363,6 +1374,10 @@ void set_forms(rtdm_ctx *c)
     if (need + (double)kRunReserve > (double)free_b) return;
     c->setting_forms = true;
     try {
+        if (left && c->opt.propagator == RTDM_PROP_ETRS) {
+            const Pattern &P = pat_of(c, R_P);
+            c->ascending = make_runs(P, P, P, 0, 2, 0, false, c->row_tile);
+        }
         if (k_right) {
             c->Kr.resize(n_kicks(c));
             for (auto &Km : c->Kr) alloc_like(c, Km, c->mats[RTDM_MAT_K]);
@@ -1398,6 +1413,10 @@ std::vector<DBufBase *> form_bufs(rtdm_ctx *c)
     for (auto &m : c->Kr)
         for (auto *b : {&m.re, &m.im})
             if (b->p) list.push_back(b);
+    if (c->ascending) {
+        list.push_back(&c->ascending->off);
+        for (auto *b : {&c->ascending->a, &c->ascending->b, &c->ascending->out, &c->ascending->order}) list.push_back(b);
+    }
     return list;
 }
 
@@ -2470,7 +2489,18 @@ void build_u(rtdm_ctx *c, double dt, bool corr, hipStream_t s)
         copy_mat(c, U, c->E1, s);
         make_a(c, 1.0, corr, s);
         build_propagator(c, 0.5 * dt, s);
-        product(c, RTDM_PROD_AT, U, c->E1, c->E2, 1.0, 0.0, s);
+        // E2 and E1 are the identity plus something small: the 1 of a diagonal element's sum
+        // enters somewhere in the middle, and of the thousand terms of one sign after it those
+        // below half an ulp of 1 are lost.  In segments (entries that feed both outputs of a
+        // run, then one) more terms come after it than in ascending k, which moved the mean of
+        // U's diagonal by -3.6e-16 (216 atoms b = 13) and K of 360 atoms after 3 steps from
+        // 2e-15 to 5e-15 from 64-bit arithmetic.  Without segments a run's absent products are
+        // issued as well: those 3 steps with two corrector passes 26.0 -> 26.9 ms.
+        {
+            ProductOut plain;
+            plain.ascending = true;
+            product_key(c, RTDM_PROD_AT, prod_key(c, RTDM_PROD_AT), U, c->E1, c->E2, 1.0, 0.0, s, false, plain);
+        }
         copy_mat(c, c->E2, U, s);
         if (use_cm(c)) left_copy(c, RTDM_PROD_UK, U, c->Uc, s);
         break;
@@ -3357,6 +3387,10 @@ void set_row_tile(rtdm_ctx *c, int tile)
             const std::vector<int32_t> ro = run_order(R, tile);
             RT_HIP(hipMemcpy(R.order.p, ro.data(), ro.size() * sizeof(int32_t), hipMemcpyHostToDevice));
         }
+    }
+    if (c->ascending && c->ascending->nch > 0) {
+        const std::vector<int32_t> ro = run_order(*c->ascending, tile);
+        RT_HIP(hipMemcpy(c->ascending->order.p, ro.data(), ro.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     }
 }
 }  // namespace

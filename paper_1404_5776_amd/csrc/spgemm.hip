@@ -625,10 +625,12 @@ __global__ __launch_bounds__(256, MINW) void k_spgemm_q4j(
 // the Taylor sum, whose own pass would read the term again.  ROWS: both operands
 // by rows as they are stored, for products recorded into a caller's graph, which
 // may use no buffer of the context's: A in the same 16-byte loads, 104 bytes from
-// lane to lane, B in two 8-byte ones; the same products in the same order.
+// lane to lane, B in two 8-byte ones; the same products in the same order.  SEG =
+// false (complex products): entries in ascending k without segments, absent ones
+// read from the zero block; more matrix instructions for the order of the sums.
 typedef double pd2 __attribute__((ext_vector_type(2), aligned(8)));
 typedef __attribute__((address_space(1))) const pd2 gpd2;
-template <int B, bool AC, bool BC, int CJB, int OUT, bool ROWS>
+template <int B, bool AC, bool BC, int CJB, int OUT, bool ROWS, bool SEG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AC || BC ? 3 : 2, AC || BC ? 3 : 2))) void k_spgemm_q4p(
     int64_t nch, const int64_t *__restrict__ off, const int32_t *__restrict__ ea,
     const int32_t *__restrict__ eb, const int32_t *__restrict__ cout,
@@ -639,6 +641,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AC || BC ? 
 {
     static_assert(B >= 5 && B <= 15 && (B & 1), "odd block sizes");
     static_assert(!ROWS || !CJB, "a conjugated right operand has its pair layout");
+    static_assert(SEG || (AC && BC), "entries without segments: complex operands");
     constexpr int BB = B * B, NJ = 2;
     const int lane = threadIdx.x & 63;
     const int64_t w = xcd_block((nch + 3) / 4, remap) * 4 + (threadIdx.x >> 6);
@@ -745,7 +748,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AC || BC ? 
 #pragma unroll
                 for (int t = 0; t < NJ; ++t) {
                     if (!((ACT >> t) & 1)) continue;
-                    const int64_t ob = (int64_t)nb[t] * BB + fb;   // present: segmented entries
+                    if (!SEG && nb[t] < 0) continue;               // (segmented entries are all present)
+                    const int64_t ob = (int64_t)nb[t] * BB + fb;
                     pb[t] = (const gdouble *)(br + ob);
                     if (BC) pbi[t] = (const gdouble *)(bi + ob);
                 }
@@ -792,10 +796,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AC || BC ? 
             }
         }
     };
-    const int nf = seg[2 * c], n0 = seg[2 * c + 1];   // uniform across the wave
-    groups(0, nf, std::integral_constant<int, 3>());
-    groups(nf, nf + n0, std::integral_constant<int, 1>());
-    groups(nf + n0, ne, std::integral_constant<int, 2>());
+    if constexpr (SEG) {
+        const int nf = seg[2 * c], n0 = seg[2 * c + 1];   // uniform across the wave
+        groups(0, nf, std::integral_constant<int, 3>());
+        groups(nf, nf + n0, std::integral_constant<int, 1>());
+        groups(nf + n0, ne, std::integral_constant<int, 2>());
+    } else {
+        groups(0, ne, std::integral_constant<int, 3>());
+    }
     constexpr double sb = CJB ? -1.0 : 1.0;
     const int col = lane & 15;
 #pragma unroll
@@ -888,12 +896,12 @@ void launch_taylor_start(hipStream_t s, int64_t nblocks, int b, double dt, const
     RT_HIP(hipGetLastError());
 }
 
-template <bool AC, bool BC, int CJB, int OUT, bool ROWS = false>
+template <bool AC, bool BC, int CJB, int OUT, bool ROWS = false, bool SEG = true>
 static void launch_q4p(hipStream_t s, const SpgemmArgs &a, const SumInto &u)
 {
     const int remap = xcd_chunk_for((a.nch + 3) / 4);
     const unsigned grid = xcd_grid((a.nch + 3) / 4, remap);
-    hipLaunchKernelGGL((k_spgemm_q4p<13, AC, BC, CJB, OUT, ROWS>), dim3(grid), dim3(256), 0, s, a.nch,
+    hipLaunchKernelGGL((k_spgemm_q4p<13, AC, BC, CJB, OUT, ROWS, SEG>), dim3(grid), dim3(256), 0, s, a.nch,
                        a.ch_off, a.ch_a, a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re,
                        a.alpha_im, a.zero, a.ch_order, remap, a.ch_seg, u.p, u.sign, u.store);
 }
@@ -901,12 +909,19 @@ static void launch_q4p(hipStream_t s, const SpgemmArgs &a, const SumInto &u)
 // Products over row runs of 2 with both operands in pair layout (b = 13, FP64;
 // a conjugated right operand U^dagger is the left pairs of U): conj_b, out
 // (kOut*; right pairs and the fused sum u for real products only).  rows: both
-// operands and the output by rows.
+// operands and the output by rows.  a.ch_seg null: entries without segments.
 void launch_spgemm_pairs(hipStream_t s, const SpgemmArgs &a, int conj_b, int out, const SumInto &u, bool rows)
 {
-    RT_CHECK(a.b == 13 && a.precision == RTDM_PREC_FP64 && a.nj == 2 && a.nch > 0 && a.ch_seg && a.zero, RTDM_E_ARG,
-             "pair-layout products need b = 13, FP64 and segmented runs of 2");
+    RT_CHECK(a.b == 13 && a.precision == RTDM_PREC_FP64 && a.nj == 2 && a.nch > 0 && a.zero, RTDM_E_ARG,
+             "pair-layout products need b = 13, FP64 and runs of 2");
     const bool ac = a.ai != nullptr, bc = a.bi != nullptr;
+    if (!a.ch_seg) {
+        RT_CHECK(ac && bc && !rows && !conj_b && out == kOutRows && !u.p, RTDM_E_ARG,
+                 "runs without segments give a plain complex product by rows");
+        launch_q4p<true, true, 0, 0, false, false>(s, a, u);
+        RT_HIP(hipGetLastError());
+        return;
+    }
     const bool real = !ac && !bc && !a.ci;
     RT_CHECK(real || (!u.p && out != kOutRight), RTDM_E_ARG, "right pairs and the fused sum need real operands");
     if (rows) {
