@@ -23,7 +23,6 @@
 
 #include "internal.h"
 
-
 namespace rtdm {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
@@ -938,13 +937,12 @@ void launch_spgemm_pairs(hipStream_t s, const SpgemmArgs &a, int conj_b, int out
         RT_HIP(hipGetLastError());
         return;
     }
-    const int out_pairs = out == kOutLeft;
-#define RT_Q4P(AC_, BC_)                                               \
-    do {                                                               \
-        if (conj_b && out_pairs) launch_q4p<AC_, BC_, 1, 1>(s, a, u);  \
-        else if (conj_b) launch_q4p<AC_, BC_, 1, 0>(s, a, u);          \
-        else if (out_pairs) launch_q4p<AC_, BC_, 0, 1>(s, a, u);       \
-        else launch_q4p<AC_, BC_, 0, 0>(s, a, u);                      \
+    RT_CHECK(!conj_b || out == kOutRows, RTDM_E_ARG, "a conjugated right operand gives its product by rows");
+#define RT_Q4P(AC_, BC_)                                                  \
+    do {                                                                  \
+        if (conj_b) launch_q4p<AC_, BC_, 1, 0>(s, a, u);                  \
+        else if (out == kOutLeft) launch_q4p<AC_, BC_, 0, 1>(s, a, u);    \
+        else launch_q4p<AC_, BC_, 0, 0>(s, a, u);                         \
     } while (0)
     if (ac && bc) RT_Q4P(true, true);
     else if (ac) RT_Q4P(true, false);
@@ -1512,8 +1510,8 @@ template <bool AC, bool BC>
 __device__ inline void b4_run_entries(int64_t e0, int64_t e1, int stride, const int32_t *__restrict__ ea,
                                       const int32_t *__restrict__ eb, const double *__restrict__ ar,
                                       const double *__restrict__ ai, const double *__restrict__ br,
-                                      const double *__restrict__ bi, int ia, int ib, int g, double cb,
-                                      double rr[4], double ii[4], double ri[4], double ir[4])
+                                      const double *__restrict__ bi, int ia, int ib, int g, double rr[4],
+                                      double ii[4], double ri[4], double ir[4])
 {
     struct Ops {
         double xar, xai, xbr[4], xbi[4];
@@ -1533,7 +1531,7 @@ __device__ inline void b4_run_entries(int64_t e0, int64_t e1, int stride, const 
             if (kb[jj] >= 0) {
                 const int64_t pb = (int64_t)kb[jj] * 16 + ib;
                 o.xbr[jj] = br[pb];
-                if (BC) o.xbi[jj] = cb * bi[pb];
+                if (BC) o.xbi[jj] = bi[pb];
             }
         }
     };
@@ -1802,22 +1800,25 @@ static void launch_b4p_as(hipStream_t s, const SpgemmArgs &a, const SumInto &u)
 
 // b = 4 FP64 product over runs of 16 from a row-major left operand and a right
 // operand with transposed blocks (conj_b: the row-major blocks of the matrix
-// whose conjugate transpose it is); out_t: the output with transposed blocks;
-// u: the output's fused sum (real products).
+// whose conjugate transpose it is); out_t: the output with transposed blocks
+// (real left operands; real right ones too below kB4SplitRuns runs); u: the
+// output's fused sum (real products).
 void launch_spgemm_b4t(hipStream_t s, const SpgemmArgs &a, int conj_b, int out_t, const SumInto &u)
 {
     RT_CHECK(a.b == 4 && a.precision == RTDM_PREC_FP64 && a.nj == 16 && a.nch > 0 && a.op_a == 0, RTDM_E_ARG,
              "transposed-block products need b = 4, FP64 and runs of 16");
     const bool ac = a.ai != nullptr, bc = a.bi != nullptr;
     RT_CHECK(!u.p || (!ac && !bc && !a.ci), RTDM_E_ARG, "the fused sum needs real operands");
-#define RT_B4P(AC_, BC_)                                                              \
-    do {                                                                              \
-        if (conj_b && out_t) launch_b4p_as<AC_, BC_, 1, 1>(s, a, u);          \
-        else if (conj_b) launch_b4p_as<AC_, BC_, 1, 0>(s, a, u);              \
-        else if (out_t) launch_b4p_as<AC_, BC_, 0, 1>(s, a, u);               \
+    RT_CHECK(!out_t || (!ac && !conj_b && (!bc || a.nch >= kB4SplitRuns)), RTDM_E_ARG,
+             "no transposed output of these operands");
+#define RT_B4P(AC_, BC_)                                                      \
+    do {                                                                      \
+        if (conj_b) launch_b4p_as<AC_, BC_, 1, 0>(s, a, u);                   \
         else launch_b4p_as<AC_, BC_, 0, 0>(s, a, u);                          \
     } while (0)
-    if (ac && bc) RT_B4P(true, true);
+    if (out_t && bc) launch_b4p_runs<false, true, 0, 1>(s, a, u);
+    else if (out_t) launch_b4p_as<false, false, 0, 1>(s, a, u);
+    else if (ac && bc) RT_B4P(true, true);
     else if (ac) RT_B4P(true, false);
     else if (bc) RT_B4P(false, true);
     else RT_B4P(false, false);
@@ -1826,12 +1827,11 @@ void launch_spgemm_b4t(hipStream_t s, const SpgemmArgs &a, int conj_b, int out_t
 }
 
 // FP64 b = 4 product over row runs with few runs (small systems) whose right
-// operand is by rows: one
-// workgroup of W waves per run, wave w taking the entries w, w + W, ..., so
+// operand is by rows: one workgroup of W waves per run, wave w taking the entries w, w + W, ..., so
 // that a run's chain of dependent loads is 1/W as long and W times as many
 // waves share the chip.  The waves' partial sums are added in LDS in the
 // fixed order w = 0, 1, ..., W - 1.
-template <bool AC, bool BC, int OPB, int W>
+template <bool AC, bool BC, int W>
 __global__ __launch_bounds__(64 * W) void k_spgemm_b4js(
     int64_t nch, const int64_t *__restrict__ off, const int32_t *__restrict__ ea,
     const int32_t *__restrict__ eb, const int32_t *__restrict__ cout, const double *__restrict__ ar,
@@ -1843,11 +1843,9 @@ __global__ __launch_bounds__(64 * W) void k_spgemm_b4js(
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int g = (lane >> 2) & 3, r = lane & 3, q = lane >> 4;
     const int64_t c = blockIdx.x;              // grid = nch: uniform across the workgroup
-    const int ia = r * 4 + q;
-    const int ib = OPB ? (r * 4 + q) : (q * 4 + r);
-    const double cb = OPB ? -1.0 : 1.0;
+    const int ia = r * 4 + q, ib = q * 4 + r;
     double rr[4] = {0, 0, 0, 0}, ii[4] = {0, 0, 0, 0}, ri[4] = {0, 0, 0, 0}, ir[4] = {0, 0, 0, 0};
-    b4_run_entries<AC, BC>(off[c] + wv, off[c + 1], W, ea, eb, ar, ai, br, bi, ia, ib, g, cb, rr, ii, ri, ir);
+    b4_run_entries<AC, BC>(off[c] + wv, off[c + 1], W, ea, eb, ar, ai, br, bi, ia, ib, g, rr, ii, ri, ir);
     auto pack = [&](double (*dst)[64]) {
         int k = 0;
 #pragma unroll
@@ -1884,21 +1882,21 @@ __global__ __launch_bounds__(64 * W) void k_spgemm_b4js(
     }
 }
 
-template <bool AC, bool BC, int OB>
+template <bool AC, bool BC>
 static void launch_b4j(hipStream_t s, const SpgemmArgs &a)
 {
     RT_CHECK(a.nj == 16, RTDM_E_ARG, "b = 4 row runs hold 16 outputs");
     if (a.nch < kB4Split8Runs) {
-        hipLaunchKernelGGL((k_spgemm_b4js<AC, BC, OB, 8>), dim3((unsigned)a.nch), dim3(512), 0, s, a.nch,
+        hipLaunchKernelGGL((k_spgemm_b4js<AC, BC, 8>), dim3((unsigned)a.nch), dim3(512), 0, s, a.nch,
                            a.ch_off, a.ch_a, a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re,
                            a.alpha_im);
         return;
     }
     if (a.nch >= kB4SplitRuns) {
-        launch_b4p_runs<AC, BC, OB, 0, OB == 0>(s, a, SumInto());
+        launch_b4p_runs<AC, BC, 0, 0, true>(s, a, SumInto());
         return;
     }
-    hipLaunchKernelGGL((k_spgemm_b4js<AC, BC, OB, 4>), dim3((unsigned)a.nch), dim3(256), 0, s, a.nch, a.ch_off, a.ch_a,
+    hipLaunchKernelGGL((k_spgemm_b4js<AC, BC, 4>), dim3((unsigned)a.nch), dim3(256), 0, s, a.nch, a.ch_off, a.ch_a,
                        a.ch_b, a.ch_out, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re, a.alpha_im);
 }
 
@@ -1950,8 +1948,8 @@ static void dispatch_ops(hipStream_t s, const SpgemmArgs &a, dim3 g, dim3 t)
             hipLaunchKernelGGL((k_spgemm_kc<4, AC, BC, OA, OB, float>), g, t, 0, s, a.nout,      \
                                a.off, a.trip, a.ar, a.ai, a.br, a.bi, a.cr, a.ci, a.alpha_re,    \
                                a.alpha_im);                                                      \
-        else if (a.b == 4 && OA == 0 && a.nch > 0)                                               \
-            launch_b4j<AC, BC, OB>(s, a);                                                        \
+        else if (a.b == 4 && OA == 0 && OB == 0 && a.nch > 0)                                    \
+            launch_b4j<AC, BC>(s, a);                                                            \
         else if (a.b == 4 && OA == 0)                                                            \
             launch_b4w<AC, BC, OB>(s, a);                                                        \
         else if (a.b == 4)                                                                       \
