@@ -296,9 +296,9 @@ __global__ __launch_bounds__(kT) void k_mulliken(int n_atoms, int n_k, int b, co
 
 // Hermitise and the charges of the new K in one launch, for small systems: the
 // first kRedBlocks workgroups hermitise, the others take the charges of one
-// atom each from the same sums 0.5 (Kn_ij + Kn_ji^*) instead of waiting for K.
-// Same bytes as the two launches.  A step of 64
-// atoms b = 4, all launches: 31.0 -> 27.6 us.
+// atom each from the same sums 0.5 (Kn_ij + Kn_ji^*) instead of waiting for K:
+// two elements of Kn for one of K, against a launch.  A step of 64 atoms b = 4,
+// all launches: 31.0 -> 26.9 us.
 template <int B>
 __global__ __launch_bounds__(kT) void k_hermitize_charges(uint32_t n, int b, const int32_t *__restrict__ trans,
                                                           const double *__restrict__ knr,
@@ -328,9 +328,12 @@ __global__ __launch_bounds__(kT) void k_hermitize_charges(uint32_t n, int b, con
 // (by the atoms alone: a kick set's sums are those of a run with that kick only)
 static bool mulliken_wide(int64_t n_atoms, int b) { return b > 4 || n_atoms < 4096; }
 
-// Up to 2^20 elements of K: hermitising them takes less than the launch and the
-// ramp that this saves.  Four waves per atom as in launch_mulliken, so the sums
-// are the same.
+// Up to 2^20 elements of K.  Whole steps, two launches -> one, us: b = 4 31.0 -> 26.9 at
+// 64 atoms (0.05 2^20 elements), 161 -> 156 at 400 (0.6), 315 -> 309 at 700 (1.1), 1,402 ->
+// 1,381 at 2,500 (5.0); b = 13 63.6 -> 60.7 at 20 atoms (0.06), 354 -> 348 at 100 (0.95),
+// 1,237 -> 1,222 at 250 (3.3).  One launch is 1 to 2 % faster beyond the line too, as far
+// as measured; the line keeps the form to the systems whose step is a chain of launches.
+// Four waves per atom as in launch_mulliken, so the sums are the same.
 bool hermitize_charges_form(int64_t n_atoms, int64_t nnzb, int b)
 {
     return nnzb * b * b <= ((int64_t)1 << 20) && mulliken_wide(n_atoms, b) && n_atoms > 0;

@@ -296,11 +296,14 @@ static inline unsigned xcd_grid(int64_t nblocks, int remap = 1)
 // blocks meet in the shared last-level cache; contiguous eighths measured
 // 11 % slower at b = 13).
 static int xcd_chunk() { return 128; }
-// Chunks for a launch of nwg workgroups: 128 from 16,384 workgroups on; below
-// that they leave the last round of chunks nearly empty, and chunks of 32 are
-// faster (b = 13, 512 atoms, 7,700 workgroups: U K 3.66 -> 3.42 ms; 1,000
-// atoms, 19,000 workgroups: 2.81 against 2.86 ms per real product; b = 4,
-// 7,560 atoms at R_K 8, 6,300 workgroups: U K 0.289 -> 0.279 ms).
+// Chunks for a launch of nwg workgroups: 128 from 16,384 workgroups on, 32 below,
+// where larger ones leave the last round of chunks nearly empty.  U K with chunks
+// of 32 / 128, us, at so many workgroups: b = 13 916 / 941 (4,925), 3,515 / 3,654
+// (9,683), 1,961 / 2,047 (10,654), 8,519 / 8,588 (21,861), 13,201 / 13,213 (33,490),
+// 16,762 / 16,973 (41,440); b = 4 156 / 181 (2,582), 414 / 426 (4,356), 505 / 503
+// (9,204), 1,217 / 1,246 (13,658), 2,139 / 2,109 (24,260).  Above the line the two
+// are within 1.5 % of each other.  The rule is wrong where rows are long: b = 4,
+// 2,744 atoms at R 16 (13 runs a row, 9,064 workgroups) takes 1,965 / 1,854.
 static int xcd_chunk_for(int64_t nwg) { return nwg < 16384 ? 32 : xcd_chunk(); }
 // The same deal in chunks of about as many output blocks (1,024) for a kernel
 // with `per_wg` output blocks per workgroup.
