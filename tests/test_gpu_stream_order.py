@@ -208,3 +208,58 @@ def test_a_measurement_behind_a_product_on_another_stream_waits_its_turn(call):
     assert np.array_equal(got, want)
     assert np.array_equal(rtdm.rtdm_download(ctx.h, "A", s.b), A)
     ctx.close()
+
+
+@pytest.mark.parametrize("use_graph", [0, 1])
+@pytest.mark.parametrize("capturing", [False, True])
+def test_a_product_behind_steps_on_the_null_stream_waits_its_turn(use_graph, capturing):
+    """A step held on the null stream (replayed: on the library's own), then a
+    product at once on a stream that is not in order with it, also while a third
+    stream is captured; and a step on the null stream behind that product."""
+    import torch
+    s, ctx = _b13(use_graph)
+    K0 = rtdm.rtdm_download(ctx.h, "K", s.b)
+    rtdm.rtdm_multiply(ctx.h, "A", "X", "H0")
+    A = rtdm.rtdm_download(ctx.h, "A", s.b)
+    rtdm.rtdm_step(ctx.h, 0.05, 2, 0)
+    K = rtdm.rtdm_download(ctx.h, "K", s.b)
+    rtdm.rtdm_upload(ctx.h, "K", K0)
+    c, other = torch.cuda.Stream(), torch.cuda.Stream()
+    x = torch.zeros(8, device="cuda:0")
+    torch.cuda.synchronize()
+    print(f"[gpu] steps on the null stream, product on another, graph={use_graph} capturing={capturing}", flush=True)
+    torch.cuda._sleep(HOLD)                            # torch's default stream is the null stream
+    rtdm.rtdm_step(ctx.h, 0.05, 1, 0)
+    done = torch.cuda.Event()
+    done.record()
+    if capturing:
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(other):
+            g.capture_begin()
+            x += 1
+    rtdm.rtdm_multiply_noalloc(ctx.h, "A", "X", "H0", 0, 0, 1.0, c)
+    if capturing:
+        with torch.cuda.stream(other):
+            g.capture_end()
+    held = not done.query()
+    end = torch.cuda.Event()
+    end.record(c)
+    end.synchronize()
+    assert held and done.query(), "the product did not run behind the step"
+    with torch.cuda.stream(c):
+        torch.cuda._sleep(HOLD)
+    rtdm.rtdm_multiply_noalloc(ctx.h, "A", "X", "H0", 0, 0, 1.0, c)
+    done.record(c)
+    rtdm.rtdm_step(ctx.h, 0.05, 1, 0)
+    held = not done.query()
+    end.record()
+    end.synchronize()
+    assert held and done.query(), "the step did not run behind the product"
+    torch.cuda.synchronize()
+    assert np.array_equal(rtdm.rtdm_download(ctx.h, "A", s.b), A)
+    assert np.array_equal(rtdm.rtdm_download(ctx.h, "K", s.b), K)
+    if capturing:
+        g.replay()
+        torch.cuda.synchronize()
+        assert float(x.sum()) == 8.0
+    ctx.close()
