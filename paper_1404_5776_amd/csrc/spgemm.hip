@@ -620,7 +620,8 @@ __global__ __launch_bounds__(256, MINW) void k_spgemm_q4j(
 // there: three waves per SIMD beat four by 8 % and five by 18 %, and with the
 // next group's loads issued behind this one's matrix instructions two beat
 // three by 4 %.  4,096 atoms, R 16, ms per launch, 8-byte loads at four waves
-// -> now: A tau 19.9 -> 15.7, U K 49.7 -> 45.8, W U^dagger 48.3 -> 45.7.
+// -> now (four cards): A tau 19.9 -> 15.5 to 15.8, U K 49.7 -> 44.9 to 47.6, W U^dagger
+// 48.3 -> 44.5 to 47.4.
 // Complex products have no registers to load a group ahead.
 // OUT: 0 row-major output, 1 left pairs, 2 right pairs.  u (real products,
 // nullable): u = u_sign * output (u_store) or u += u_sign * output, row-major:
