@@ -1333,15 +1333,24 @@ void drop_graph(rtdm_ctx *c)
     c->graph_multi = nullptr;
 }
 
+// W by rows, where the last step left it column-major or as left pairs.
+void w_by_rows(rtdm_ctx *c, hipStream_t s)
+{
+    if (!c->W_in_cm) return;
+    Mat &W = c->mats[RTDM_MAT_W];
+    if (c->pairs_cplx) pack_planes(c, c->Wc, W, kUnpackLeft, s);
+    else transpose_into(c, c->Wc, W, s);
+    if (!is_capturing(s)) c->W_in_cm = false;
+}
+
 // Gives the operand forms back (Kr, Bp, Lp, Ap): the products then read K, right
 // operands and, at b = 13, column-major copies as without pair layout.
 void drop_forms(rtdm_ctx *c)
 {
     drop_graph(c);
     if (c->W_in_cm && c->pairs_cplx) {
-        pack_planes(c, c->Wc, c->mats[RTDM_MAT_W], kUnpackLeft, nullptr);
+        w_by_rows(c, nullptr);
         RT_HIP(hipDeviceSynchronize());
-        c->W_in_cm = false;
     }
     c->pairs_real = c->pairs_cplx = false;
     c->Ap.re.release();
@@ -2142,11 +2151,7 @@ int rtdm_download(rtdm_ctx *c, rtdm_mat mat, void *dst, int is_device, void *str
     hipStream_t s = (hipStream_t)stream;
     Mat &M = mat == RTDM_MAT_K ? kmat(c, c->kick_sel) : c->mats[mat];
     const int64_t ne = elems(c, M);
-    if (mat == RTDM_MAT_W && c->W_in_cm) {             // the step keeps W column-major
-        if (c->pairs_cplx) pack_planes(c, c->Wc, M, kUnpackLeft, s);
-        else transpose_into(c, c->Wc, M, s);
-        c->W_in_cm = false;
-    }
+    if (mat == RTDM_MAT_W) w_by_rows(c, s);
     RT_CHECK(!(c->mixed && is_device), RTDM_E_UNSUPPORTED, "device downloads need equal block sizes");
     if (is_device) {
         launch_interleave(s, ne, M.re.p, M.cplx ? M.im.p : nullptr, (double *)dst);
@@ -3665,6 +3670,7 @@ void multiply(rtdm_ctx *c, rtdm_mat Cm, rtdm_mat Am, rtdm_mat Bm, int op_a, int 
     const bool cres = A.cplx || B.cplx || ali != 0.0;
     RT_CHECK(C.cplx || !cres, RTDM_E_UNSUPPORTED, "complex result for a real matrix slot");
     const Turn turn(c, s);
+    if (Am == RTDM_MAT_W || Bm == RTDM_MAT_W) w_by_rows(c, s);
     struct Issue {             // arithmetic and operand form of the product, whatever ends it
         rtdm_ctx *c;
         ~Issue()
