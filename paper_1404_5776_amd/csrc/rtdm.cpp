@@ -2705,6 +2705,8 @@ void after_step(StepCall &sc)
 {
     rtdm_ctx *c = sc.c;
     hipStream_t s = sc.s;
+    const int prec = all_products_prec(c);
+    c->W_in_cm = c->b == 13 && (prec == RTDM_PREC_FP64 || prec == RTDM_PREC_FP32);   // also behind a replayed step
     c->t_now = sc.t_start + (double)(sc.k + 1) * sc.dt;
     if (c->opt.unit_check_every > 0 && (c->obs_rows + 1) % c->opt.unit_check_every == 0) {
         c->prec = RTDM_PREC_FP64;               // the unitarity check stays FP64

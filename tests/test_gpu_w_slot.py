@@ -36,3 +36,20 @@ def test_a_product_reads_w_of_the_last_step(b, precision):
         got.append(rtdm.rtdm_download(ctx.h, "K", b))
         ctx.close()
     assert np.array_equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("b", [4, 13])
+def test_w_downloaded_between_replayed_steps(b):
+    """Graph steps, W, graph steps, W: each the W of the last step, as after eager steps."""
+    got = []
+    for use_graph in (0, 1):
+        ctx = _context(b, use_graph=use_graph)
+        ws = []
+        for _ in range(3):
+            rtdm.rtdm_step(ctx.h, DT, 3)
+            ws.append(rtdm.rtdm_download(ctx.h, "W", b))
+        got.append(ws)
+        ctx.close()
+    for eager, replayed in zip(*got):
+        assert np.array_equal(eager, replayed)
+    assert not np.array_equal(got[0][0], got[0][1])
