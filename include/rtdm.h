@@ -42,10 +42,10 @@
  *   order at its replays: a recorded rtdm_multiply or rtdm_multiply_noalloc uses
  *   no operand buffer of the context's; replays of any other call have to be
  *   ordered by the caller against every other call on the context.
- *   K may be written in such a graph (upload, kick, product, steps): calls after a
- *   replay see it.  Writes of S, H0, X and U are noted when the call is issued, not
- *   at its replays: steps after a replay that writes one of these may use what was
- *   derived from the old one, unless it is written again outside a graph.
+ *   Products after a replay that writes K (upload, kick, product, steps) read the
+ *   new K.  Everything else that a write brings with it is noted when the call is
+ *   issued, not at its replays: K's charges and trace, and what is derived from S,
+ *   H0, X and U.  Write such a slot outside a graph before the next step.
  */
 #ifndef RTDM_H
 #define RTDM_H
